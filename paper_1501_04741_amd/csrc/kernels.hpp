@@ -1348,11 +1348,12 @@ __global__ __launch_bounds__(256) void k_window_seed(Params<Real> p, const Real*
 
 // J of the window: glob[kNG] = (1/W) sum of the window's objectives (each slot of
 // win holds kNG sums and J); glob[0..kNG) keep the final state's sums.
-__global__ void k_window_mean(const double* __restrict__ win, int W, double* __restrict__ glob) {
+template <typename D>
+__global__ void k_window_mean(const D* __restrict__ win, int W, D* __restrict__ glob) {
   if (blockIdx.x != 0 || threadIdx.x != 0) return;
-  double J = 0.0;
+  D J = 0;
   for (int s = 0; s < W; ++s) J += win[(size_t)s * (kNG + 1) + kNG];
-  glob[kNG] = J / (double)W;
+  glob[kNG] = J / (D)W;
 }
 
 // ------------------------------------------------------------ adjoint step

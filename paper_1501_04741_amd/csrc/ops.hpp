@@ -1,0 +1,775 @@
+// Typed operations of one lattice, precision and variant: Ops<Q, QS, Real, V>
+// launches the kernels, the Run* templates are the bodies of the C ABI calls
+// (declared in context.hpp).  Only variants.hip includes this file: each
+// instantiation is a translation unit of its own.
+#pragma once
+
+#include "context.hpp"
+
+namespace lbmh {
+
+// Typed operations on one context.
+template <int Q, int QS, typename Real, int V>
+struct Ops {
+  using RealT = Real;
+  static constexpr int kQ = Q, kQS = QS;
+  static Params<Real> P(lbm_ctx* c) { return make_params<Real>(c->cfg, c->plan.N); }
+  static int batch_blocks(lbm_ctx* c, int kw, int rpb) {
+    const int rows = c->cfg.ny * c->cfg.nz;
+    return rpb == 1 ? batch_waves(c) / kw * rows : (rows + rpb - 1) / rpb;
+  }
+  // batched steps in access pattern acc (ping-pong, or one in-place phase)
+  template <bool NTV, bool MOMV>
+  static void primal_batch_acc(hipStream_t st, const BatchArgs<Real>& A, dim3 g, dim3 b, int acc) {
+    constexpr bool kLx = !(V & kVarMRT);  // the MRT kernels keep the plain access (see lx_rows)
+    if (acc == ACC_EVEN && NTV && A.nte)
+      hipLaunchKernelGGL((k_primal_batch<Q, QS, Real, V, NTV, MOMV, ACC_EVEN, true>), g, b, 0, st, A);
+    else if (acc == ACC_EVEN) hipLaunchKernelGGL((k_primal_batch<Q, QS, Real, V, NTV, MOMV, ACC_EVEN>), g, b, 0, st, A);
+    else if (acc == ACC_ODD && A.lx)
+      hipLaunchKernelGGL((k_primal_batch<Q, QS, Real, V, NTV, MOMV, ACC_ODD, false, kLx>), g, b, 0, st, A);
+    else if (acc == ACC_ODD) hipLaunchKernelGGL((k_primal_batch<Q, QS, Real, V, NTV, MOMV, ACC_ODD>), g, b, 0, st, A);
+    else if (A.lx) hipLaunchKernelGGL((k_primal_batch<Q, QS, Real, V, NTV, MOMV, ACC_PP, false, kLx>), g, b, 0, st, A);
+    else hipLaunchKernelGGL((k_primal_batch<Q, QS, Real, V, NTV, MOMV, ACC_PP>), g, b, 0, st, A);
+  }
+  static void primal_batch(hipStream_t st, const BatchArgs<Real>& A, int blocks, int acc = ACC_PP) {
+    const dim3 g(blocks), b(kWave * A.kw * A.rpb);
+    const bool mom = A.m[0] != nullptr;  // every member records, or none
+    if (A.nt) {
+      if (mom) primal_batch_acc<true, true>(st, A, g, b, acc);
+      else primal_batch_acc<true, false>(st, A, g, b, acc);
+    } else {
+      if (mom) primal_batch_acc<false, true>(st, A, g, b, acc);
+      else primal_batch_acc<false, false>(st, A, g, b, acc);
+    }
+  }
+  template <bool NTV>
+  static void adjoint_batch_acc(hipStream_t st, const BatchArgs<Real>& A, dim3 g, dim3 b, int acc) {
+    constexpr bool kLx = !(V & kVarMRT);  // the MRT kernels keep the plain access (see lx_rows)
+    if (acc == ACC_EVEN && NTV && A.nte)
+      hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, NTV, ACC_EVEN, true>), g, b, 0, st, A);
+    else if (acc == ACC_EVEN) hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, NTV, ACC_EVEN>), g, b, 0, st, A);
+    else if (acc == ACC_ODD && A.lx && A.nte)
+      hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, NTV, ACC_ODD, true, kLx>), g, b, 0, st, A);
+    else if (acc == ACC_ODD && A.lx)
+      hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, NTV, ACC_ODD, false, kLx>), g, b, 0, st, A);
+    else if (acc == ACC_ODD) hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, NTV, ACC_ODD>), g, b, 0, st, A);
+    else if (A.lx) hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, NTV, ACC_PP, false, kLx>), g, b, 0, st, A);
+    else hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, NTV, ACC_PP>), g, b, 0, st, A);
+  }
+  static void adjoint_batch(hipStream_t st, const BatchArgs<Real>& A, int blocks, int acc = ACC_PP) {
+    const dim3 g(blocks), b(kWave * A.kw * A.rpb);
+    if (A.nt) adjoint_batch_acc<true>(st, A, g, b, acc);
+    else adjoint_batch_acc<false>(st, A, g, b, acc);
+  }
+
+  // streaming stores (and cotangent loads) when the state buffers a launch touches exceed the
+  // last-level cache: ping-pong primal and adjoint 2, in-place primal 1, one-shot 4 (2 in place)
+  static bool nt(lbm_ctx* c, int buffers) { return buffers * c->plan.state_bytes > kLastLevelCacheBytes; }
+  // dynamic LDS of an LX launch: the staging runs of `states` states, one value per thread each
+  static size_t lx_bytes(const Geo& g, int states) {
+    return (size_t)states * Shifted<Q, QS>::count() * g.block.x * g.block.y * sizeof(Real);
+  }
+  // LX variant for this context and launch: rows that fit a block, and staging
+  // within 64 KB of LDS per block (the FP64 one-shot of D3Q19 + D3Q7 on 512-wide
+  // blocks would need 96 KB and keeps the plain access)
+  static bool lx(lbm_ctx* c, const Geo& g, int states) {
+    return lx_rows(c->cfg) && lx_bytes(g, states) <= 65536;
+  }
+  // access pattern of the current state buffer: ping-pong, or the in-place phase of step t
+  static int acc(lbm_ctx* c) { return c->plan.inplace ? ((c->t % 2 == 0) ? ACC_EVEN : ACC_ODD) : ACC_PP; }
+  // One in-place step from the current phase; records the moments when mom != null.
+  // Streaming stores and hints: a recorded step takes them once its state exceeds
+  // the last-level cache (plain stores: 0.819 -> 0.748 of peak, D3Q19 FP32
+  // 256x128x128), its even phase's loads only beyond twice the cache.  An
+  // unrecorded step stores plainly up to the cache size (NT stores in the odd
+  // phase cost 0.76 -> 0.73 at 128x96x96 and 0.88 -> 0.86 at 192x128x128); between
+  // one and two caches its odd (staged) phase takes NT stores and the even phase
+  // stays plain (0.787 -> 0.860 at 256x128x128; NT stores in both phases 0.741,
+  // with the even-phase load hint 0.839); beyond twice the cache it takes NT
+  // stores and hinted loads in both phases (0.662 -> 0.750 at 512x256x128, 0.668 ->
+  // 0.815 at 512x128x128; a plain even phase there 0.66 and 0.67).
+  static void primal_inplace(lbm_ctx* c, void* buf, int64_t t, void* mom) {
+    Geo g = hot_geometry(c->cfg);
+    Real* a = (Real*)buf;
+    const Real* w = (const Real*)c->w;
+    Real* m = (Real*)mom;
+    const bool even = (t % 2 == 0);
+    const bool lx = Ops::lx(c, g, 1);
+#define LBM_PI(NTV, MOMV, ACCV)                                                                                    \
+  do {                                                                                                             \
+    if (ACCV == ACC_ODD && lx)                                                                                     \
+      hipLaunchKernelGGL((k_primal_inplace<Q, QS, Real, NTV, MOMV, V, ACC_ODD, false, true>), g.grid, g.block,     \
+                         lx_bytes(g, 1), c->stream, P(c), a, w, m);                                                \
+    else                                                                                                           \
+      hipLaunchKernelGGL((k_primal_inplace<Q, QS, Real, NTV, MOMV, V, ACCV>), g.grid, g.block, 0, c->stream, P(c), \
+                         a, w, m);                                                                                 \
+  } while (0)
+    if (m && nt(c, 1)) {
+      // the even phase's loads take the streaming hint too once the state is far beyond the cache
+      if (even && c->plan.state_bytes > 2 * kLastLevelCacheBytes)
+        hipLaunchKernelGGL((k_primal_inplace<Q, QS, Real, true, true, V, ACC_EVEN, true>), g.grid, g.block, 0,
+                           c->stream, P(c), a, w, m);
+      else if (even) LBM_PI(true, true, ACC_EVEN);
+      else LBM_PI(true, true, ACC_ODD);
+    } else if (m) {
+      if (even) LBM_PI(false, true, ACC_EVEN);
+      else LBM_PI(false, true, ACC_ODD);
+    } else if (c->plan.state_bytes > 2 * kLastLevelCacheBytes) {
+      // unrecorded, state far beyond the cache: streaming stores and hinted loads in both phases
+      if (even)
+        hipLaunchKernelGGL((k_primal_inplace<Q, QS, Real, true, false, V, ACC_EVEN, true>), g.grid, g.block, 0,
+                           c->stream, P(c), a, w, m);
+      else LBM_PI(true, false, ACC_ODD);
+    } else if (nt(c, 1)) {
+      // unrecorded, state between one and two caches: streaming stores in the odd phase only
+      if (even) LBM_PI(false, false, ACC_EVEN);
+      else LBM_PI(true, false, ACC_ODD);
+    } else {
+      if (even) LBM_PI(false, false, ACC_EVEN);
+      else LBM_PI(false, false, ACC_ODD);
+    }
+#undef LBM_PI
+  }
+  static void oneshot_inplace(lbm_ctx* c, double zeta, double pen) {
+    Geo g = hot_geometry(c->cfg);
+    Real* a = (Real*)c->cur;
+    Real* l = (Real*)c->lam[0];
+    Real* w = (Real*)c->w;
+    Real* gr = (Real*)c->grad;
+    const double* gl = (const double*)c->glob;
+    const bool even = (c->t % 2 == 0);
+    const bool lx = Ops::lx(c, g, 2);
+#define LBM_OS_INPLACE(NTV, ACCV)                                                                                 \
+  do {                                                                                                            \
+    if (ACCV == ACC_ODD && lx)                                                                                    \
+      hipLaunchKernelGGL((k_oneshot_inplace<Q, QS, Real, NTV, V, ACC_ODD, true>), g.grid, g.block, lx_bytes(g, 2),  \
+                         c->stream, P(c), a, l, w, gr, gl, (Real)zeta, (Real)pen);                                \
+    else                                                                                                          \
+      hipLaunchKernelGGL((k_oneshot_inplace<Q, QS, Real, NTV, V, ACCV>), g.grid, g.block, 0, c->stream, P(c), a, l, \
+                         w, gr, gl, (Real)zeta, (Real)pen);                                                       \
+  } while (0)
+    if (nt(c, 2)) {
+      if (even) LBM_OS_INPLACE(true, ACC_EVEN);
+      else LBM_OS_INPLACE(true, ACC_ODD);
+    } else {
+      if (even) LBM_OS_INPLACE(false, ACC_EVEN);
+      else LBM_OS_INPLACE(false, ACC_ODD);
+    }
+#undef LBM_OS_INPLACE
+  }
+  static lbm_status write_static(lbm_ctx* c) {
+    static_assert(sizeof(BatchStatic<Real>) <= kDescBytes, "descriptor region too small");
+    BatchStatic<Real> h;
+    h.p = P(c);
+    h.waves = batch_waves(c);
+    hipLaunchKernelGGL((k_write_desc<Real>), dim3(1), dim3(64), 0, c->stream, h, (BatchStatic<Real>*)c->desc);
+    return launch_check(c, "descriptor upload");
+  }
+  static_assert(Mom<Q, QS, V>::N == (Q == 19 ? 3 : 2) + 1 + (QS > 0 ? ((V & kVarVD) ? QS : 1) : 0),
+                "moment count mismatch");
+  // One primal step; records the moments of the pulled state when mom != null.
+  static void primal(lbm_ctx* c, const void* src, void* dst, void* mom = nullptr) {
+    Geo g = hot_geometry(c->cfg);
+    const Real* s = (const Real*)src;
+    Real* d = (Real*)dst;
+    const Real* w = (const Real*)c->w;
+    Real* m = (Real*)mom;
+#define LBM_PP(NTV, MOMV)                                                                                     \
+  do {                                                                                                        \
+    if (Ops::lx(c, g, 1))                                                                                     \
+      hipLaunchKernelGGL((k_primal<Q, QS, Real, NTV, MOMV, V, true>), g.grid, g.block, lx_bytes(g, 1), c->stream,  \
+                         P(c), s, d, w, m);                                                                   \
+    else                                                                                                      \
+      hipLaunchKernelGGL((k_primal<Q, QS, Real, NTV, MOMV, V>), g.grid, g.block, 0, c->stream, P(c), s, d, w, m); \
+  } while (0)
+    if (nt(c, 2)) {
+      if (m) LBM_PP(true, true);
+      else LBM_PP(true, false);
+    } else {
+      if (m) LBM_PP(false, true);
+      else LBM_PP(false, false);
+    }
+#undef LBM_PP
+  }
+  static void objective(lbm_ctx* c, const void* src, double* out) {
+    double* part = c->glob + kGlobSlots;
+    hipLaunchKernelGGL((k_objective_partial<Q, QS, Real>), dim3(kObjBlocks), dim3(kObjThreads), 0, c->stream, P(c),
+                       (const Real*)src, part, acc(c));
+    hipLaunchKernelGGL((k_objective_final<Q, QS, Real>), dim3(1), dim3(64), 0, c->stream, P(c),
+                       (const double*)part, out);
+  }
+  static void seed(lbm_ctx* c, const void* src, void* lam) {
+    Geo g = node_geometry(c->cfg);
+    hipLaunchKernelGGL((k_seed<Q, QS, Real>), g.grid, g.block, 0, c->stream, P(c), (const Real*)src,
+                       (const double*)c->glob, (Real*)lam, acc(c), c->plan.inplace ? 1 : 0,
+                       1.0 / (double)c->plan.W);
+  }
+  // Window state s: its boundary sums and objective, and its inlet/outlet columns.
+  static void capture(lbm_ctx* c, const void* src, int64_t s) {
+    objective(c, src, win_glob(c, s));
+    const int n = 2 * c->cfg.ny * c->cfg.nz;
+    hipLaunchKernelGGL((k_capture_columns<Q, QS, Real>), dim3((n + 255) / 256), dim3(256), 0, c->stream, P(c),
+                       (const Real*)src, acc(c), (Real*)win_cols(c, s));
+  }
+  // lambda^n += (1/W) dJ/df^n of window state s, lambda^n in layout pattern.
+  static void window_seed(lbm_ctx* c, int64_t s, void* lam, int pattern) {
+    const int n = 2 * c->cfg.ny * c->cfg.nz;
+    hipLaunchKernelGGL((k_window_seed<Q, QS, Real>), dim3((n + 255) / 256), dim3(256), 0, c->stream, P(c),
+                       (const Real*)win_cols(c, s), (const double*)win_glob(c, s), (Real*)lam, pattern,
+                       1.0 / (double)c->plan.W);
+  }
+  // One in-place adjoint step: the cotangent buffer is in the odd-pattern layout
+  // after an even number of adjoint steps (the seed writes that layout).
+  static void adjoint_inplace(lbm_ctx* c, const void* mom, int64_t steps_done) {
+    Geo g = hot_geometry(c->cfg);
+    const Real* m = (const Real*)mom;
+    Real* l = (Real*)c->lam[0];
+    const Real* w = (const Real*)c->w;
+    Real* gr = (Real*)c->grad;
+    const bool odd = (steps_done % 2 == 0);
+    const bool lx = Ops::lx(c, g, 1);
+    const bool far = c->plan.state_bytes > 2 * kLastLevelCacheBytes;  // streaming hints on the staged accesses
+#define LBM_AI(NTV, ACCV)                                                                                         \
+  do {                                                                                                            \
+    if (ACCV == ACC_ODD && lx && far)                                                                             \
+      hipLaunchKernelGGL((k_adjoint_inplace<Q, QS, Real, NTV, V, ACC_ODD, true, true>), g.grid, g.block,          \
+                         lx_bytes(g, 1), c->stream, P(c), m, l, w, gr);                                           \
+    else if (ACCV == ACC_ODD && lx)                                                                               \
+      hipLaunchKernelGGL((k_adjoint_inplace<Q, QS, Real, NTV, V, ACC_ODD, false, true>), g.grid, g.block,         \
+                         lx_bytes(g, 1), c->stream, P(c), m, l, w, gr);                                           \
+    else                                                                                                          \
+      hipLaunchKernelGGL((k_adjoint_inplace<Q, QS, Real, NTV, V, ACCV>), g.grid, g.block, 0, c->stream, P(c), m, l, \
+                         w, gr);                                                                                  \
+  } while (0)
+    // streaming stores and hints whatever the state size: the adjoint also streams a moment set per
+    // step, and a cotangent state that fits the last-level cache gains nothing from staying there
+    // (192x96x96 D3Q19 FP32, 134 MB: 0.769 -> 0.836 of HBM peak; 128x96x96: 0.738 -> 0.771)
+    if (odd) LBM_AI(true, ACC_ODD);
+    else if (c->plan.state_bytes > 2 * kLastLevelCacheBytes)  // even-phase hint far beyond the cache
+      hipLaunchKernelGGL((k_adjoint_inplace<Q, QS, Real, true, V, ACC_EVEN, true>), g.grid, g.block, 0, c->stream,
+                         P(c), m, l, w, gr);
+    else LBM_AI(true, ACC_EVEN);
+#undef LBM_AI
+  }
+  static void adjoint(lbm_ctx* c, const void* mom, const void* lin, void* lout) {
+    Geo g = hot_geometry(c->cfg);
+    const Real *m = (const Real*)mom, *li = (const Real*)lin, *w = (const Real*)c->w;
+    Real *lo = (Real*)lout, *gr = (Real*)c->grad;
+    const bool lx = Ops::lx(c, g, 1);
+    // streaming whatever the state size, as the in-place adjoint
+    if (lx)
+      hipLaunchKernelGGL((k_adjoint<Q, QS, Real, true, V, true>), g.grid, g.block, lx_bytes(g, 1), c->stream, P(c), m,
+                         li, lo, w, gr);
+    else
+      hipLaunchKernelGGL((k_adjoint<Q, QS, Real, true, V>), g.grid, g.block, 0, c->stream, P(c), m, li, lo, w, gr);
+  }
+  static void oneshot(lbm_ctx* c, const void* src, void* dst, const void* lin, void* lout, double zeta,
+                      double pen) {
+    Geo g = hot_geometry(c->cfg);
+    const Real *s = (const Real*)src, *li = (const Real*)lin;
+    Real *d = (Real*)dst, *lo = (Real*)lout, *w = (Real*)c->w, *gr = (Real*)c->grad;
+    const double* gl = (const double*)c->glob;
+    const bool lx = Ops::lx(c, g, 2);
+#define LBM_OS(NTV, LXV)                                                                                   \
+  hipLaunchKernelGGL((k_oneshot<Q, QS, Real, NTV, V, LXV>), g.grid, g.block, LXV ? lx_bytes(g, 2) : 0, c->stream, \
+                     P(c), s, d, li, lo, w, gr, gl, (Real)zeta, (Real)pen)
+    if (nt(c, 4)) {
+      if (lx) LBM_OS(true, true);
+      else LBM_OS(true, false);
+    } else {
+      if (lx) LBM_OS(false, true);
+      else LBM_OS(false, false);
+    }
+#undef LBM_OS
+  }
+  static void get_adjoint(lbm_ctx* c, const void* lam, double* lf, double* lg, int pattern) {
+    Geo g = node_geometry(c->cfg);
+    hipLaunchKernelGGL((k_get_adjoint<Q, QS, Real>), g.grid, g.block, 0, c->stream, P(c), (const Real*)lam, lf, lg,
+                       pattern);
+  }
+  static void fields(lbm_ctx* c, const void* src, double* rho, double* u, double* s) {
+    Geo g = node_geometry(c->cfg);
+    hipLaunchKernelGGL((k_fields<Q, QS, Real>), g.grid, g.block, 0, c->stream, P(c), (const Real*)src, rho, u, s,
+                       acc(c));
+  }
+  static void get_state(lbm_ctx* c, const void* src, double* f, double* gg) {
+    Geo g = node_geometry(c->cfg);
+    hipLaunchKernelGGL((k_get_state<Q, QS, Real>), g.grid, g.block, 0, c->stream, P(c), (const Real*)src, f, gg,
+                       acc(c));
+  }
+  static void set_state(lbm_ctx* c, const double* f, const double* gg, void* dst) {
+    Geo g = node_geometry(c->cfg);
+    hipLaunchKernelGGL((k_set_state<Q, QS, Real>), g.grid, g.block, 0, c->stream, P(c), f, gg, (Real*)dst,
+                       c->plan.inplace ? ACC_EVEN : ACC_PP);
+  }
+  static void maps(lbm_ctx* c, uint8_t* mask, int64_t* src) {
+    Geo g = node_geometry(c->cfg);
+    hipLaunchKernelGGL((k_maps<Q, QS, Real>), g.grid, g.block, 0, c->stream, P(c), mask, src);
+  }
+  static void fill(lbm_ctx* c, void* a, size_t n) {
+    hipLaunchKernelGGL((k_fill<Real>), flat_grid(n), dim3(256), 0, c->stream, (Real*)a, n, Real(0));
+  }
+  static void copy(lbm_ctx* c, const void* a, void* b, size_t n) {
+    hipLaunchKernelGGL((k_copy<Real>), flat_grid(n), dim3(256), 0, c->stream, (const Real*)a, (Real*)b, n);
+  }
+  // node array: compact ABI layout -> padded workspace layout, and back
+  static void node_in(lbm_ctx* c, const void* a, void* b) {
+    Geo g = node_geometry(c->cfg);
+    hipLaunchKernelGGL((k_node_in<Real>), g.grid, g.block, 0, c->stream, P(c), (const Real*)a, (Real*)b);
+  }
+  static void grad_penalty(lbm_ctx* c, double pen, void* b) {
+    Geo g = node_geometry(c->cfg);
+    hipLaunchKernelGGL((k_grad_penalty<Real>), g.grid, g.block, 0, c->stream, P(c), (const Real*)c->grad,
+                       (const Real*)c->w, (Real)pen, (Real*)b);
+  }
+  static void node_out(lbm_ctx* c, const void* a, void* b) {
+    Geo g = node_geometry(c->cfg);
+    hipLaunchKernelGGL((k_node_out<Real>), g.grid, g.block, 0, c->stream, P(c), (const Real*)a, (Real*)b);
+  }
+};
+
+// Time-averaged objective: capture the state just produced (time t) when it is
+// the next state of the window [N - W + 1, N] of a run that started at t = 0.
+template <class O>
+void capture_window(lbm_ctx* c) {
+  const int64_t W = c->plan.W, first = c->cfg.nsteps - W + 1;
+  if (W > 1 && c->t >= first && c->t - first == c->win_count) {
+    O::capture(c, c->cur, c->win_count);
+    ++c->win_count;
+  }
+}
+
+template <class O>
+lbm_status RunPrimal<O>::run(lbm_ctx* c, int64_t nsteps, int record) {
+  // A recorded run keeps the moments of the horizon's last segment only (all of
+  // them in a store-all plan): the backward recomputes every earlier segment
+  // from its checkpoint before it reads that segment's moments.
+  const int64_t keep_from = last_segment(c) * c->plan.C;
+  if (c->plan.inplace) {
+    const bool ckpts = record && c->work != ckpt_slot(c, 0);  // checkpointed plan (C < N)
+    for (int64_t i = 0; i < nsteps; ++i) {
+      if (ckpts && c->t % c->plan.C == 0)  // the state at t = sC, in its phase's layout
+        O::copy(c, c->work, ckpt_slot(c, c->t / c->plan.C), (size_t)c->plan.QT * c->plan.Np);
+      O::primal_inplace(c, c->work, c->t, record && c->t >= keep_from ? mom_slot(c, c->t) : nullptr);
+      ++c->t;
+      capture_window<O>(c);
+    }
+    return launch_check(c, "in-place primal step");
+  }
+  for (int64_t i = 0; i < nsteps; ++i) {
+    void* src = c->cur;
+    void* dst = record ? rec_dst(c, c->t) : other_pp(c, c->cur);
+    O::primal(c, src, dst, record && c->t >= keep_from ? mom_slot(c, c->t) : nullptr);
+    c->cur = dst;
+    ++c->t;
+    capture_window<O>(c);
+  }
+  return launch_check(c, "primal step");
+}
+
+template <class O>
+lbm_status RunObjective<O>::run(lbm_ctx* c, double* J_dev) {
+  O::objective(c, c->cur, c->glob);
+  if (window_complete(c))
+    hipLaunchKernelGGL((k_window_mean<double>), dim3(1), dim3(64), 0, c->stream, (const double*)c->win, (int)c->plan.W,
+                       c->glob);
+  if (J_dev) {
+    hipError_t e = hipMemcpyAsync(J_dev, c->glob + kNG, sizeof(double), hipMemcpyDeviceToDevice, c->stream);
+    if (e != hipSuccess) return fail(c, LBM_EHIP, "objective copy: %s", hipGetErrorString(e));
+  }
+  return launch_check(c, "objective");
+}
+
+// Recompute segment s from its checkpoint: steps k = sC .. min(sC + C, N) - 1,
+// recording their moments (the states themselves go through the ping-pong).
+template <class O>
+void recompute_segment(lbm_ctx* c, int64_t s) {
+  Range r("lbm recompute segment");
+  const int64_t C = c->plan.C;
+  const int64_t end = std::min<int64_t>(s * C + C, c->rec_len);
+  const void* src = ckpt_slot(c, s);
+  for (int64_t k = s * C; k < end; ++k) {
+    void* dst = other_pp(c, src);
+    O::primal(c, src, dst, mom_slot(c, k));
+    src = dst;
+  }
+  c->mom_seg = s;
+}
+
+// In-place plan: recompute segment s inside its own checkpoint slot (its last
+// use), recording the moments of steps sC .. min(sC + C, N) - 1; step k runs in
+// the access pattern of its phase k mod 2, the layout the slot was saved in.
+template <class O>
+void recompute_segment_inplace(lbm_ctx* c, int64_t s) {
+  Range r("lbm recompute segment (in place)");
+  const int64_t C = c->plan.C;
+  const int64_t end = std::min<int64_t>(s * C + C, c->rec_len);
+  void* buf = ckpt_slot(c, s);
+  for (int64_t k = s * C; k < end; ++k) O::primal_inplace(c, buf, k, mom_slot(c, k));
+  c->mom_seg = s;
+}
+
+// Seeds lambda^N = dJ/df^N and zeroes the gradient (first adjoint call).
+template <class O>
+void start_adjoint(lbm_ctx* c) {
+  const int64_t C = c->plan.C;
+  O::objective(c, c->cur, c->glob);
+  O::seed(c, c->cur, c->lam[0]);
+  O::fill(c, c->grad, (size_t)c->plan.Np);
+  c->lam_cur = 0;
+  c->t_adj = c->rec_len;
+  // the recorded run's moments are held when it ended in the horizon's last segment
+  // (a batched run records every step, so this can miss a segment it holds: that
+  // segment is then recomputed, with the same result)
+  const int64_t s = c->rec_len > 0 ? (c->rec_len - 1) / C : -1;
+  c->mom_seg = s == last_segment(c) ? s : -1;
+  c->adj_started = true;
+}
+
+template <class O>
+lbm_status RunAdjoint<O>::run(lbm_ctx* c, int64_t nsteps) {
+  const int64_t C = c->plan.C;
+  // window states n < N whose objective terms enter lambda^n (none unless W > 1)
+  const int64_t first = c->plan.W > 1 ? c->cfg.nsteps - c->plan.W + 1 : INT64_MAX;
+  if (!c->adj_started) start_adjoint<O>(c);
+  if (c->plan.inplace) {  // store-all never recomputes; C < N recomputes each segment in place
+    for (int64_t i = 0; i < nsteps; ++i) {
+      const int64_t n = c->t_adj - 1;
+      const int64_t s = n / C;
+      if (s != c->mom_seg) recompute_segment_inplace<O>(c, s);
+      O::adjoint_inplace(c, mom_slot(c, n), c->rec_len - c->t_adj);
+      --c->t_adj;
+      if (n >= first)  // lambda^n now in the layout of its step count
+        O::window_seed(c, n - first, c->lam[0], ((c->rec_len - c->t_adj) % 2 == 0) ? ACC_ODD : ACC_EVEN);
+    }
+    return launch_check(c, "in-place adjoint step");
+  }
+  for (int64_t i = 0; i < nsteps; ++i) {
+    const int64_t n = c->t_adj - 1;
+    const int64_t s = n / C;
+    if (s != c->mom_seg) recompute_segment<O>(c, s);
+    O::adjoint(c, mom_slot(c, n), c->lam[c->lam_cur], c->lam[1 - c->lam_cur]);
+    c->lam_cur ^= 1;
+    --c->t_adj;
+    if (n >= first) O::window_seed(c, n - first, c->lam[c->lam_cur], ACC_PP);
+  }
+  return launch_check(c, "adjoint step");
+}
+
+template <class O>
+lbm_status RunReset<O>::run(lbm_ctx* c) {
+  O::fill(c, initial_buffer(c), (size_t)c->plan.QT * c->plan.Np);
+  return launch_check(c, "reset");
+}
+
+template <class O>
+lbm_status RunSetState<O>::run(lbm_ctx* c, const double* f, const double* g) {
+  O::set_state(c, f, g, initial_buffer(c));
+  return launch_check(c, "set_state");
+}
+
+template <class O>
+lbm_status RunGradient<O>::run(lbm_ctx* c, void* out) {
+  O::node_out(c, c->grad, out);
+  return launch_check(c, "gradient");
+}
+
+template <class O>
+lbm_status RunGradientPenalty<O>::run(lbm_ctx* c, double pen, void* out) {
+  O::grad_penalty(c, pen, out);
+  return launch_check(c, "gradient_penalty");
+}
+
+template <class O>
+lbm_status RunFields<O>::run(lbm_ctx* c, double* rho, double* u, double* s) {
+  O::fields(c, c->cur, rho, u, s);
+  return launch_check(c, "fields");
+}
+
+template <class O>
+lbm_status RunGetState<O>::run(lbm_ctx* c, double* f, double* g) {
+  O::get_state(c, c->cur, f, g);
+  return launch_check(c, "get_state");
+}
+
+template <class O>
+lbm_status RunGetAdjoint<O>::run(lbm_ctx* c, double* lf, double* lg) {
+  // the one-shot's in-place buffer follows the primal's phase; the unsteady adjoint's
+  // alternates from the seed's layout (odd pattern after an even number of steps)
+  int pattern = c->adj_started ? ACC_PP : O::acc(c);
+  if (c->plan.inplace && c->adj_started) pattern = ((c->rec_len - c->t_adj) % 2 == 0) ? ACC_ODD : ACC_EVEN;
+  O::get_adjoint(c, c->lam[c->lam_cur], lf, c->plan.QS ? lg : nullptr, pattern);
+  return launch_check(c, "get_adjoint");
+}
+
+template <class O>
+lbm_status RunMaps<O>::run(lbm_ctx* c, uint8_t* mask, int64_t* src) {
+  O::maps(c, mask, src);
+  return launch_check(c, "export_maps");
+}
+
+template <class O>
+lbm_status RunSetDesign<O>::run(lbm_ctx* c, const void* w) {
+  O::node_in(c, w, c->w);
+  return launch_check(c, "set_design");
+}
+
+// One-shot iterations: each is [objective sums of f^n when the seed depends
+// on them] + one fused k_oneshot launch.  The first call zeroes lambda.
+template <class O>
+lbm_status RunOneshot<O>::run(lbm_ctx* c, int64_t nsteps, double zeta, double pen) {
+  if (!c->os_active) {
+    O::fill(c, c->lam[0], (size_t)c->plan.QT * c->plan.Np);
+    c->lam_cur = 0;
+    O::objective(c, c->cur, c->glob);
+    c->os_active = true;
+    c->rec_open = false;
+  }
+  // the variance term's source depends on the current outlet mean: refresh the sums every iteration
+  const bool state_dependent_seed = (c->cfg.c_var != 0.0);
+  for (int64_t i = 0; i < nsteps; ++i) {
+    if (state_dependent_seed) O::objective(c, c->cur, c->glob);
+    if (c->plan.inplace) {
+      O::oneshot_inplace(c, zeta, pen);
+      ++c->t;
+      continue;
+    }
+    void* dst = (c->cur == c->pp[0]) ? c->pp[1] : c->pp[0];
+    O::oneshot(c, c->cur, dst, c->lam[c->lam_cur], c->lam[1 - c->lam_cur], zeta, pen);
+    c->cur = dst;
+    c->lam_cur ^= 1;
+    ++c->t;
+  }
+  return launch_check(c, "one-shot step");
+}
+
+template <class O>
+lbm_status RunGetDesign<O>::run(lbm_ctx* c, void* out) {
+  O::node_out(c, c->w, out);
+  return launch_check(c, "get_design");
+}
+
+template <class O>
+lbm_status RunWriteStatic<O>::run(lbm_ctx* c) { return O::write_static(c); }
+
+// Batched primal steps: one launch per step covers every context.
+// In place: per step, the checkpoint copies of members at t = sC (checkpointed
+// plans), then one launch per phase among the members (two when their
+// parities differ), each member's buffer read and rewritten in place.
+template <class O>
+lbm_status primal_batch_inplace(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64_t nsteps, int record) {
+  using Real = typename O::RealT;
+  BatchArgs<Real> A;
+  std::memset(&A, 0, sizeof A);
+  for (int64_t i = 0; i < nsteps; ++i) {
+    for (int k = 0; k < n; ++k) {
+      lbm_ctx* c = cs[k];
+      const bool ckpts = record && c->work != ckpt_slot(c, 0);  // checkpointed plan (C < N)
+      if (ckpts && c->t % c->plan.C == 0)
+        O::copy(c, c->work, ckpt_slot(c, c->t / c->plan.C), (size_t)c->plan.QT * c->plan.Np);
+    }
+    for (int phase = 0; phase < 2; ++phase) {
+      lbm_ctx* mem[kBatchMax];
+      int nm = 0;
+      for (int k = 0; k < n; ++k)
+        if (cs[k]->t % 2 == phase) mem[nm++] = cs[k];
+      if (nm == 0) continue;
+      A.n = nm;
+      A.kw = batch_block_waves(mem, nm);
+      A.rpb = batch_rows_per_block(mem, nm, A.kw);
+      A.lx = batch_lx(mem, nm, A.kw);
+      batch_nt_inplace(mem, nm, !record, phase == 1, &A.nt, &A.nte);
+      int total = 0;
+      for (int k = 0; k < nm; ++k) {
+        lbm_ctx* c = mem[k];
+        A.start[k] = total;
+        A.st[k] = (const BatchStatic<Real>*)c->desc;
+        A.w[k] = (const Real*)c->w;
+        A.g[k] = (Real*)c->grad;
+        A.a[k] = (const Real*)c->work;
+        A.b[k] = nullptr;
+        A.c[k] = (Real*)c->work;
+        A.m[k] = record ? (Real*)mom_slot(c, c->t) : nullptr;
+        total += O::batch_blocks(c, A.kw, A.rpb);
+      }
+      A.start[nm] = total;
+      O::primal_batch(c0->stream, A, total, phase == 0 ? ACC_EVEN : ACC_ODD);
+    }
+    for (int k = 0; k < n; ++k) ++cs[k]->t;
+  }
+  return launch_check(c0, "batched in-place primal step");
+}
+
+template <class O>
+lbm_status RunPrimalBatch<O>::run(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64_t nsteps, int record) {
+  using Real = typename O::RealT;
+  if (c0->plan.inplace) return primal_batch_inplace<O>(c0, cs, n, nsteps, record);
+  BatchArgs<Real> A;
+  std::memset(&A, 0, sizeof A);
+  A.n = n;
+  A.kw = batch_block_waves(cs, n);
+  A.rpb = batch_rows_per_block(cs, n, A.kw);
+  A.lx = batch_lx(cs, n, A.kw);
+  A.nt = batch_nt(cs, n);
+  for (int64_t i = 0; i < nsteps; ++i) {
+    int total = 0;
+    for (int k = 0; k < n; ++k) {
+      lbm_ctx* c = cs[k];
+      void* dst = record ? rec_dst(c, c->t) : other_pp(c, c->cur);
+      A.start[k] = total;
+      A.st[k] = (const BatchStatic<Real>*)c->desc;
+      A.w[k] = (const Real*)c->w;
+      A.g[k] = (Real*)c->grad;
+      A.a[k] = (const Real*)c->cur;
+      A.b[k] = nullptr;
+      A.c[k] = (Real*)dst;
+      A.m[k] = record ? (Real*)mom_slot(c, c->t) : nullptr;
+      total += O::batch_blocks(c, A.kw, A.rpb);
+      c->cur = dst;
+      ++c->t;
+    }
+    A.start[n] = total;
+    O::primal_batch(c0->stream, A, total);
+  }
+  return launch_check(c0, "batched primal step");
+}
+
+// Batched adjoint steps.  Contexts that still have to be seeded are seeded
+// first; before each reverse step, the contexts whose next step lies in a
+// segment whose moments are not held recompute it, batched together.
+// In place: members whose next step lies in a segment whose moments are not
+// held recompute it inside its checkpoint (single-context launches); then one
+// launch per cotangent pattern among the members.
+template <class O>
+lbm_status adjoint_batch_inplace(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64_t nsteps) {
+  using Real = typename O::RealT;
+  BatchArgs<Real> A;
+  std::memset(&A, 0, sizeof A);
+  for (int64_t i = 0; i < nsteps; ++i) {
+    for (int k = 0; k < n; ++k) {
+      lbm_ctx* c = cs[k];
+      const int64_t s = (c->t_adj - 1) / c->plan.C;
+      if (s != c->mom_seg) recompute_segment_inplace<O>(c, s);
+    }
+    for (int odd = 0; odd < 2; ++odd) {
+      lbm_ctx* mem[kBatchMax];
+      int nm = 0;
+      for (int k = 0; k < n; ++k)  // the cotangent is in the odd-pattern layout after an even step count
+        if (((cs[k]->rec_len - cs[k]->t_adj) % 2 == 0) == (odd == 1)) mem[nm++] = cs[k];
+      if (nm == 0) continue;
+      A.n = nm;
+      A.kw = batch_block_waves(mem, nm);
+      A.rpb = batch_rows_per_block(mem, nm, A.kw);
+      A.lx = batch_lx(mem, nm, A.kw);
+      batch_nt_inplace(mem, nm, false, false, &A.nt, &A.nte);
+      A.nt = 1;  // the adjoint streams whatever the state size (see Ops::adjoint_inplace)
+      int total = 0;
+      for (int k = 0; k < nm; ++k) {
+        lbm_ctx* c = mem[k];
+        A.start[k] = total;
+        A.st[k] = (const BatchStatic<Real>*)c->desc;
+        A.w[k] = (const Real*)c->w;
+        A.g[k] = (Real*)c->grad;
+        A.a[k] = (const Real*)mom_slot(c, c->t_adj - 1);
+        A.m[k] = nullptr;
+        A.b[k] = (const Real*)c->lam[0];
+        A.c[k] = (Real*)c->lam[0];
+        total += O::batch_blocks(c, A.kw, A.rpb);
+      }
+      A.start[nm] = total;
+      O::adjoint_batch(c0->stream, A, total, odd ? ACC_ODD : ACC_EVEN);
+    }
+    for (int k = 0; k < n; ++k) --cs[k]->t_adj;
+  }
+  return launch_check(c0, "batched in-place adjoint step");
+}
+
+template <class O>
+lbm_status RunAdjointBatch<O>::run(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64_t nsteps) {
+  using Real = typename O::RealT;
+  for (int k = 0; k < n; ++k)
+    if (!cs[k]->adj_started) start_adjoint<O>(cs[k]);
+  if (c0->plan.inplace) return adjoint_batch_inplace<O>(c0, cs, n, nsteps);
+  BatchArgs<Real> A;
+  std::memset(&A, 0, sizeof A);
+  for (int64_t i = 0; i < nsteps; ++i) {
+    // segment recomputes
+    lbm_ctx* need[kBatchMax];
+    int64_t first[kBatchMax], last[kBatchMax], seg[kBatchMax];
+    const void* src[kBatchMax];
+    int nn = 0;
+    int64_t longest = 0;
+    for (int k = 0; k < n; ++k) {
+      lbm_ctx* c = cs[k];
+      const int64_t C = c->plan.C;
+      const int64_t s = (c->t_adj - 1) / C;
+      if (s == c->mom_seg) continue;
+      need[nn] = c;
+      seg[nn] = s;
+      first[nn] = s * C;
+      last[nn] = std::min<int64_t>(s * C + C, c->rec_len) - 1;
+      src[nn] = ckpt_slot(c, s);
+      longest = std::max<int64_t>(longest, last[nn] - first[nn] + 1);
+      ++nn;
+    }
+    for (int64_t r = 0; r < longest; ++r) {
+      lbm_ctx* mem[kBatchMax];  // the contexts with a recompute step r left
+      int nm = 0;
+      for (int q = 0; q < nn; ++q)
+        if (first[q] + r <= last[q]) mem[nm++] = need[q];
+      A.kw = batch_block_waves(mem, nm);
+      A.rpb = batch_rows_per_block(mem, nm, A.kw);
+      A.lx = batch_lx(mem, nm, A.kw);
+      A.nt = batch_nt(mem, nm);
+      int m = 0, total = 0;
+      for (int q = 0; q < nn; ++q) {
+        const int64_t kk = first[q] + r;
+        if (kk > last[q]) continue;
+        lbm_ctx* c = need[q];
+        void* dst = other_pp(c, src[q]);
+        A.start[m] = total;
+        A.st[m] = (const BatchStatic<Real>*)c->desc;
+        A.w[m] = (const Real*)c->w;
+        A.g[m] = (Real*)c->grad;
+        A.a[m] = (const Real*)src[q];
+        A.b[m] = nullptr;
+        A.c[m] = (Real*)dst;
+        A.m[m] = (Real*)mom_slot(c, kk);
+        total += O::batch_blocks(c, A.kw, A.rpb);
+        src[q] = dst;
+        ++m;
+      }
+      A.n = m;
+      A.start[m] = total;
+      O::primal_batch(c0->stream, A, total);
+    }
+    for (int q = 0; q < nn; ++q) need[q]->mom_seg = seg[q];
+    // one reverse step for every context
+    int total = 0;
+    A.n = n;
+    A.kw = batch_block_waves(cs, n);
+    A.rpb = batch_rows_per_block(cs, n, A.kw);
+    A.lx = batch_lx(cs, n, A.kw);
+    A.nt = 1;  // the adjoint streams whatever the state size (see Ops::adjoint_inplace)
+    for (int k = 0; k < n; ++k) {
+      lbm_ctx* c = cs[k];
+      const int64_t nstep = c->t_adj - 1;
+      A.start[k] = total;
+      A.st[k] = (const BatchStatic<Real>*)c->desc;
+      A.w[k] = (const Real*)c->w;
+      A.g[k] = (Real*)c->grad;
+      A.a[k] = (const Real*)mom_slot(c, nstep);
+      A.m[k] = nullptr;
+      A.b[k] = (const Real*)c->lam[c->lam_cur];
+      A.c[k] = (Real*)c->lam[1 - c->lam_cur];
+      total += O::batch_blocks(c, A.kw, A.rpb);
+      c->lam_cur ^= 1;
+      --c->t_adj;
+    }
+    A.start[n] = total;
+    O::adjoint_batch(c0->stream, A, total);
+  }
+  return launch_check(c0, "batched adjoint step");
+}
+
+}  // namespace lbmh
