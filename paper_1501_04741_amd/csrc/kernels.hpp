@@ -32,11 +32,14 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "lattice.hpp"
 
 namespace lbmk {
 
-enum : int { INTERIOR = 0, WALL = 1, INLET = 2, OUTLET = 3 };
+// PAD: lanes beyond the row (staged kernels keep them for the barriers).
+enum : int { INTERIOR = 0, WALL = 1, INLET = 2, OUTLET = 3, PAD = 4 };
 enum : int { G_POWER = 0, G_RAMP = 1 };
 enum : int { S_ADIABATIC = 0, S_DIRICHLET = 1 };
 enum : int { IN_VELOCITY = 0, IN_PRESSURE = 1 };
@@ -81,19 +84,23 @@ __device__ __forceinline__ int node_class(const P& p, int x, int y, int z, bool 
 // Wrapped neighbour coordinates for s in {-1, 0, +1}: X[s+1] = (x+s) mod nx,
 // Yr[s+1] = (y+s) mod ny, Zr[s+1] = ny*((z+s) mod nz); a row index is Yr + Zr.
 // y and z are block-uniform, so the row parts live in scalar registers.
+// O[s+1] is X[s+1] in bytes of the state's type.
 struct Nbr {
   int nx, pitch;
   int X[3], Yr[3], Zr[3];
+  unsigned O[3];
 };
 
-template <typename P>
-__device__ __forceinline__ Nbr make_nbr(const P& p, int x, int y, int z) {
+template <typename Real>
+__device__ __forceinline__ Nbr make_nbr(const Params<Real>& p, int x, int y, int z) {
   Nbr b;
   b.nx = p.nx;
   b.pitch = p.pitch;
   b.X[0] = (x == 0) ? p.nx - 1 : x - 1;
   b.X[1] = x;
   b.X[2] = (x == p.nx - 1) ? 0 : x + 1;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) b.O[k] = (unsigned)b.X[k] * (unsigned)sizeof(Real);
   b.Yr[0] = (y == 0) ? p.ny - 1 : y - 1;
   b.Yr[1] = y;
   b.Yr[2] = (y == p.ny - 1) ? 0 : y + 1;
@@ -129,6 +136,55 @@ __device__ __forceinline__ int own_addr(const Nbr& b, int j) {
   return ((b.Yr[1] + b.Zr[1]) * QT + j) * b.pitch + b.X[1];
 }
 
+// The same addresses as pointers for the hot kernels: the run (row, slot) is
+// wave-uniform, so its address is 64-bit scalar arithmetic and the lane adds one
+// 32-bit byte offset that all accesses share (global_load with a scalar base).
+// Taking the address through readfirstlane (no code on a scalar value) keeps the
+// compiler from adding the lane first, which costs a
+// 64-bit vector add (with an int index also a sign extension) per access: 126 of
+// the 570 VALU instructions of a D3Q19 primal wave.
+template <typename R>
+using Global = __attribute__((address_space(1))) R*;
+
+template <typename R>
+__device__ __forceinline__ Global<R> lane_at(R* run, unsigned bytes) {
+  using C = std::conditional_t<std::is_const<R>::value, const char, char>;
+  const uint64_t v = reinterpret_cast<uint64_t>(run);
+  const uint64_t u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v) |
+                     (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32;
+  return (Global<R>)((Global<C>)u + bytes);
+}
+template <int QT, typename R>
+__device__ __forceinline__ R* run_at(R* a, const Nbr& b, int jj, int dy, int dz) {
+  return a + (size_t)(unsigned)(((b.Yr[1 + dy] + b.Zr[1 + dz]) * QT + jj) * b.pitch);
+}
+template <int QT, typename R>
+__device__ __forceinline__ Global<R> pull_at(R* a, const Nbr& b, int j, int ex, int ey, int ez) {
+  return lane_at(run_at<QT>(a, b, j, -ey, -ez), b.O[1 - ex]);
+}
+template <int QT, typename R>
+__device__ __forceinline__ Global<R> push_at(R* a, const Nbr& b, int j, int ex, int ey, int ez) {
+  return lane_at(run_at<QT>(a, b, j, ey, ez), b.O[1 + ex]);
+}
+template <int QT, typename R>
+__device__ __forceinline__ Global<R> own_at(R* a, const Nbr& b, int j) {
+  return lane_at(run_at<QT>(a, b, j, 0, 0), b.O[1]);
+}
+// The neighbourhood with its lane offsets made values of the current basic block:
+// the scalar-base form of an access is only selected where the 32-bit offset (and
+// not its extension to 64 bits from an earlier block) is in sight.
+__device__ __forceinline__ Nbr here(const Nbr& b) {
+  Nbr c = b;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) asm("" : "+v"(c.O[k]));
+  return c;
+}
+// The node's value in a padded node array (w, grad, one moment plane).
+template <typename R>
+__device__ __forceinline__ Global<R> node_at(R* a, const Nbr& b) {
+  return lane_at(a + (size_t)(unsigned)((b.Yr[1] + b.Zr[1]) * b.pitch), b.O[1]);
+}
+
 // Position of the calling thread in the hot kernels' launch geometry: blocks
 // of blockDim.x = 64k threads along x (a multiple of the wave) and blockDim.y
 // rows, grid (ceil(nx / blockDim.x), ceil(ny / blockDim.y), nz).  A wave never
@@ -145,7 +201,7 @@ __device__ __forceinline__ bool hot_pos(const P& p, int& x, int& y, int& z) {
 // Streaming stores: non-temporal when the state is too large to be re-read
 // from the last-level cache by the next launch.
 template <bool NT, typename Real>
-__device__ __forceinline__ void put(Real* p, Real v) {
+__device__ __forceinline__ void put(Global<Real> p, Real v) {
   if constexpr (NT) {
     __builtin_nontemporal_store(v, p);
   } else {
@@ -167,7 +223,7 @@ __device__ __forceinline__ void put(Real* p, Real v) {
 // a run-time flag, even one that folds to a constant after unrolling, lets the
 // compiler merge the hinted and plain load of the same address and drop the hint.
 template <bool NT, typename Real>
-__device__ __forceinline__ Real get(const Real* p) {
+__device__ __forceinline__ Real get(Global<const Real> p) {
   if constexpr (NT) {
     return __builtin_nontemporal_load(p);
   } else {
@@ -260,73 +316,64 @@ __device__ __forceinline__ void load_state(const Real* a, const Nbr& b, Real (&f
   if constexpr (ACC == ACC_PP) {
 #pragma unroll
     for (int j = 0; j < Q; ++j)
-      if (L::ex(j) == 0) f[j] = get<NT>(a + pull_addr<QT>(b, j, L::ex(j), L::ey(j), L::ez(j)));
+      if (L::ex(j) == 0) f[j] = get<NT>(pull_at<QT>(a, b, j, L::ex(j), L::ey(j), L::ez(j)));
 #pragma unroll
     for (int j = 0; j < Q; ++j)
-      if (L::ex(j) != 0) f[j] = a[pull_addr<QT>(b, j, L::ex(j), L::ey(j), L::ez(j))];
+      if (L::ex(j) != 0) f[j] = *pull_at<QT>(a, b, j, L::ex(j), L::ey(j), L::ez(j));
 #pragma unroll
     for (int i = 0; i < QS; ++i)
-      if (S::ex(i) == 0) g[i] = get<NT>(a + pull_addr<QT>(b, Q + i, S::ex(i), S::ey(i), S::ez(i)));
+      if (S::ex(i) == 0) g[i] = get<NT>(pull_at<QT>(a, b, Q + i, S::ex(i), S::ey(i), S::ez(i)));
 #pragma unroll
     for (int i = 0; i < QS; ++i)
-      if (S::ex(i) != 0) g[i] = a[pull_addr<QT>(b, Q + i, S::ex(i), S::ey(i), S::ez(i))];
+      if (S::ex(i) != 0) g[i] = *pull_at<QT>(a, b, Q + i, S::ex(i), S::ey(i), S::ez(i));
   } else if constexpr (ACC == ACC_EVEN) {
 #pragma unroll
-    for (int j = 0; j < Q; ++j) f[j] = get<NT>(a + own_addr<QT>(b, j));
+    for (int j = 0; j < Q; ++j) f[j] = get<NT>(own_at<QT>(a, b, j));
 #pragma unroll
-    for (int i = 0; i < QS; ++i) g[i] = get<NT>(a + own_addr<QT>(b, Q + i));
+    for (int i = 0; i < QS; ++i) g[i] = get<NT>(own_at<QT>(a, b, Q + i));
   } else {
 #pragma unroll
     for (int j = 0; j < Q; ++j)
-      if (L::ex(j) == 0) f[j] = get<NT>(a + pull_addr<QT>(b, L::opp(j), L::ex(j), L::ey(j), L::ez(j)));
+      if (L::ex(j) == 0) f[j] = get<NT>(pull_at<QT>(a, b, L::opp(j), L::ex(j), L::ey(j), L::ez(j)));
 #pragma unroll
     for (int j = 0; j < Q; ++j)
-      if (L::ex(j) != 0) f[j] = a[pull_addr<QT>(b, L::opp(j), L::ex(j), L::ey(j), L::ez(j))];
+      if (L::ex(j) != 0) f[j] = *pull_at<QT>(a, b, L::opp(j), L::ex(j), L::ey(j), L::ez(j));
 #pragma unroll
     for (int i = 0; i < QS; ++i)
-      if (S::ex(i) == 0) g[i] = get<NT>(a + pull_addr<QT>(b, Q + S::opp(i), S::ex(i), S::ey(i), S::ez(i)));
+      if (S::ex(i) == 0) g[i] = get<NT>(pull_at<QT>(a, b, Q + S::opp(i), S::ex(i), S::ey(i), S::ez(i)));
 #pragma unroll
     for (int i = 0; i < QS; ++i)
-      if (S::ex(i) != 0) g[i] = a[pull_addr<QT>(b, Q + S::opp(i), S::ex(i), S::ey(i), S::ez(i))];
+      if (S::ex(i) != 0) g[i] = *pull_at<QT>(a, b, Q + S::opp(i), S::ex(i), S::ey(i), S::ez(i));
   }
 }
 
 template <int Q, int QS, typename Real, bool NT, int ACC>
-__device__ __forceinline__ void store_state(Real* a, const Nbr& b, const Real (&f)[Q], const Real (&g)[QS > 0 ? QS : 1]) {
+__device__ __forceinline__ void store_state(Real* a, const Nbr& nb, const Real (&f)[Q], const Real (&g)[QS > 0 ? QS : 1]) {
   using L = Lat<Q>;
   using S = SLat<QS>;
   constexpr int QT = Q + QS;
-  // In place the stores hit the addresses the loads used; an empty asm hides the
-  // lane index so the compiler recomputes the store addresses instead of keeping
-  // every load address live across the node update (measured: 92 -> 55 VGPRs and
-  // 0.75 -> 0.81 of peak for the in-place primal; 186 -> 92 VGPRs and 0.784 ->
-  // 0.799 for the in-place one-shot).  It emits no code.
-  Nbr bb = b;
-  if constexpr (ACC != ACC_PP) {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) asm volatile("" : "+v"(bb.X[k]));
-  }
+  const Nbr b = here(nb);
   if constexpr (ACC == ACC_PP) {
 #pragma unroll
-    for (int j = 0; j < Q; ++j) put<NT>(a + own_addr<QT>(bb, j), f[j]);
+    for (int j = 0; j < Q; ++j) put<NT>(own_at<QT>(a, b, j), f[j]);
 #pragma unroll
-    for (int i = 0; i < QS; ++i) put<NT>(a + own_addr<QT>(bb, Q + i), g[i]);
+    for (int i = 0; i < QS; ++i) put<NT>(own_at<QT>(a, b, Q + i), g[i]);
   } else if constexpr (ACC == ACC_EVEN) {
 #pragma unroll
-    for (int j = 0; j < Q; ++j) put<NT>(a + own_addr<QT>(bb, L::opp(j)), f[j]);
+    for (int j = 0; j < Q; ++j) put<NT>(own_at<QT>(a, b, L::opp(j)), f[j]);
 #pragma unroll
-    for (int i = 0; i < QS; ++i) put<NT>(a + own_addr<QT>(bb, Q + S::opp(i)), g[i]);
+    for (int i = 0; i < QS; ++i) put<NT>(own_at<QT>(a, b, Q + S::opp(i)), g[i]);
   } else {
     // stores shifted along x share their end lines with the neighbouring wave's:
     // plain stores let the L2 merge the two halves (in-place primal 0.836 -> 0.839)
 #pragma unroll
     for (int j = 0; j < Q; ++j)
-      if (L::ex(j) == 0) put<NT>(a + push_addr<QT>(bb, j, L::ex(j), L::ey(j), L::ez(j)), f[j]);
+      if (L::ex(j) == 0) put<NT>(push_at<QT>(a, b, j, L::ex(j), L::ey(j), L::ez(j)), f[j]);
 #pragma unroll
     for (int j = 0; j < Q; ++j)
-      if (L::ex(j) != 0) put<false>(a + push_addr<QT>(bb, j, L::ex(j), L::ey(j), L::ez(j)), f[j]);
+      if (L::ex(j) != 0) put<false>(push_at<QT>(a, b, j, L::ex(j), L::ey(j), L::ez(j)), f[j]);
 #pragma unroll
-    for (int i = 0; i < QS; ++i) put<NT>(a + push_addr<QT>(bb, Q + i, S::ex(i), S::ey(i), S::ez(i)), g[i]);
+    for (int i = 0; i < QS; ++i) put<NT>(push_at<QT>(a, b, Q + i, S::ex(i), S::ey(i), S::ez(i)), g[i]);
   }
 }
 
@@ -340,72 +387,63 @@ __device__ __forceinline__ void load_cot(const Real* a, const Nbr& b, Real (&mu)
   if constexpr (ACC == ACC_PP) {
 #pragma unroll
     for (int j = 0; j < Q; ++j)
-      if (L::ex(j) == 0) mu[j] = get<NT>(a + push_addr<QT>(b, j, L::ex(j), L::ey(j), L::ez(j)));
+      if (L::ex(j) == 0) mu[j] = get<NT>(push_at<QT>(a, b, j, L::ex(j), L::ey(j), L::ez(j)));
 #pragma unroll
     for (int j = 0; j < Q; ++j)
-      if (L::ex(j) != 0) mu[j] = a[push_addr<QT>(b, j, L::ex(j), L::ey(j), L::ez(j))];
+      if (L::ex(j) != 0) mu[j] = *push_at<QT>(a, b, j, L::ex(j), L::ey(j), L::ez(j));
 #pragma unroll
     for (int i = 0; i < QS; ++i)
-      if (S::ex(i) == 0) nu[i] = get<NT>(a + push_addr<QT>(b, Q + i, S::ex(i), S::ey(i), S::ez(i)));
+      if (S::ex(i) == 0) nu[i] = get<NT>(push_at<QT>(a, b, Q + i, S::ex(i), S::ey(i), S::ez(i)));
 #pragma unroll
     for (int i = 0; i < QS; ++i)
-      if (S::ex(i) != 0) nu[i] = a[push_addr<QT>(b, Q + i, S::ex(i), S::ey(i), S::ez(i))];
+      if (S::ex(i) != 0) nu[i] = *push_at<QT>(a, b, Q + i, S::ex(i), S::ey(i), S::ez(i));
   } else if constexpr (ACC == ACC_EVEN) {
 #pragma unroll
-    for (int j = 0; j < Q; ++j) mu[j] = get<NT>(a + own_addr<QT>(b, j));
+    for (int j = 0; j < Q; ++j) mu[j] = get<NT>(own_at<QT>(a, b, j));
 #pragma unroll
-    for (int i = 0; i < QS; ++i) nu[i] = get<NT>(a + own_addr<QT>(b, Q + i));
+    for (int i = 0; i < QS; ++i) nu[i] = get<NT>(own_at<QT>(a, b, Q + i));
   } else {
 #pragma unroll
     for (int j = 0; j < Q; ++j)
-      if (L::ex(j) == 0) mu[j] = get<NT>(a + push_addr<QT>(b, L::opp(j), L::ex(j), L::ey(j), L::ez(j)));
+      if (L::ex(j) == 0) mu[j] = get<NT>(push_at<QT>(a, b, L::opp(j), L::ex(j), L::ey(j), L::ez(j)));
 #pragma unroll
     for (int j = 0; j < Q; ++j)
-      if (L::ex(j) != 0) mu[j] = a[push_addr<QT>(b, L::opp(j), L::ex(j), L::ey(j), L::ez(j))];
+      if (L::ex(j) != 0) mu[j] = *push_at<QT>(a, b, L::opp(j), L::ex(j), L::ey(j), L::ez(j));
 #pragma unroll
     for (int i = 0; i < QS; ++i)
-      if (S::ex(i) == 0) nu[i] = get<NT>(a + push_addr<QT>(b, Q + S::opp(i), S::ex(i), S::ey(i), S::ez(i)));
+      if (S::ex(i) == 0) nu[i] = get<NT>(push_at<QT>(a, b, Q + S::opp(i), S::ex(i), S::ey(i), S::ez(i)));
 #pragma unroll
     for (int i = 0; i < QS; ++i)
-      if (S::ex(i) != 0) nu[i] = a[push_addr<QT>(b, Q + S::opp(i), S::ex(i), S::ey(i), S::ez(i))];
+      if (S::ex(i) != 0) nu[i] = *push_at<QT>(a, b, Q + S::opp(i), S::ex(i), S::ey(i), S::ez(i));
   }
 }
 
 template <int Q, int QS, typename Real, bool NT, int ACC>
-__device__ __forceinline__ void store_cot(Real* a, const Nbr& b, const Real (&lf)[Q], const Real (&lg)[QS > 0 ? QS : 1]) {
+__device__ __forceinline__ void store_cot(Real* a, const Nbr& nb, const Real (&lf)[Q], const Real (&lg)[QS > 0 ? QS : 1]) {
   using L = Lat<Q>;
   using S = SLat<QS>;
   constexpr int QT = Q + QS;
-  // In place the stores hit the addresses the loads used; an empty asm hides the
-  // lane index so the compiler recomputes the store addresses instead of keeping
-  // every load address live across the node update (measured: 92 -> 55 VGPRs and
-  // 0.75 -> 0.81 of peak for the in-place primal; 186 -> 92 VGPRs and 0.784 ->
-  // 0.799 for the in-place one-shot).  It emits no code.
-  Nbr bb = b;
-  if constexpr (ACC != ACC_PP) {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) asm volatile("" : "+v"(bb.X[k]));
-  }
+  const Nbr b = here(nb);
   if constexpr (ACC == ACC_PP) {
 #pragma unroll
-    for (int j = 0; j < Q; ++j) put<NT>(a + own_addr<QT>(bb, j), lf[j]);
+    for (int j = 0; j < Q; ++j) put<NT>(own_at<QT>(a, b, j), lf[j]);
 #pragma unroll
-    for (int i = 0; i < QS; ++i) put<NT>(a + own_addr<QT>(bb, Q + i), lg[i]);
+    for (int i = 0; i < QS; ++i) put<NT>(own_at<QT>(a, b, Q + i), lg[i]);
   } else if constexpr (ACC == ACC_EVEN) {
 #pragma unroll
-    for (int j = 0; j < Q; ++j) put<NT>(a + own_addr<QT>(bb, L::opp(j)), lf[j]);
+    for (int j = 0; j < Q; ++j) put<NT>(own_at<QT>(a, b, L::opp(j)), lf[j]);
 #pragma unroll
-    for (int i = 0; i < QS; ++i) put<NT>(a + own_addr<QT>(bb, Q + S::opp(i)), lg[i]);
+    for (int i = 0; i < QS; ++i) put<NT>(own_at<QT>(a, b, Q + S::opp(i)), lg[i]);
   } else {
     // shifted stores plain, as for the state
 #pragma unroll
     for (int j = 0; j < Q; ++j)
-      if (L::ex(j) == 0) put<NT>(a + pull_addr<QT>(bb, j, L::ex(j), L::ey(j), L::ez(j)), lf[j]);
+      if (L::ex(j) == 0) put<NT>(pull_at<QT>(a, b, j, L::ex(j), L::ey(j), L::ez(j)), lf[j]);
 #pragma unroll
     for (int j = 0; j < Q; ++j)
-      if (L::ex(j) != 0) put<false>(a + pull_addr<QT>(bb, j, L::ex(j), L::ey(j), L::ez(j)), lf[j]);
+      if (L::ex(j) != 0) put<false>(pull_at<QT>(a, b, j, L::ex(j), L::ey(j), L::ez(j)), lf[j]);
 #pragma unroll
-    for (int i = 0; i < QS; ++i) put<NT>(a + pull_addr<QT>(bb, Q + i, S::ex(i), S::ey(i), S::ez(i)), lg[i]);
+    for (int i = 0; i < QS; ++i) put<NT>(pull_at<QT>(a, b, Q + i, S::ex(i), S::ey(i), S::ez(i)), lg[i]);
   }
 }
 
@@ -456,12 +494,6 @@ __device__ __forceinline__ Real* lx_lds() {
 __device__ __forceinline__ int lx_seg() { return threadIdx.y * blockDim.x; }
 __device__ __forceinline__ int lx_span() { return blockDim.x * blockDim.y; }
 
-// Row r(dy, dz) = Yr[1 + dy] + Zr[1 + dz]; address of slot jj's run in it.
-template <int QT>
-__device__ __forceinline__ int run_addr(const Nbr& b, int jj, int dy, int dz) {
-  return ((b.Yr[1 + dy] + b.Zr[1 + dz]) * QT + jj) * b.pitch;
-}
-
 // Loads of a pulled (ping-pong, odd in-place phase) state with the x-shifted
 // populations staged through LDS; the others as load_state.
 // NTS: streaming hint on the staged (now aligned) loads.  It pays for the
@@ -482,22 +514,22 @@ __device__ __forceinline__ void load_state_lx(const Real* a, const Nbr& b, Real 
 #pragma unroll
   for (int j = 0; j < Q; ++j)
     if (L::ex(j) == 0)
-      f[j] = act ? get<NT>(a + pull_addr<QT>(b, odd ? L::opp(j) : j, L::ex(j), L::ey(j), L::ez(j))) : Real(0);
+      f[j] = act ? get<NT>(pull_at<QT>(a, b, odd ? L::opp(j) : j, L::ex(j), L::ey(j), L::ez(j))) : Real(0);
 #pragma unroll
   for (int i = 0; i < QS; ++i)
     if (S::ex(i) == 0)
-      g[i] = act ? get<NT>(a + pull_addr<QT>(b, Q + (odd ? S::opp(i) : i), S::ex(i), S::ey(i), S::ez(i))) : Real(0);
+      g[i] = act ? get<NT>(pull_at<QT>(a, b, Q + (odd ? S::opp(i) : i), S::ex(i), S::ey(i), S::ez(i))) : Real(0);
   if (act) {
 #pragma unroll
     for (int j = 0; j < Q; ++j)
       if (L::ex(j) != 0)
         lds[H::flow_slot(j) * bt + seg + b.X[1]] =
-            get<NTS>(a + run_addr<QT>(b, odd ? L::opp(j) : j, -L::ey(j), -L::ez(j)) + b.X[1]);
+            get<NTS>(lane_at(run_at<QT>(a, b, odd ? L::opp(j) : j, -L::ey(j), -L::ez(j)), b.O[1]));
 #pragma unroll
     for (int i = 0; i < QS; ++i)
       if (S::ex(i) != 0)
         lds[H::scalar_slot(i) * bt + seg + b.X[1]] =
-            get<NTS>(a + run_addr<QT>(b, Q + (odd ? S::opp(i) : i), -S::ey(i), -S::ez(i)) + b.X[1]);
+            get<NTS>(lane_at(run_at<QT>(a, b, Q + (odd ? S::opp(i) : i), -S::ey(i), -S::ez(i)), b.O[1]));
   }
   __syncthreads();
 #pragma unroll
@@ -509,45 +541,50 @@ __device__ __forceinline__ void load_state_lx(const Real* a, const Nbr& b, Real 
 }
 
 // Stores of the odd in-place phase (pushed to x + e_j) with the x-shifted
-// populations staged through LDS.  The first barrier keeps the staging of the
-// loads intact until every thread has read it.
+// populations staged through LDS: store_state_lx stores the others and fills the
+// runs (after a barrier that keeps the staging of the loads intact until every
+// thread has read it; inside the branch of the node's class, see primal_operator),
+// store_state_lx_end, after a barrier, stores the runs.
 // NTS: streaming stores for the staged populations.
-template <int Q, int QS, typename Real, bool NT, bool NTS>
-__device__ __forceinline__ void store_state_lx(Real* a, const Nbr& b, const Real (&f)[Q],
-                                               const Real (&g)[QS > 0 ? QS : 1], Real* lds, int seg, int bt,
-    bool act) {
+template <int Q, int QS, typename Real, bool NT>
+__device__ __forceinline__ void store_state_lx(Real* a, const Nbr& nb, const Real (&f)[Q],
+                                               const Real (&g)[QS > 0 ? QS : 1], Real* lds, int seg, int bt) {
+  using L = Lat<Q>;
+  using S = SLat<QS>;
+  using H = Shifted<Q, QS>;
+  constexpr int QT = Q + QS;
+  const Nbr b = here(nb);
+#pragma unroll
+  for (int j = 0; j < Q; ++j)
+    if (L::ex(j) != 0) lds[H::flow_slot(j) * bt + seg + b.X[1 + L::ex(j)]] = f[j];
+#pragma unroll
+  for (int i = 0; i < QS; ++i)
+    if (S::ex(i) != 0) lds[H::scalar_slot(i) * bt + seg + b.X[1 + S::ex(i)]] = g[i];
+#pragma unroll
+  for (int j = 0; j < Q; ++j)
+    if (L::ex(j) == 0) put<NT>(push_at<QT>(a, b, j, L::ex(j), L::ey(j), L::ez(j)), f[j]);
+#pragma unroll
+  for (int i = 0; i < QS; ++i)
+    if (S::ex(i) == 0) put<NT>(push_at<QT>(a, b, Q + i, S::ex(i), S::ey(i), S::ez(i)), g[i]);
+}
+
+template <int Q, int QS, typename Real, bool NTS>
+__device__ __forceinline__ void store_state_lx_end(Real* a, const Nbr& nb, const Real* lds, int seg, int bt, bool act) {
   using L = Lat<Q>;
   using S = SLat<QS>;
   using H = Shifted<Q, QS>;
   constexpr int QT = Q + QS;
   __syncthreads();
-  if (act) {
-#pragma unroll
-    for (int j = 0; j < Q; ++j)
-      if (L::ex(j) != 0) lds[H::flow_slot(j) * bt + seg + b.X[1 + L::ex(j)]] = f[j];
-#pragma unroll
-    for (int i = 0; i < QS; ++i)
-      if (S::ex(i) != 0) lds[H::scalar_slot(i) * bt + seg + b.X[1 + S::ex(i)]] = g[i];
-  }
-  __syncthreads();
   if (!act) return;
-  Nbr bb = b;  // addresses recomputed (see store_state)
-#pragma unroll
-  for (int k = 0; k < 3; ++k) asm volatile("" : "+v"(bb.X[k]));
-#pragma unroll
-  for (int j = 0; j < Q; ++j)
-    if (L::ex(j) == 0) put<NT>(a + push_addr<QT>(bb, j, L::ex(j), L::ey(j), L::ez(j)), f[j]);
-#pragma unroll
-  for (int i = 0; i < QS; ++i)
-    if (S::ex(i) == 0) put<NT>(a + push_addr<QT>(bb, Q + i, S::ex(i), S::ey(i), S::ez(i)), g[i]);
+  const Nbr b = here(nb);
 #pragma unroll
   for (int j = 0; j < Q; ++j)
     if (L::ex(j) != 0)
-      put<NTS>(a + run_addr<QT>(bb, j, L::ey(j), L::ez(j)) + bb.X[1], lds[H::flow_slot(j) * bt + seg + bb.X[1]]);
+      put<NTS>(lane_at(run_at<QT>(a, b, j, L::ey(j), L::ez(j)), b.O[1]), lds[H::flow_slot(j) * bt + seg + b.X[1]]);
 #pragma unroll
   for (int i = 0; i < QS; ++i)
     if (S::ex(i) != 0)
-      put<NTS>(a + run_addr<QT>(bb, Q + i, S::ey(i), S::ez(i)) + bb.X[1], lds[H::scalar_slot(i) * bt + seg + bb.X[1]]);
+      put<NTS>(lane_at(run_at<QT>(a, b, Q + i, S::ey(i), S::ez(i)), b.O[1]), lds[H::scalar_slot(i) * bt + seg + b.X[1]]);
 }
 
 // Cotangent loads (mu_j(x) = lambda_j(x + e_j): ping-pong, or the odd in-place
@@ -565,22 +602,22 @@ __device__ __forceinline__ void load_cot_lx(const Real* a, const Nbr& b, Real (&
 #pragma unroll
   for (int j = 0; j < Q; ++j)
     if (L::ex(j) == 0)
-      mu[j] = act ? get<NT>(a + push_addr<QT>(b, odd ? L::opp(j) : j, L::ex(j), L::ey(j), L::ez(j))) : Real(0);
+      mu[j] = act ? get<NT>(push_at<QT>(a, b, odd ? L::opp(j) : j, L::ex(j), L::ey(j), L::ez(j))) : Real(0);
 #pragma unroll
   for (int i = 0; i < QS; ++i)
     if (S::ex(i) == 0)
-      nu[i] = act ? get<NT>(a + push_addr<QT>(b, Q + (odd ? S::opp(i) : i), S::ex(i), S::ey(i), S::ez(i))) : Real(0);
+      nu[i] = act ? get<NT>(push_at<QT>(a, b, Q + (odd ? S::opp(i) : i), S::ex(i), S::ey(i), S::ez(i))) : Real(0);
   if (act) {
 #pragma unroll
     for (int j = 0; j < Q; ++j)
       if (L::ex(j) != 0)
         lds[H::flow_slot(j) * bt + seg + b.X[1]] =
-            get<NTS>(a + run_addr<QT>(b, odd ? L::opp(j) : j, L::ey(j), L::ez(j)) + b.X[1]);
+            get<NTS>(lane_at(run_at<QT>(a, b, odd ? L::opp(j) : j, L::ey(j), L::ez(j)), b.O[1]));
 #pragma unroll
     for (int i = 0; i < QS; ++i)
       if (S::ex(i) != 0)
         lds[H::scalar_slot(i) * bt + seg + b.X[1]] =
-            get<NTS>(a + run_addr<QT>(b, Q + (odd ? S::opp(i) : i), S::ey(i), S::ez(i)) + b.X[1]);
+            get<NTS>(lane_at(run_at<QT>(a, b, Q + (odd ? S::opp(i) : i), S::ey(i), S::ez(i)), b.O[1]));
   }
   __syncthreads();
 #pragma unroll
@@ -593,53 +630,65 @@ __device__ __forceinline__ void load_cot_lx(const Real* a, const Nbr& b, Real (&
 
 // Cotangent stores of the odd in-place pattern (lambda_j(x) to slot j of
 // x - e_j) with the x-shifted populations staged through LDS.
-template <int Q, int QS, typename Real, bool NT, bool NTS>
-__device__ __forceinline__ void store_cot_lx(Real* a, const Nbr& b, const Real (&lf)[Q],
-                                             const Real (&lg)[QS > 0 ? QS : 1], Real* lds, int seg, int bt,
-    bool act) {
+template <int Q, int QS, typename Real, bool NT>
+__device__ __forceinline__ void store_cot_lx(Real* a, const Nbr& nb, const Real (&lf)[Q],
+                                             const Real (&lg)[QS > 0 ? QS : 1], Real* lds, int seg, int bt) {
+  using L = Lat<Q>;
+  using S = SLat<QS>;
+  using H = Shifted<Q, QS>;
+  constexpr int QT = Q + QS;
+  const Nbr b = here(nb);
+#pragma unroll
+  for (int j = 0; j < Q; ++j)
+    if (L::ex(j) != 0) lds[H::flow_slot(j) * bt + seg + b.X[1 - L::ex(j)]] = lf[j];
+#pragma unroll
+  for (int i = 0; i < QS; ++i)
+    if (S::ex(i) != 0) lds[H::scalar_slot(i) * bt + seg + b.X[1 - S::ex(i)]] = lg[i];
+#pragma unroll
+  for (int j = 0; j < Q; ++j)
+    if (L::ex(j) == 0) put<NT>(pull_at<QT>(a, b, j, L::ex(j), L::ey(j), L::ez(j)), lf[j]);
+#pragma unroll
+  for (int i = 0; i < QS; ++i)
+    if (S::ex(i) == 0) put<NT>(pull_at<QT>(a, b, Q + i, S::ex(i), S::ey(i), S::ez(i)), lg[i]);
+}
+
+template <int Q, int QS, typename Real, bool NTS>
+__device__ __forceinline__ void store_cot_lx_end(Real* a, const Nbr& nb, const Real* lds, int seg, int bt, bool act) {
   using L = Lat<Q>;
   using S = SLat<QS>;
   using H = Shifted<Q, QS>;
   constexpr int QT = Q + QS;
   __syncthreads();
-  if (act) {
-#pragma unroll
-    for (int j = 0; j < Q; ++j)
-      if (L::ex(j) != 0) lds[H::flow_slot(j) * bt + seg + b.X[1 - L::ex(j)]] = lf[j];
-#pragma unroll
-    for (int i = 0; i < QS; ++i)
-      if (S::ex(i) != 0) lds[H::scalar_slot(i) * bt + seg + b.X[1 - S::ex(i)]] = lg[i];
-  }
-  __syncthreads();
   if (!act) return;
-  Nbr bb = b;  // addresses recomputed (see store_state)
-#pragma unroll
-  for (int k = 0; k < 3; ++k) asm volatile("" : "+v"(bb.X[k]));
-#pragma unroll
-  for (int j = 0; j < Q; ++j)
-    if (L::ex(j) == 0) put<NT>(a + pull_addr<QT>(bb, j, L::ex(j), L::ey(j), L::ez(j)), lf[j]);
-#pragma unroll
-  for (int i = 0; i < QS; ++i)
-    if (S::ex(i) == 0) put<NT>(a + pull_addr<QT>(bb, Q + i, S::ex(i), S::ey(i), S::ez(i)), lg[i]);
+  const Nbr b = here(nb);
 #pragma unroll
   for (int j = 0; j < Q; ++j)
     if (L::ex(j) != 0)
-      put<NTS>(a + run_addr<QT>(bb, j, -L::ey(j), -L::ez(j)) + bb.X[1], lds[H::flow_slot(j) * bt + seg + bb.X[1]]);
+      put<NTS>(lane_at(run_at<QT>(a, b, j, -L::ey(j), -L::ez(j)), b.O[1]), lds[H::flow_slot(j) * bt + seg + b.X[1]]);
 #pragma unroll
   for (int i = 0; i < QS; ++i)
     if (S::ex(i) != 0)
-      put<NTS>(a + run_addr<QT>(bb, Q + i, -S::ey(i), -S::ez(i)) + bb.X[1],
-               lds[H::scalar_slot(i) * bt + seg + bb.X[1]]);
+      put<NTS>(lane_at(run_at<QT>(a, b, Q + i, -S::ey(i), -S::ez(i)), b.O[1]),
+               lds[H::scalar_slot(i) * bt + seg + b.X[1]]);
 }
 
 // Pre-collision state of a node for the inspection and objective kernels: the
-// access pattern of the buffer is a run-time argument there.
+// access pattern of the buffer is a run-time argument there, and a wave's nodes
+// may lie in different rows.
 template <int Q, int QS, typename Real>
 __device__ __forceinline__ void load_state_rt(const Real* a, const Nbr& b, int acc, Real (&f)[Q],
                                               Real (&g)[QS > 0 ? QS : 1]) {
-  if (acc == ACC_EVEN) load_state<Q, QS, Real, ACC_EVEN>(a, b, f, g);
-  else if (acc == ACC_ODD) load_state<Q, QS, Real, ACC_ODD>(a, b, f, g);
-  else load_state<Q, QS, Real, ACC_PP>(a, b, f, g);
+  using L = Lat<Q>;
+  using S = SLat<QS>;
+  constexpr int QT = Q + QS;
+#pragma unroll
+  for (int j = 0; j < Q; ++j)
+    f[j] = a[acc == ACC_EVEN ? own_addr<QT>(b, j)
+                             : pull_addr<QT>(b, acc == ACC_ODD ? L::opp(j) : j, L::ex(j), L::ey(j), L::ez(j))];
+#pragma unroll
+  for (int i = 0; i < QS; ++i)
+    g[i] = a[acc == ACC_EVEN ? own_addr<QT>(b, Q + i)
+                             : pull_addr<QT>(b, Q + (acc == ACC_ODD ? S::opp(i) : i), S::ex(i), S::ey(i), S::ez(i))];
 }
 
 // ------------------------------------------------------- node operators
@@ -680,26 +729,66 @@ __device__ __forceinline__ void mrt_apply(const Params<Real>& p, const Real (&d)
   }
 }
 
+// e.v of a velocity with components in {-1, 0, 1}: the sum of the non-zero
+// components only.  Written as ex*vx + ey*vy + ez*vz the products with a literal
+// zero stay in the code (0*v is not foldable in IEEE arithmetic); with the
+// per-pair sharing below this halved the VALU work of the node operators
+// (D3Q19 primal wave 570 -> 280 instructions, adjoint 525 -> 290) at bitwise the
+// same results.
+template <typename Real>
+__device__ __forceinline__ Real edot(int ex, int ey, int ez, Real vx, Real vy, Real vz) {
+  Real s = ex ? (ex > 0 ? vx : -vx) : (ey ? (ey > 0 ? vy : -vy) : (ez ? (ez > 0 ? vz : -vz) : Real(0)));
+  if (ex && ey) s = s + (ey > 0 ? vy : -vy);
+  if ((ex || ey) && ez) s = s + (ez > 0 ? vz : -vz);
+  return s;
+}
+
+// Density, velocity and switching values of an interior node's pre-collision
+// state: formed once for the recorded moments, the collision and the transposed
+// Jacobian.
+template <typename Real>
+struct Macro {
+  Real drho, rho, inv, ux, uy, uz, T;
+  Real G, dG;
+};
+
+template <int Q, int QS, typename Real>
+__device__ __forceinline__ Macro<Real> macro_interior(const Params<Real>& p, Real wn, const Real (&f)[Q],
+                                                      const Real (&g)[QS > 0 ? QS : 1]) {
+  using L = Lat<Q>;
+  Macro<Real> a;
+  Real mx = 0, my = 0, mz = 0;
+  a.drho = 0;
+#pragma unroll
+  for (int j = 0; j < Q; ++j) {
+    a.drho += f[j];
+    if (L::ex(j)) mx += Real(L::ex(j)) * f[j];
+    if (L::ey(j)) my += Real(L::ey(j)) * f[j];
+    if (L::ez(j)) mz += Real(L::ez(j)) * f[j];
+  }
+  a.rho = Real(1) + a.drho;
+  a.inv = Real(1) / a.rho;
+  a.ux = mx * a.inv;
+  a.uy = my * a.inv;
+  a.uz = mz * a.inv;
+  a.T = 0;
+  if constexpr (QS > 0) {
+#pragma unroll
+    for (int i = 0; i < QS; ++i) a.T += g[i];
+  }
+  switch_fn(p, wn, a.G, a.dG);
+  return a;
+}
+
+// The loop runs over pairs (j, opp(j)): e.u and P1 change sign, P2 does not.
 template <int Q, int QS, typename Real, int V = 0>
-__device__ __forceinline__ void collide_interior(const Params<Real>& p, Real wn, Real (&f)[Q],
+__device__ __forceinline__ void collide_interior(const Params<Real>& p, Real wn, const Macro<Real>& a, Real (&f)[Q],
                                                  Real (&g)[QS > 0 ? QS : 1]) {
   using L = Lat<Q>;
   using S = SLat<QS>;
   constexpr bool MRT = (V & kVarMRT) != 0;
   constexpr bool VD = (V & kVarVD) != 0;
-  Real drho = 0, mx = 0, my = 0, mz = 0;
-#pragma unroll
-  for (int j = 0; j < Q; ++j) {
-    drho += f[j];
-    if (L::ex(j)) mx += Real(L::ex(j)) * f[j];
-    if (L::ey(j)) my += Real(L::ey(j)) * f[j];
-    if (L::ez(j)) mz += Real(L::ez(j)) * f[j];
-  }
-  const Real rho = Real(1) + drho;
-  const Real inv = Real(1) / rho;
-  const Real ux = mx * inv, uy = my * inv, uz = mz * inv;
-  Real G, dG;
-  switch_fn(p, wn, G, dG);
+  const Real drho = a.drho, rho = a.rho, ux = a.ux, uy = a.uy, uz = a.uz, G = a.G;
   const Real usq = ux * ux + uy * uy + uz * uz;
   const Real G2 = G * G;
   if constexpr (MRT) {
@@ -708,36 +797,55 @@ __device__ __forceinline__ void collide_interior(const Params<Real>& p, Real wn,
     Real d[19];
 #pragma unroll
     for (int j = 0; j < Q; ++j) {
-      const Real eu = Real(L::ex(j)) * ux + Real(L::ey(j)) * uy + Real(L::ez(j)) * uz;
-      const Real Pu = Real(3) * eu + Real(4.5) * eu * eu - Real(1.5) * usq;
-      d[j] = f[j] - Real(L::w(j)) * (drho + rho * Pu);  // shifted f minus shifted E(rho, u)
+      if (L::opp(j) < j) continue;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int k = s ? L::opp(j) : j;
+        if (s && k == j) continue;
+        const Real eu0 = edot(L::ex(j), L::ey(j), L::ez(j), ux, uy, uz);
+        const Real eu = s ? -eu0 : eu0;
+        const Real Pu = Real(3) * eu + Real(4.5) * eu * eu - Real(1.5) * usq;
+        d[k] = f[k] - Real(L::w(k)) * (drho + rho * Pu);  // shifted f minus shifted E(rho, u)
+      }
     }
     Real r[19];
     mrt_apply<Real>(p, d, r);
 #pragma unroll
     for (int j = 0; j < Q; ++j) {
-      const Real eu = Real(L::ex(j)) * ux + Real(L::ey(j)) * uy + Real(L::ez(j)) * uz;
-      const Real Pv = G * Real(3) * eu + G2 * (Real(4.5) * eu * eu - Real(1.5) * usq);
-      f[j] = Real(L::w(j)) * (drho + rho * Pv) + r[j];
+      if (L::opp(j) < j) continue;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int k = s ? L::opp(j) : j;
+        if (s && k == j) continue;
+        const Real eu0 = edot(L::ex(j), L::ey(j), L::ez(j), ux, uy, uz);
+        const Real eu = s ? -eu0 : eu0;
+        const Real Pv = G * Real(3) * eu + G2 * (Real(4.5) * eu0 * eu0 - Real(1.5) * usq);
+        f[k] = Real(L::w(k)) * (drho + rho * Pv) + r[k];
+      }
     }
   } else {
     const Real om1 = Real(1) - p.om;
     const Real a0 = p.om * drho;
 #pragma unroll
     for (int j = 0; j < Q; ++j) {
-      const Real eu = Real(L::ex(j)) * ux + Real(L::ey(j)) * uy + Real(L::ez(j)) * uz;
+      if (L::opp(j) < j) continue;
+      const Real eu = edot(L::ex(j), L::ey(j), L::ez(j), ux, uy, uz);
       // P(u) = 3 e.u + 4.5 (e.u)^2 - 1.5 u^2 (c_s^2 = 1/3), P(Gu) = G P1 + G^2 P2
       const Real P1 = Real(3) * eu;
       const Real P2 = Real(4.5) * eu * eu - Real(1.5) * usq;
-      const Real Pu = P1 + P2;
-      const Real Pv = G * P1 + G2 * P2;
-      f[j] = om1 * f[j] + Real(L::w(j)) * (a0 + rho * (Pv - om1 * Pu));
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int k = s ? L::opp(j) : j;
+        if (s && k == j) continue;
+        const Real Q1 = s ? -P1 : P1;
+        const Real Pu = Q1 + P2;
+        const Real Pv = G * Q1 + G2 * P2;
+        f[k] = om1 * f[k] + Real(L::w(k)) * (a0 + rho * (Pv - om1 * Pu));
+      }
     }
   }
   if constexpr (QS > 0) {
-    Real T = 0;
-#pragma unroll
-    for (int i = 0; i < QS; ++i) T += g[i];
+    const Real T = a.T;
     const Real vx = G * ux, vy = G * uy, vz = G * uz;
     // blended diffusivity: tau_s(w) = w tau_fluid + (1 - w) tau_solid (Section 3.2)
     const Real oms = VD ? Real(1) / (wn * p.taus_f + (Real(1) - wn) * p.taus_s) : p.oms;
@@ -751,7 +859,7 @@ __device__ __forceinline__ void collide_interior(const Params<Real>& p, Real wn,
     Real E[QS], Es = 0;
 #pragma unroll
     for (int i = 1; i < QS; ++i) {
-      const Real ev = Real(S::ex(i)) * vx + Real(S::ey(i)) * vy + Real(S::ez(i)) * vz;
+      const Real ev = edot(S::ex(i), S::ey(i), S::ez(i), vx, vy, vz);
       E[i] = Real(S::w(i)) * T * (Real(1) + ev * ic2);
       Es += E[i];
     }
@@ -934,40 +1042,34 @@ __device__ __forceinline__ bool has_moments(const Params<Real>& p, int cls) {
   return cls == INTERIOR || cls == OUTLET || (cls == INLET && p.inlet_mode == IN_PRESSURE);
 }
 
+// The moments of an interior node from its macroscopic values ...
 template <int Q, int QS, typename Real, int V = 0>
-__device__ __forceinline__ void node_moments(const Params<Real>& p, int cls, int y, int z, const Real (&f)[Q],
-                                             const Real (&g)[QS > 0 ? QS : 1], Real (&m)[Mom<Q, QS, V>::N]) {
+__device__ __forceinline__ void interior_moments(const Macro<Real>& a, const Real (&g)[QS > 0 ? QS : 1],
+                                                 Real (&m)[Mom<Q, QS, V>::N]) {
+  using M = Mom<Q, QS, V>;
+  m[0] = a.rho;
+  m[1] = a.ux;
+  m[2] = a.uy;
+  if constexpr (M::D == 3) m[3] = a.uz;
+  if constexpr (QS > 0) {
+    if constexpr (M::VD) {
+#pragma unroll
+      for (int i = 0; i < QS; ++i) m[M::T + i] = g[i];
+    } else {
+      m[M::T] = a.T;
+    }
+  }
+}
+
+// ... and of an inlet or outlet node from its populations.
+template <int Q, int QS, typename Real, int V = 0>
+__device__ __forceinline__ void boundary_moments(const Params<Real>& p, int cls, int y, int z, const Real (&f)[Q],
+                                                 const Real (&g)[QS > 0 ? QS : 1], Real (&m)[Mom<Q, QS, V>::N]) {
   using L = Lat<Q>;
   using M = Mom<Q, QS, V>;
 #pragma unroll
   for (int k = 0; k < M::N; ++k) m[k] = Real(0);
-  if (cls == INTERIOR) {
-    Real drho = 0, mx = 0, my = 0, mz = 0;
-#pragma unroll
-    for (int j = 0; j < Q; ++j) {
-      drho += f[j];
-      if (L::ex(j)) mx += Real(L::ex(j)) * f[j];
-      if (L::ey(j)) my += Real(L::ey(j)) * f[j];
-      if (L::ez(j)) mz += Real(L::ez(j)) * f[j];
-    }
-    const Real rho = Real(1) + drho;
-    const Real inv = Real(1) / rho;
-    m[0] = rho;
-    m[1] = mx * inv;
-    m[2] = my * inv;
-    if constexpr (M::D == 3) m[3] = mz * inv;
-    if constexpr (QS > 0) {
-      if constexpr (M::VD) {
-#pragma unroll
-        for (int i = 0; i < QS; ++i) m[M::T + i] = g[i];
-      } else {
-        Real T = 0;
-#pragma unroll
-        for (int i = 0; i < QS; ++i) T += g[i];
-        m[M::T] = T;
-      }
-    }
-  } else if (cls == OUTLET) {
+  if (cls == OUTLET) {
     Real s0 = 0, sp = 0;
 #pragma unroll
     for (int j = 0; j < Q; ++j) {
@@ -997,6 +1099,64 @@ __device__ __forceinline__ void node_moments(const Params<Real>& p, int cls, int
   }
 }
 
+// The node operator of an interior, inlet or outlet node: its pre-collision
+// populations (f, g) become the post-collision ones; with MOM its moments m too.
+// The classes are one-armed branches that the compiler may not join (the empty asm
+// hides that they exclude each other): in an if-else chain the populations of the
+// lanes still to come stay live beside the finished ones, two sets of registers
+// (D3Q19 FP32 72 VGPRs instead of 52, 102 instead of 86 in FP64).
+template <int Q, int QS, typename Real, bool MOM, int V>
+__device__ __forceinline__ void primal_open(const Params<Real>& p, int cls, Real wn, int y, int z, Real (&f)[Q],
+                                            Real (&g)[QS > 0 ? QS : 1], Real (&m)[Mom<Q, QS, V>::N]) {
+  if (cls == INTERIOR) {
+    const Macro<Real> a = macro_interior<Q, QS, Real>(p, wn, f, g);
+    if constexpr (MOM) interior_moments<Q, QS, Real, V>(a, g, m);
+    collide_interior<Q, QS, Real, V>(p, wn, a, f, g);
+  }
+  asm("" : "+v"(cls));
+  if (cls == INLET) {
+    if constexpr (MOM) boundary_moments<Q, QS, Real, V>(p, INLET, y, z, f, g, m);
+    collide_inlet<Q, QS, Real>(p, y, z, f, g);
+  }
+  asm("" : "+v"(cls));
+  if (cls == OUTLET) {
+    if constexpr (MOM) boundary_moments<Q, QS, Real, V>(p, OUTLET, y, z, f, g, m);
+    collide_outlet<Q, QS, Real>(p, f, g);
+  }
+}
+
+// The node operator of one node of a wave whose nodes share a row; with MOM its
+// moments are recorded (only the classes whose transposes read them).  Streaming
+// stores whatever the state size: a moment set is read once, by the adjoint,
+// after the rest of the run has passed through the cache.
+// done(f, g) stores the result: wall rows (wave-uniform) in their own branch, so
+// that their permutation shares no registers with the collisions; the others
+// once, after their branches have merged -- stored inside the branches, the one
+// inlet or outlet lane of a wave writes its part of every line by itself (batched
+// 8 x 96x48x48 with streaming stores: 22.1 -> 41.4 ms per pass).
+template <int Q, int QS, typename Real, bool MOM, int V, class Done>
+__device__ __forceinline__ void primal_operator(const Params<Real>& p, int cls, const Nbr& b,
+                                                const Real* __restrict__ w, Real* __restrict__ mom, int x, int y,
+                                                int z, Real (&f)[Q], Real (&g)[QS > 0 ? QS : 1], Done&& done) {
+  if (cls == WALL) {
+    collide_wall<Q, QS, Real>(p, x, y, f, g);
+    done(f, g);
+    return;
+  }
+  if (cls == PAD) return;
+  const Nbr bi = here(b);
+  const Real wn = *node_at(w, bi);
+  Real m[Mom<Q, QS, V>::N];
+  primal_open<Q, QS, Real, MOM, V>(p, cls, wn, y, z, f, g, m);
+  if constexpr (MOM) {
+    if (has_moments(p, cls)) {
+#pragma unroll
+      for (int k = 0; k < Mom<Q, QS, V>::N; ++k) put<true>(node_at(mom + (size_t)k * p.Np, bi), m[k]);
+    }
+  }
+  done(f, g);
+}
+
 // One primal node update: pull, collide by node class, store (coalesced).
 // With MOM, also records the node's pre-collision moments (see Mom).
 // src and dst are the same buffer for the in-place patterns, so they carry no
@@ -1009,37 +1169,19 @@ __device__ __forceinline__ void primal_node(const Params<Real>& p, const Real* s
                                             int z, Real* lds = nullptr, int seg = 0, int bt = 0, bool act = true) {
   constexpr bool is3d = (Q == 19);
   const Nbr b = make_nbr(p, x, y, z);
-  const int n = own_inode(b);  // workspace node arrays
   Real f[Q], g[QS > 0 ? QS : 1];
   if constexpr (LX)
     load_state_lx<Q, QS, Real, ACC, NT, NT && ACC == ACC_PP>(src, b, f, g, lds, seg, bt, act);
   else
     load_state<Q, QS, Real, ACC, NT && (ACC != ACC_EVEN || NTE)>(src, b, f, g);
-  // padding lanes (LX only) take the wall operator: a permutation, no memory access
-  const int cls = act ? node_class(p, x, y, z, is3d) : WALL;
-  if constexpr (MOM) {
-    if (has_moments(p, cls)) {  // the only classes whose transposes read them
-      Real m[Mom<Q, QS, V>::N];
-      node_moments<Q, QS, Real, V>(p, cls, y, z, f, g, m);
-      // streaming stores whatever the state size: a moment set is read once, by the
-      // adjoint, after the rest of the run has passed through the cache
-#pragma unroll
-      for (int k = 0; k < Mom<Q, QS, V>::N; ++k) put<true>(mom + (size_t)k * p.Np + n, m[k]);
-    }
-  }
-  if (cls == INTERIOR) {
-    collide_interior<Q, QS, Real, V>(p, w[n], f, g);
-  } else if (cls == WALL) {
-    collide_wall<Q, QS, Real>(p, x, y, f, g);
-  } else if (cls == INLET) {
-    collide_inlet<Q, QS, Real>(p, y, z, f, g);
-  } else {
-    collide_outlet<Q, QS, Real>(p, f, g);
-  }
-  if constexpr (LX && ACC == ACC_ODD)
-    store_state_lx<Q, QS, Real, NT, false>(dst, b, f, g, lds, seg, bt, act);
-  else if (act)
-    store_state<Q, QS, Real, NT, ACC>(dst, b, f, g);
+  const int cls = act ? node_class(p, x, y, z, is3d) : PAD;
+  constexpr bool kStaged = LX && ACC == ACC_ODD;
+  if constexpr (kStaged) __syncthreads();
+  primal_operator<Q, QS, Real, MOM, V>(p, cls, b, w, mom, x, y, z, f, g, [&](const auto& fo, const auto& go) {
+    if constexpr (kStaged) store_state_lx<Q, QS, Real, NT>(dst, b, fo, go, lds, seg, bt);
+    else store_state<Q, QS, Real, NT, ACC>(dst, b, fo, go);
+  });
+  if constexpr (kStaged) store_state_lx_end<Q, QS, Real, false>(dst, b, lds, seg, bt, act);
 }
 
 // LX: the block spans whole rows and the x-shifted populations go through LDS
@@ -1363,257 +1505,361 @@ __global__ void k_window_mean(const D* __restrict__ win, int W, D* __restrict__ 
 // (dW/d(f,g))^T (mu, nu) and gw = (dW/dw)^T (mu, nu) (zero except at interior
 // nodes).  Wall and velocity-inlet operators are affine in (f, g): their
 // products do not read m.  Hand-derived from the operators above.
+// The product of an interior node: from its macroscopic values and, with blended
+// diffusivity, its scalar populations g (otherwise not read).
 template <int Q, int QS, typename Real, int V = 0>
-__device__ __forceinline__ void adjoint_vjp(const Params<Real>& p, int cls, int x, int y,
-                                            const Real (&m)[Mom<Q, QS, V>::N],
-                                            Real wn, const Real (&mu)[Q], const Real (&nu)[QS > 0 ? QS : 1],
-                                            Real (&lf)[Q], Real (&lg)[QS > 0 ? QS : 1], Real& gw) {
+__device__ __forceinline__ void adjoint_interior(const Params<Real>& p, const Macro<Real>& a,
+                                                 const Real (&g)[QS > 0 ? QS : 1], Real wn, const Real (&mu)[Q],
+                                                 const Real (&nu)[QS > 0 ? QS : 1], Real (&lf)[Q],
+                                                 Real (&lg)[QS > 0 ? QS : 1], Real& gw) {
+  using L = Lat<Q>;
+  using S = SLat<QS>;
+  constexpr bool MRT = (V & kVarMRT) != 0;
+  constexpr bool VD = (V & kVarVD) != 0;
+  const Real om1 = Real(1) - p.om;
+  const Real rho = a.rho, inv = a.inv, ux = a.ux, uy = a.uy, uz = a.uz, G = a.G;
+  const Real usq = ux * ux + uy * uy + uz * uz;
+  const Real G2 = G * G;
+  // cotangent moments M0 = sum mu w, M1 = sum mu w e, P = sum mu w (e.u) e; M0 is
+  // taken as mu_0 + sum_{j>0} w_j (mu_j - mu_0), which is exact for a uniform
+  // cotangent however the weights round (the rounded weights sum to 1 + 1.5e-8
+  // in FP32, and the plain sum would grow a uniform cotangent by that each step)
+  Real M0 = mu[0], M1x = 0, M1y = 0, M1z = 0, Px = 0, Py = 0, Pz = 0;
+#pragma unroll
+  for (int j = 0; j < Q; ++j) {
+    const Real a = mu[j] * Real(L::w(j));
+    const Real eu = edot(L::ex(j), L::ey(j), L::ez(j), ux, uy, uz);
+    const Real be = a * eu;
+    if (j > 0) M0 += Real(L::w(j)) * (mu[j] - mu[0]);
+    if (L::ex(j)) { M1x += Real(L::ex(j)) * a; Px += Real(L::ex(j)) * be; }
+    if (L::ey(j)) { M1y += Real(L::ey(j)) * a; Py += Real(L::ey(j)) * be; }
+    if (L::ez(j)) { M1z += Real(L::ez(j)) * a; Pz += Real(L::ez(j)) * be; }
+  }
+  const Real Mu = M1x * ux + M1y * uy + M1z * uz;
+  const Real Pu = Px * ux + Py * uy + Pz * uz;
+  Real dL_drho, dux, duy, duz;
+  Real kap[Q];  // MRT: the relaxed cotangent K mu (K symmetric); BGK uses (1 - omega) mu
+  if constexpr (MRT) {
+    // h = E(rho, G u) + K (f - E(rho, u)):  lambda = K mu + (dE(rho,Gu)/df)^T mu - (dE(rho,u)/df)^T K mu
+    mrt_apply<Real>(p, mu, kap);
+    Real K0 = kap[0], K1x = 0, K1y = 0, K1z = 0, KPx = 0, KPy = 0, KPz = 0;
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+      const Real a = kap[j] * Real(L::w(j));
+      const Real eu = edot(L::ex(j), L::ey(j), L::ez(j), ux, uy, uz);
+      const Real be = a * eu;
+      if (j > 0) K0 += Real(L::w(j)) * (kap[j] - kap[0]);  // as M0
+      if (L::ex(j)) { K1x += Real(L::ex(j)) * a; KPx += Real(L::ex(j)) * be; }
+      if (L::ey(j)) { K1y += Real(L::ey(j)) * a; KPy += Real(L::ey(j)) * be; }
+      if (L::ez(j)) { K1z += Real(L::ez(j)) * a; KPz += Real(L::ez(j)) * be; }
+    }
+    const Real Ku = K1x * ux + K1y * uy + K1z * uz;
+    const Real KPu = KPx * ux + KPy * uy + KPz * uz;
+    dL_drho = (M0 + Real(3) * G * Mu + Real(4.5) * G2 * Pu - Real(1.5) * G2 * M0 * usq) -
+              (K0 + Real(3) * Ku + Real(4.5) * KPu - Real(1.5) * K0 * usq);
+    const Real g1 = Real(3) * G, g2 = Real(9) * G2, g3 = Real(3) * G2 * M0, k3 = Real(3) * K0;
+    dux = rho * ((g1 * M1x + g2 * Px - g3 * ux) - (Real(3) * K1x + Real(9) * KPx - k3 * ux));
+    duy = rho * ((g1 * M1y + g2 * Py - g3 * uy) - (Real(3) * K1y + Real(9) * KPy - k3 * uy));
+    duz = rho * ((g1 * M1z + g2 * Pz - g3 * uz) - (Real(3) * K1z + Real(9) * KPz - k3 * uz));
+  } else {
+    // d/drho at fixed u of A(rho, G u) - (1-omega) A(rho, u), A = sum mu_j E_j
+    dL_drho = M0 * (Real(1) - om1) + Real(3) * (G - om1) * Mu + Real(4.5) * (G2 - om1) * Pu -
+              Real(1.5) * (G2 - om1) * M0 * usq;
+    const Real c1 = Real(3) * (G - om1), c2 = Real(9) * (G2 - om1), c3 = Real(3) * (G2 - om1) * M0;
+    dux = rho * (c1 * M1x + c2 * Px - c3 * ux);
+    duy = rho * (c1 * M1y + c2 * Py - c3 * uy);
+    duz = rho * (c1 * M1z + c2 * Pz - c3 * uz);
+  }
+  Real dLdG = rho * (Real(3) * Mu + Real(9) * G * Pu - Real(3) * G * M0 * usq);
+  Real gws = 0;  // blended diffusivity: d omega_s / dw times the scalar's non-equilibrium product
+  if constexpr (QS > 0) {
+    const Real T = a.T;
+    // N0 = sum nu w as nu_0 + sum_{i>0} w_i (nu_i - nu_0), the transpose of the
+    // primal's rest equilibrium taken by difference
+    Real N0 = nu[0], N1x = 0, N1y = 0, N1z = 0;
+#pragma unroll
+    for (int i = 0; i < QS; ++i) {
+      const Real a = nu[i] * Real(S::w(i));
+      if (i > 0) N0 += Real(S::w(i)) * (nu[i] - nu[0]);
+      if (S::ex(i)) N1x += Real(S::ex(i)) * a;
+      if (S::ey(i)) N1y += Real(S::ey(i)) * a;
+      if (S::ez(i)) N1z += Real(S::ez(i)) * a;
+    }
+    const Real ic2 = Real(1.0 / S::c2());
+    const Real N1u = N1x * ux + N1y * uy + N1z * uz;
+    Real oms = p.oms;
+    if constexpr (VD) {
+      // g' = g + omega(w) (E^s - g), omega(w) = 1 / (w tau_f + (1 - w) tau_s):
+      // the w-derivative adds omega'(w) sum_i nu_i (E^s_i - g_i)
+      const Real tw = wn * p.taus_f + (Real(1) - wn) * p.taus_s;
+      oms = Real(1) / tw;
+      Real nug = 0;
+#pragma unroll
+      for (int i = 0; i < QS; ++i) nug += nu[i] * g[i];
+      gws = -(p.taus_f - p.taus_s) * oms * oms * (T * (N0 + G * N1u * ic2) - nug);
+    }
+    const Real k = oms * T * G * ic2;
+    dux += k * N1x;
+    duy += k * N1y;
+    duz += k * N1z;
+    dLdG += oms * T * N1u * ic2;
+    const Real dT = oms * (N0 + G * N1u * ic2);
+    const Real oms1w = Real(1) - oms;
+#pragma unroll
+    for (int i = 0; i < QS; ++i) lg[i] = oms1w * nu[i] + dT;
+  }
+  const Real dmx = dux * inv, dmy = duy * inv, dmz = duz * inv;
+  const Real drt = dL_drho - (dux * ux + duy * uy + duz * uz) * inv;
+#pragma unroll
+  for (int k = 0; k < Q; ++k) {
+    Real v;
+    if constexpr (MRT) v = kap[k] + drt;
+    else v = om1 * mu[k] + drt;
+    if (L::ex(k)) v += Real(L::ex(k)) * dmx;
+    if (L::ey(k)) v += Real(L::ey(k)) * dmy;
+    if (L::ez(k)) v += Real(L::ez(k)) * dmz;
+    lf[k] = v;
+  }
+  gw = a.dG * dLdG + gws;
+}
+
+// Macroscopic values of an interior node from its recorded moments.
+template <int Q, int QS, typename Real, int V = 0>
+__device__ __forceinline__ Macro<Real> macro_recorded(const Params<Real>& p, Real wn,
+                                                      const Real (&m)[Mom<Q, QS, V>::N]) {
+  using M = Mom<Q, QS, V>;
+  Macro<Real> a;
+  a.drho = Real(0);  // not read by the transposed Jacobian
+  a.rho = m[0];
+  a.inv = Real(1) / a.rho;
+  a.ux = m[1];
+  a.uy = m[2];
+  a.uz = Real(0);
+  if constexpr (M::D == 3) a.uz = m[3];
+  a.T = Real(0);
+  if constexpr (QS > 0) {
+    if constexpr (M::VD) {
+#pragma unroll
+      for (int i = 0; i < QS; ++i) a.T += m[M::T + i];
+    } else {
+      a.T = m[M::T];
+    }
+  }
+  switch_fn(p, wn, a.G, a.dG);
+  return a;
+}
+
+// The products of a wall, inlet and outlet node (no design derivative).
+template <int Q, int QS, typename Real>
+__device__ __forceinline__ void adjoint_wall(const Params<Real>& p, int x, int y, const Real (&mu)[Q],
+                                             const Real (&nu)[QS > 0 ? QS : 1], Real (&lf)[Q],
+                                             Real (&lg)[QS > 0 ? QS : 1]) {
+  using L = Lat<Q>;
+  using S = SLat<QS>;
+#pragma unroll
+  for (int j = 0; j < Q; ++j) lf[j] = mu[L::opp(j)];
+  Real tw;
+  const bool dir = wall_dirichlet(p, x, y, tw);  // Dirichlet: g' does not depend on g
+#pragma unroll
+  for (int i = 0; i < QS; ++i) lg[i] = dir ? Real(0) : nu[S::opp(i)];
+}
+
+template <int Q, int QS, typename Real, int V = 0>
+__device__ __forceinline__ void adjoint_inlet(const Params<Real>& p, const Real (&m)[Mom<Q, QS, V>::N],
+                                   const Real (&mu)[Q], const Real (&nu)[QS > 0 ? QS : 1], Real (&lf)[Q],
+                                   Real (&lg)[QS > 0 ? QS : 1]) {
   using L = Lat<Q>;
   using S = SLat<QS>;
   using M = Mom<Q, QS, V>;
-  constexpr bool MRT = (V & kVarMRT) != 0;
-  constexpr bool VD = (V & kVarVD) != 0;
-  gw = Real(0);
   const Real om1 = Real(1) - p.om;
   const Real oms1 = Real(1) - p.oms;
-  if (cls == WALL) {
+  // Velocity form (u_in, or u_cap where the pressure form was limited):
+  // h = (1-omega) f* + omega E(rho, u) is affine in f.  Pressure form: rho is
+  // fixed and u = (rho_in - P) / rho_in, so the product runs through u; which
+  // form ran is read from the recorded pressure-form velocity m[1].
+  bool pressure = false;
+  Real u = p.u_in;
+  if (p.inlet_mode == IN_PRESSURE) {
+    const Real up = m[1];
+    pressure = !(p.u_cap > Real(0) && up > p.u_cap);
+    u = pressure ? up : p.u_cap;
+  }
+  if (!pressure) {
+    const Real usq = u * u;
+    Real B = 0, drho = 0, dNy = 0, dNz = 0;
 #pragma unroll
-    for (int j = 0; j < Q; ++j) lf[j] = mu[L::opp(j)];
-    Real tw;
-    const bool dir = wall_dirichlet(p, x, y, tw);  // Dirichlet: g' does not depend on g
-#pragma unroll
-    for (int i = 0; i < QS; ++i) lg[i] = dir ? Real(0) : nu[S::opp(i)];
-  } else if (cls == INLET) {
-    // Velocity form (u_in, or u_cap where the pressure form was limited):
-    // h = (1-omega) f* + omega E(rho, u) is affine in f.  Pressure form: rho is
-    // fixed and u = (rho_in - P) / rho_in, so the product runs through u; which
-    // form ran is read from the recorded pressure-form velocity m[1].
-    bool pressure = false;
-    Real u = p.u_in;
-    if (p.inlet_mode == IN_PRESSURE) {
-      const Real up = m[1];
-      pressure = !(p.u_cap > Real(0) && up > p.u_cap);
-      u = pressure ? up : p.u_cap;
+    for (int j = 0; j < Q; ++j) {
+      const Real eu = Real(L::ex(j)) * u;
+      B += mu[j] * Real(L::w(j)) * (Real(1) + Real(3) * eu + Real(4.5) * eu * eu - Real(1.5) * usq);
+      if (L::ex(j) == 1) {
+        drho += om1 * mu[j] * Real(6.0 * L::w(j)) * u;
+        if (L::ey(j)) dNy -= om1 * mu[j] * Real(L::ey(j));
+        if (L::ez(j)) dNz -= om1 * mu[j] * Real(L::ez(j));
+      }
     }
-    if (!pressure) {
-      const Real usq = u * u;
-      Real B = 0, drho = 0, dNy = 0, dNz = 0;
+    drho += p.om * B;
+    const Real c = drho / (Real(1) - u);
 #pragma unroll
-      for (int j = 0; j < Q; ++j) {
-        const Real eu = Real(L::ex(j)) * u;
-        B += mu[j] * Real(L::w(j)) * (Real(1) + Real(3) * eu + Real(4.5) * eu * eu - Real(1.5) * usq);
-        if (L::ex(j) == 1) {
-          drho += om1 * mu[j] * Real(6.0 * L::w(j)) * u;
-          if (L::ey(j)) dNy -= om1 * mu[j] * Real(L::ey(j));
-          if (L::ez(j)) dNz -= om1 * mu[j] * Real(L::ez(j));
-        }
-      }
-      drho += p.om * B;
-      const Real c = drho / (Real(1) - u);
+    for (int k = 0; k < Q; ++k) {
+      Real v = 0;
+      if (L::ex(k) == 0) v = om1 * mu[k] + c + Real(0.5) * (Real(L::ey(k)) * dNy + Real(L::ez(k)) * dNz);
+      if (L::ex(k) == -1) v = om1 * (mu[k] + mu[L::opp(k)]) + Real(2) * c;
+      lf[k] = v;
+    }
+  } else {
+    const Real ro = Real(1) + p.drho_in;
+    Real dux = 0, dNy = 0, dNz = 0;
 #pragma unroll
-      for (int k = 0; k < Q; ++k) {
-        Real v = 0;
-        if (L::ex(k) == 0) v = om1 * mu[k] + c + Real(0.5) * (Real(L::ey(k)) * dNy + Real(L::ez(k)) * dNz);
-        if (L::ex(k) == -1) v = om1 * (mu[k] + mu[L::opp(k)]) + Real(2) * c;
-        lf[k] = v;
-      }
-    } else {
-      const Real ro = Real(1) + p.drho_in;
-      Real dux = 0, dNy = 0, dNz = 0;
-#pragma unroll
-      for (int j = 0; j < Q; ++j) {
-        const Real ex = Real(L::ex(j));
-        dux += p.om * ro * mu[j] * Real(L::w(j)) * (Real(3) * ex + Real(9) * ex * ex * u - Real(3) * u);
-        if (L::ex(j) == 1) {
-          dux += om1 * mu[j] * Real(6.0 * L::w(j)) * ro;
-          if (L::ey(j)) dNy -= om1 * mu[j] * Real(L::ey(j));
-          if (L::ez(j)) dNz -= om1 * mu[j] * Real(L::ez(j));
-        }
-      }
-      if constexpr (QS > 0) {
-        // the scalar equilibrium at the fixed inlet value T_in (m[T]) moves with u
-        Real N1x = 0;
-#pragma unroll
-        for (int i = 0; i < QS; ++i)
-          if (S::ex(i)) N1x += Real(S::ex(i)) * nu[i] * Real(S::w(i));
-        dux += p.oms * m[M::T] * N1x * Real(1.0 / S::c2());
-      }
-      const Real c = -dux / ro;
-#pragma unroll
-      for (int k = 0; k < Q; ++k) {
-        Real v = 0;
-        if (L::ex(k) == 0) v = om1 * mu[k] + c + Real(0.5) * (Real(L::ey(k)) * dNy + Real(L::ez(k)) * dNz);
-        if (L::ex(k) == -1) v = om1 * (mu[k] + mu[L::opp(k)]) + Real(2) * c;
-        lf[k] = v;
+    for (int j = 0; j < Q; ++j) {
+      const Real ex = Real(L::ex(j));
+      dux += p.om * ro * mu[j] * Real(L::w(j)) * (Real(3) * ex + Real(9) * ex * ex * u - Real(3) * u);
+      if (L::ex(j) == 1) {
+        dux += om1 * mu[j] * Real(6.0 * L::w(j)) * ro;
+        if (L::ey(j)) dNy -= om1 * mu[j] * Real(L::ey(j));
+        if (L::ez(j)) dNz -= om1 * mu[j] * Real(L::ez(j));
       }
     }
     if constexpr (QS > 0) {
+      // the scalar equilibrium at the fixed inlet value T_in (m[T]) moves with u
+      Real N1x = 0;
 #pragma unroll
-      for (int i = 0; i < QS; ++i) lg[i] = (i == kPX) ? Real(0) : oms1 * (nu[i] - nu[kPX]);
+      for (int i = 0; i < QS; ++i)
+        if (S::ex(i)) N1x += Real(S::ex(i)) * nu[i] * Real(S::w(i));
+      dux += p.oms * m[M::T] * N1x * Real(1.0 / S::c2());
     }
-  } else {
-    if (cls == INTERIOR) {
-      const Real rho = m[0];
-      const Real inv = Real(1) / rho;
-      const Real ux = m[1], uy = m[2];
-      Real uz = Real(0);
-      if constexpr (M::D == 3) uz = m[3];
-      const Real usq = ux * ux + uy * uy + uz * uz;
-      Real G, dG;
-      switch_fn(p, wn, G, dG);
-      const Real G2 = G * G;
-      // cotangent moments M0 = sum mu w, M1 = sum mu w e, P = sum mu w (e.u) e; M0 is
-      // taken as mu_0 + sum_{j>0} w_j (mu_j - mu_0), which is exact for a uniform
-      // cotangent however the weights round (the rounded weights sum to 1 + 1.5e-8
-      // in FP32, and the plain sum would grow a uniform cotangent by that each step)
-      Real M0 = mu[0], M1x = 0, M1y = 0, M1z = 0, Px = 0, Py = 0, Pz = 0;
+    const Real c = -dux / ro;
 #pragma unroll
-      for (int j = 0; j < Q; ++j) {
-        const Real a = mu[j] * Real(L::w(j));
-        const Real eu = Real(L::ex(j)) * ux + Real(L::ey(j)) * uy + Real(L::ez(j)) * uz;
-        const Real be = a * eu;
-        if (j > 0) M0 += Real(L::w(j)) * (mu[j] - mu[0]);
-        if (L::ex(j)) { M1x += Real(L::ex(j)) * a; Px += Real(L::ex(j)) * be; }
-        if (L::ey(j)) { M1y += Real(L::ey(j)) * a; Py += Real(L::ey(j)) * be; }
-        if (L::ez(j)) { M1z += Real(L::ez(j)) * a; Pz += Real(L::ez(j)) * be; }
-      }
-      const Real Mu = M1x * ux + M1y * uy + M1z * uz;
-      const Real Pu = Px * ux + Py * uy + Pz * uz;
-      Real dL_drho, dux, duy, duz;
-      Real kap[Q];  // MRT: the relaxed cotangent K mu (K symmetric); BGK uses (1 - omega) mu
-      if constexpr (MRT) {
-        // h = E(rho, G u) + K (f - E(rho, u)):  lambda = K mu + (dE(rho,Gu)/df)^T mu - (dE(rho,u)/df)^T K mu
-        mrt_apply<Real>(p, mu, kap);
-        Real K0 = kap[0], K1x = 0, K1y = 0, K1z = 0, KPx = 0, KPy = 0, KPz = 0;
-#pragma unroll
-        for (int j = 0; j < Q; ++j) {
-          const Real a = kap[j] * Real(L::w(j));
-          const Real eu = Real(L::ex(j)) * ux + Real(L::ey(j)) * uy + Real(L::ez(j)) * uz;
-          const Real be = a * eu;
-          if (j > 0) K0 += Real(L::w(j)) * (kap[j] - kap[0]);  // as M0
-          if (L::ex(j)) { K1x += Real(L::ex(j)) * a; KPx += Real(L::ex(j)) * be; }
-          if (L::ey(j)) { K1y += Real(L::ey(j)) * a; KPy += Real(L::ey(j)) * be; }
-          if (L::ez(j)) { K1z += Real(L::ez(j)) * a; KPz += Real(L::ez(j)) * be; }
-        }
-        const Real Ku = K1x * ux + K1y * uy + K1z * uz;
-        const Real KPu = KPx * ux + KPy * uy + KPz * uz;
-        dL_drho = (M0 + Real(3) * G * Mu + Real(4.5) * G2 * Pu - Real(1.5) * G2 * M0 * usq) -
-                  (K0 + Real(3) * Ku + Real(4.5) * KPu - Real(1.5) * K0 * usq);
-        const Real g1 = Real(3) * G, g2 = Real(9) * G2, g3 = Real(3) * G2 * M0, k3 = Real(3) * K0;
-        dux = rho * ((g1 * M1x + g2 * Px - g3 * ux) - (Real(3) * K1x + Real(9) * KPx - k3 * ux));
-        duy = rho * ((g1 * M1y + g2 * Py - g3 * uy) - (Real(3) * K1y + Real(9) * KPy - k3 * uy));
-        duz = rho * ((g1 * M1z + g2 * Pz - g3 * uz) - (Real(3) * K1z + Real(9) * KPz - k3 * uz));
-      } else {
-        // d/drho at fixed u of A(rho, G u) - (1-omega) A(rho, u), A = sum mu_j E_j
-        dL_drho = M0 * (Real(1) - om1) + Real(3) * (G - om1) * Mu + Real(4.5) * (G2 - om1) * Pu -
-                  Real(1.5) * (G2 - om1) * M0 * usq;
-        const Real c1 = Real(3) * (G - om1), c2 = Real(9) * (G2 - om1), c3 = Real(3) * (G2 - om1) * M0;
-        dux = rho * (c1 * M1x + c2 * Px - c3 * ux);
-        duy = rho * (c1 * M1y + c2 * Py - c3 * uy);
-        duz = rho * (c1 * M1z + c2 * Pz - c3 * uz);
-      }
-      Real dLdG = rho * (Real(3) * Mu + Real(9) * G * Pu - Real(3) * G * M0 * usq);
-      Real gws = 0;  // blended diffusivity: d omega_s / dw times the scalar's non-equilibrium product
-      if constexpr (QS > 0) {
-        Real T;
-        if constexpr (VD) {
-          T = 0;
-#pragma unroll
-          for (int i = 0; i < QS; ++i) T += m[M::T + i];
-        } else {
-          T = m[M::T];
-        }
-        // N0 = sum nu w as nu_0 + sum_{i>0} w_i (nu_i - nu_0), the transpose of the
-        // primal's rest equilibrium taken by difference
-        Real N0 = nu[0], N1x = 0, N1y = 0, N1z = 0;
-#pragma unroll
-        for (int i = 0; i < QS; ++i) {
-          const Real a = nu[i] * Real(S::w(i));
-          if (i > 0) N0 += Real(S::w(i)) * (nu[i] - nu[0]);
-          if (S::ex(i)) N1x += Real(S::ex(i)) * a;
-          if (S::ey(i)) N1y += Real(S::ey(i)) * a;
-          if (S::ez(i)) N1z += Real(S::ez(i)) * a;
-        }
-        const Real ic2 = Real(1.0 / S::c2());
-        const Real N1u = N1x * ux + N1y * uy + N1z * uz;
-        Real oms = p.oms;
-        if constexpr (VD) {
-          // g' = g + omega(w) (E^s - g), omega(w) = 1 / (w tau_f + (1 - w) tau_s):
-          // the w-derivative adds omega'(w) sum_i nu_i (E^s_i - g_i)
-          const Real tw = wn * p.taus_f + (Real(1) - wn) * p.taus_s;
-          oms = Real(1) / tw;
-          Real nug = 0;
-#pragma unroll
-          for (int i = 0; i < QS; ++i) nug += nu[i] * m[M::T + i];
-          gws = -(p.taus_f - p.taus_s) * oms * oms * (T * (N0 + G * N1u * ic2) - nug);
-        }
-        const Real k = oms * T * G * ic2;
-        dux += k * N1x;
-        duy += k * N1y;
-        duz += k * N1z;
-        dLdG += oms * T * N1u * ic2;
-        const Real dT = oms * (N0 + G * N1u * ic2);
-        const Real oms1w = Real(1) - oms;
-#pragma unroll
-        for (int i = 0; i < QS; ++i) lg[i] = oms1w * nu[i] + dT;
-      }
-      const Real dmx = dux * inv, dmy = duy * inv, dmz = duz * inv;
-      const Real drt = dL_drho - (dux * ux + duy * uy + duz * uz) * inv;
-#pragma unroll
-      for (int k = 0; k < Q; ++k) {
-        Real v;
-        if constexpr (MRT) v = kap[k] + drt;
-        else v = om1 * mu[k] + drt;
-        if (L::ex(k)) v += Real(L::ex(k)) * dmx;
-        if (L::ey(k)) v += Real(L::ey(k)) * dmy;
-        if (L::ez(k)) v += Real(L::ez(k)) * dmz;
-        lf[k] = v;
-      }
-      gw = dG * dLdG + gws;
-    } else {  // OUTLET
-      const Real ro = p.rho_out;
-      const Real ux = m[1];
-      Real dux = 0, dNy = 0, dNz = 0;
-#pragma unroll
-      for (int j = 0; j < Q; ++j) {
-        const Real ex = Real(L::ex(j));
-        dux += p.om * ro * mu[j] * Real(L::w(j)) * (Real(3) * ex + Real(9) * ex * ex * ux - Real(3) * ux);
-        if (L::ex(j) == -1) {
-          dux -= om1 * mu[j] * Real(6.0 * L::w(j)) * ro;
-          if (L::ey(j)) dNy -= om1 * mu[j] * Real(L::ey(j));
-          if (L::ez(j)) dNz -= om1 * mu[j] * Real(L::ez(j));
-        }
-      }
-      if constexpr (QS > 0) {
-        const Real ic2 = Real(1.0 / S::c2());
-        const Real rest = m[M::T];
-        Real N0 = 0, N1x = 0;
-#pragma unroll
-        for (int i = 0; i < QS; ++i) {
-          const Real a = nu[i] * Real(S::w(i));
-          N0 += a;
-          if (S::ex(i)) N1x += Real(S::ex(i)) * a;
-        }
-        const Real a = Real(S::w(kMX)) * (Real(1) - ux * ic2);
-        const Real inv1a = Real(1) / (Real(1) - a);
-        const Real T = rest * inv1a;
-        const Real dT = oms1 * nu[kMX] * a + p.oms * (N0 + N1x * ux * ic2);
-        const Real da = oms1 * nu[kMX] * T + dT * T * inv1a;
-        const Real dS = dT * inv1a;
-        dux += p.oms * T * N1x * ic2 - da * Real(S::w(kMX)) * ic2;
-#pragma unroll
-        for (int i = 0; i < QS; ++i) lg[i] = (i == kMX) ? Real(0) : oms1 * nu[i] + dS;
-      }
-      const Real c = dux / ro;
-#pragma unroll
-      for (int k = 0; k < Q; ++k) {
-        Real v = 0;
-        if (L::ex(k) == 0) v = om1 * mu[k] + c + Real(0.5) * (Real(L::ey(k)) * dNy + Real(L::ez(k)) * dNz);
-        if (L::ex(k) == 1) v = om1 * (mu[k] + mu[L::opp(k)]) + Real(2) * c;
-        lf[k] = v;
-      }
+    for (int k = 0; k < Q; ++k) {
+      Real v = 0;
+      if (L::ex(k) == 0) v = om1 * mu[k] + c + Real(0.5) * (Real(L::ey(k)) * dNy + Real(L::ez(k)) * dNz);
+      if (L::ex(k) == -1) v = om1 * (mu[k] + mu[L::opp(k)]) + Real(2) * c;
+      lf[k] = v;
     }
   }
+  if constexpr (QS > 0) {
+#pragma unroll
+    for (int i = 0; i < QS; ++i) lg[i] = (i == kPX) ? Real(0) : oms1 * (nu[i] - nu[kPX]);
+  }
+}
+
+template <int Q, int QS, typename Real, int V = 0>
+__device__ __forceinline__ void adjoint_outlet(const Params<Real>& p, const Real (&m)[Mom<Q, QS, V>::N],
+                                   const Real (&mu)[Q], const Real (&nu)[QS > 0 ? QS : 1], Real (&lf)[Q],
+                                   Real (&lg)[QS > 0 ? QS : 1]) {
+  using L = Lat<Q>;
+  using S = SLat<QS>;
+  using M = Mom<Q, QS, V>;
+  const Real om1 = Real(1) - p.om;
+  const Real oms1 = Real(1) - p.oms;
+  const Real ro = p.rho_out;
+  const Real ux = m[1];
+  Real dux = 0, dNy = 0, dNz = 0;
+#pragma unroll
+  for (int j = 0; j < Q; ++j) {
+    const Real ex = Real(L::ex(j));
+    dux += p.om * ro * mu[j] * Real(L::w(j)) * (Real(3) * ex + Real(9) * ex * ex * ux - Real(3) * ux);
+    if (L::ex(j) == -1) {
+      dux -= om1 * mu[j] * Real(6.0 * L::w(j)) * ro;
+      if (L::ey(j)) dNy -= om1 * mu[j] * Real(L::ey(j));
+      if (L::ez(j)) dNz -= om1 * mu[j] * Real(L::ez(j));
+    }
+  }
+  if constexpr (QS > 0) {
+    const Real ic2 = Real(1.0 / S::c2());
+    const Real rest = m[M::T];
+    Real N0 = 0, N1x = 0;
+#pragma unroll
+    for (int i = 0; i < QS; ++i) {
+      const Real a = nu[i] * Real(S::w(i));
+      N0 += a;
+      if (S::ex(i)) N1x += Real(S::ex(i)) * a;
+    }
+    const Real a = Real(S::w(kMX)) * (Real(1) - ux * ic2);
+    const Real inv1a = Real(1) / (Real(1) - a);
+    const Real T = rest * inv1a;
+    const Real dT = oms1 * nu[kMX] * a + p.oms * (N0 + N1x * ux * ic2);
+    const Real da = oms1 * nu[kMX] * T + dT * T * inv1a;
+    const Real dS = dT * inv1a;
+    dux += p.oms * T * N1x * ic2 - da * Real(S::w(kMX)) * ic2;
+#pragma unroll
+    for (int i = 0; i < QS; ++i) lg[i] = (i == kMX) ? Real(0) : oms1 * nu[i] + dS;
+  }
+  const Real c = dux / ro;
+#pragma unroll
+  for (int k = 0; k < Q; ++k) {
+    Real v = 0;
+    if (L::ex(k) == 0) v = om1 * mu[k] + c + Real(0.5) * (Real(L::ey(k)) * dNy + Real(L::ez(k)) * dNz);
+    if (L::ex(k) == 1) v = om1 * (mu[k] + mu[L::opp(k)]) + Real(2) * c;
+    lf[k] = v;
+  }
+}
+
+// The transposed operator of an interior, inlet or outlet node from its recorded
+// moments m: the cotangents (mu, nu) of its post-collision populations become
+// those of the pre-collision ones; gw is the gradient term (zero except at
+// interior nodes).  Branches as in primal_open.
+template <int Q, int QS, typename Real, int V>
+__device__ __forceinline__ void adjoint_open(const Params<Real>& p, int cls, Real wn,
+                                             const Real (&m)[Mom<Q, QS, V>::N], Real (&mu)[Q],
+                                             Real (&nu)[QS > 0 ? QS : 1], Real& gw) {
+  using M = Mom<Q, QS, V>;
+  const auto keep = [&](const Real(&lf)[Q], const Real(&lg)[QS > 0 ? QS : 1]) {
+#pragma unroll
+    for (int j = 0; j < Q; ++j) mu[j] = lf[j];
+#pragma unroll
+    for (int i = 0; i < QS; ++i) nu[i] = lg[i];
+  };
+  gw = Real(0);
+  if (cls == INTERIOR) {
+    const Macro<Real> a = macro_recorded<Q, QS, Real, V>(p, wn, m);
+    Real g[QS > 0 ? QS : 1] = {}, lf[Q], lg[QS > 0 ? QS : 1];
+    if constexpr (M::VD) {
+#pragma unroll
+      for (int i = 0; i < QS; ++i) g[i] = m[M::T + i];
+    }
+    adjoint_interior<Q, QS, Real, V>(p, a, g, wn, mu, nu, lf, lg, gw);
+    keep(lf, lg);
+  }
+  asm("" : "+v"(cls));
+  if (cls == INLET) {
+    Real lf[Q], lg[QS > 0 ? QS : 1];
+    adjoint_inlet<Q, QS, Real, V>(p, m, mu, nu, lf, lg);
+    keep(lf, lg);
+  }
+  asm("" : "+v"(cls));
+  if (cls == OUTLET) {
+    Real lf[Q], lg[QS > 0 ? QS : 1];
+    adjoint_outlet<Q, QS, Real, V>(p, m, mu, nu, lf, lg);
+    keep(lf, lg);
+  }
+}
+
+// The transposed operator of one node of a wave whose nodes share a row; adds the
+// node's gradient term and hands the new cotangent to done(mu, nu) (see
+// primal_operator).  Moments are read once: streaming hint whatever the state
+// size, so that they do not evict a cotangent state the last-level cache could
+// hold between steps.
+template <int Q, int QS, typename Real, int V, class Done>
+__device__ __forceinline__ void adjoint_operator(const Params<Real>& p, int cls, const Nbr& nb,
+                                                 const Real* __restrict__ mom, const Real* __restrict__ w,
+                                                 Real* __restrict__ grad, int x, int y, Real (&mu)[Q],
+                                                 Real (&nu)[QS > 0 ? QS : 1], Done&& done) {
+  using M = Mom<Q, QS, V>;
+  if (cls == WALL) {
+    Real lf[Q], lg[QS > 0 ? QS : 1];
+    adjoint_wall<Q, QS, Real>(p, x, y, mu, nu, lf, lg);
+    done(lf, lg);
+    return;
+  }
+  if (cls == PAD) return;
+  const Nbr b = here(nb);
+  Real m[M::N], gw;  // a velocity inlet reads none of its moments (none are recorded)
+#pragma unroll
+  for (int k = 0; k < M::N; ++k) m[k] = get<true>(node_at(mom + (size_t)k * p.Np, b));
+  const Real wn = *node_at(w, b), g0 = *node_at(grad, b);
+  adjoint_open<Q, QS, Real, V>(p, cls, wn, m, mu, nu, gw);
+  if (cls == INTERIOR) *node_at(grad, b) = g0 + gw;
+  done(mu, nu);
 }
 
 // lambda^n(x) = (dW^x/df)^T(f^n(x)) mu(x),  mu_j(x) = lambda^{n+1}_j(x + e_j)
@@ -1633,30 +1879,19 @@ __device__ __forceinline__ void adjoint_node(const Params<Real>& p, const Real* 
   constexpr bool is3d = (Q == 19);
   constexpr int QSA = QS > 0 ? QS : 1;
   const Nbr b = make_nbr(p, x, y, z);
-  const int n = own_inode(b);  // workspace node arrays
   Real mu[Q], nu[QSA];
   if constexpr (LX)
     load_cot_lx<Q, QS, Real, ACC, NT, NT && (ACC == ACC_PP || NTE)>(lam_in, b, mu, nu, lds, seg, bt, act);
   else
     load_cot<Q, QS, Real, ACC, NT && (ACC != ACC_EVEN || NTE)>(lam_in, b, mu, nu);
-  // padding lanes (LX only) take the wall transpose: a permutation, no memory access
-  const int cls = act ? node_class(p, x, y, z, is3d) : WALL;
-  Real m[Mom<Q, QS, V>::N], lf[Q], lg[QSA], gw;
-#pragma unroll
-  for (int k = 0; k < Mom<Q, QS, V>::N; ++k) m[k] = Real(0);
-  if (has_moments(p, cls)) {
-#pragma unroll
-    // read once: streaming hint whatever the state size, so that the moments do not
-    // evict a cotangent state the last-level cache could hold between steps
-    for (int k = 0; k < Mom<Q, QS, V>::N; ++k) m[k] = get<true>(mom + (size_t)k * p.Np + n);
-  }
-  const Real wn = (cls == INTERIOR) ? w[n] : Real(1);
-  adjoint_vjp<Q, QS, Real, V>(p, cls, x, y, m, wn, mu, nu, lf, lg, gw);
-  if (cls == INTERIOR) grad[n] += gw;
-  if constexpr (LX && ACC == ACC_ODD)
-    store_cot_lx<Q, QS, Real, NT, NT && NTE>(lam_out, b, lf, lg, lds, seg, bt, act);
-  else if (act)
-    store_cot<Q, QS, Real, NT, ACC>(lam_out, b, lf, lg);
+  const int cls = act ? node_class(p, x, y, z, is3d) : PAD;
+  constexpr bool kStaged = LX && ACC == ACC_ODD;
+  if constexpr (kStaged) __syncthreads();
+  adjoint_operator<Q, QS, Real, V>(p, cls, b, mom, w, grad, x, y, mu, nu, [&](const auto& lf, const auto& lg) {
+    if constexpr (kStaged) store_cot_lx<Q, QS, Real, NT>(lam_out, b, lf, lg, lds, seg, bt);
+    else store_cot<Q, QS, Real, NT, ACC>(lam_out, b, lf, lg);
+  });
+  if constexpr (kStaged) store_cot_lx_end<Q, QS, Real, NT && NTE>(lam_out, b, lds, seg, bt, act);
 }
 
 // LX as for k_primal.
@@ -1885,9 +2120,7 @@ __device__ __forceinline__ void oneshot_node(const Params<Real>& p, const Real* 
   constexpr int QSA = QS > 0 ? QS : 1;
   const int kRuns = Shifted<Q, QS>::count() * bt;  // the cotangent's runs follow the primal's
   const Nbr b = make_nbr(p, x, y, z);
-  const int n = own_inode(b);  // workspace node arrays
-  // padding lanes (LX only) take the wall operators: permutations, no memory access
-  const int cls = act ? node_class(p, x, y, z, is3d) : WALL;
+  const int cls = act ? node_class(p, x, y, z, is3d) : PAD;
   Real f[Q], g[QSA], mu[Q], nu[QSA];
   if constexpr (LX) {
     load_state_lx<Q, QS, Real, ACC, NT, NT && ACC == ACC_PP>(prim_in, b, f, g, lds, seg, bt, act);
@@ -1896,39 +2129,67 @@ __device__ __forceinline__ void oneshot_node(const Params<Real>& p, const Real* 
     load_state<Q, QS, Real, ACC, NT>(prim_in, b, f, g);
     load_cot<Q, QS, Real, ACC, NT>(lam_in, b, mu, nu);
   }
-  const Real wn = (cls == INTERIOR) ? w[n] : Real(1);
-  Real m[Mom<Q, QS, V>::N], lf[Q], lg[QSA], gw;
-  node_moments<Q, QS, Real, V>(p, cls, y, z, f, g, m);
-  adjoint_vjp<Q, QS, Real, V>(p, cls, x, y, m, wn, mu, nu, lf, lg, gw);
-  if (cls == INLET || cls == OUTLET) {
-    double sf[Q], sg[QSA];
-    seed_values<Q, QS, Real>(p, cls, f, g, glob, sf, sg);
-#pragma unroll
-    for (int j = 0; j < Q; ++j) lf[j] += (Real)sf[j];
-#pragma unroll
-    for (int i = 0; i < QS; ++i) lg[i] += (Real)sg[i];
-  }
-  if (cls == INTERIOR) {
-    collide_interior<Q, QS, Real, V>(p, wn, f, g);
-  } else if (cls == WALL) {
+  constexpr bool kStaged = LX && ACC == ACC_ODD;
+  if constexpr (kStaged) __syncthreads();
+  const auto keep_cot = [&](const auto& lf, const auto& lg) {
+    if constexpr (kStaged) store_cot_lx<Q, QS, Real, NT>(lam_out, b, lf, lg, lds + kRuns, seg, bt);
+    else store_cot<Q, QS, Real, NT, ACC>(lam_out, b, lf, lg);
+  };
+  const auto keep_state = [&](const auto& fo, const auto& go) {
+    if constexpr (kStaged) store_state_lx<Q, QS, Real, NT>(prim_out, b, fo, go, lds, seg, bt);
+    else store_state<Q, QS, Real, NT, ACC>(prim_out, b, fo, go);
+  };
+  Real lf[Q], lg[QSA];
+  if (cls == WALL) {
+    adjoint_wall<Q, QS, Real>(p, x, y, mu, nu, lf, lg);
+    keep_cot(lf, lg);
     collide_wall<Q, QS, Real>(p, x, y, f, g);
-  } else if (cls == INLET) {
-    collide_inlet<Q, QS, Real>(p, y, z, f, g);
-  } else {
-    collide_outlet<Q, QS, Real>(p, f, g);
+    keep_state(f, g);
+    *node_at(grad, here(b)) = Real(0);
+  } else if (cls != PAD) {
+    const Nbr bi = here(b);
+    Real gw = Real(0), wn = *node_at(w, bi);
+    const auto take = [&]() {  // the new cotangent in place of the old one (see primal_open)
+#pragma unroll
+      for (int j = 0; j < Q; ++j) mu[j] = lf[j];
+#pragma unroll
+      for (int i = 0; i < QS; ++i) nu[i] = lg[i];
+    };
+    int c = cls;
+    if (c == INTERIOR) {
+      const Macro<Real> a = macro_interior<Q, QS, Real>(p, wn, f, g);
+      adjoint_interior<Q, QS, Real, V>(p, a, g, wn, mu, nu, lf, lg, gw);
+      take();
+      collide_interior<Q, QS, Real, V>(p, wn, a, f, g);
+      const Real v = wn + zeta * (gw + c_pen * (Real(1) - Real(2) * wn));
+      wn = v < Real(0) ? Real(0) : (v > Real(1) ? Real(1) : v);
+    }
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+      asm("" : "+v"(c));
+      if (c != (side ? OUTLET : INLET)) continue;
+      Real m[Mom<Q, QS, V>::N];
+      boundary_moments<Q, QS, Real, V>(p, side ? OUTLET : INLET, y, z, f, g, m);
+      double sf[Q], sg[QSA];
+      seed_values<Q, QS, Real>(p, side ? OUTLET : INLET, f, g, glob, sf, sg);
+      if (side) adjoint_outlet<Q, QS, Real, V>(p, m, mu, nu, lf, lg);
+      else adjoint_inlet<Q, QS, Real, V>(p, m, mu, nu, lf, lg);
+#pragma unroll
+      for (int j = 0; j < Q; ++j) lf[j] += (Real)sf[j];
+#pragma unroll
+      for (int i = 0; i < QS; ++i) lg[i] += (Real)sg[i];
+      take();
+      if (side) collide_outlet<Q, QS, Real>(p, f, g);
+      else collide_inlet<Q, QS, Real>(p, y, z, f, g);
+    }
+    keep_cot(mu, nu);
+    keep_state(f, g);
+    *node_at(grad, bi) = gw;
+    *node_at(w, bi) = wn;
   }
-  if constexpr (LX && ACC == ACC_ODD) {
-    store_state_lx<Q, QS, Real, NT, false>(prim_out, b, f, g, lds, seg, bt, act);
-    store_cot_lx<Q, QS, Real, NT, false>(lam_out, b, lf, lg, lds + kRuns, seg, bt, act);
-  } else if (act) {
-    store_state<Q, QS, Real, NT, ACC>(prim_out, b, f, g);
-    store_cot<Q, QS, Real, NT, ACC>(lam_out, b, lf, lg);
-  }
-  if (!act) return;
-  grad[n] = gw;
-  if (cls == INTERIOR) {
-    const Real v = wn + zeta * (gw + c_pen * (Real(1) - Real(2) * wn));
-    w[n] = v < Real(0) ? Real(0) : (v > Real(1) ? Real(1) : v);
+  if constexpr (kStaged) {
+    store_state_lx_end<Q, QS, Real, false>(prim_out, b, lds, seg, bt, act);
+    store_cot_lx_end<Q, QS, Real, false>(lam_out, b, lds + kRuns, seg, bt, act);
   }
 }
 
@@ -2037,8 +2298,8 @@ __device__ __forceinline__ bool batch_pos(const BatchArgs<Real>& A, const Params
     row = __builtin_amdgcn_readfirstlane((int)(lb * A.rpb + threadIdx.x / tw));
   }
   x = bx * tw + (int)(threadIdx.x % tw);
-  y = row % p.ny;
-  z = row / p.ny;
+  y = __builtin_amdgcn_readfirstlane(row % p.ny);
+  z = __builtin_amdgcn_readfirstlane(row / p.ny);
   return x < p.nx && z < p.nz;
 }
 
