@@ -22,7 +22,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbmadj.so")
 SOURCES = [os.path.join(CSRC, f) for f in ("lbm_adj.hip", "variants.hip")]
-DEPS = SOURCES + [os.path.join(CSRC, f) for f in ("kernels.hpp", "lattice.hpp", "context.hpp", "ops.hpp")] + [
+DEPS = SOURCES + [os.path.join(CSRC, f) for f in ("kernels.hpp", "lattice.hpp", "tiles.hpp", "context.hpp", "ops.hpp")] + [
     os.path.join(ROOT, "include", "lbm_adj.h")]
 # (Q, QS, variant mask) of the kernels; each is compiled for both precisions in
 # a translation unit of its own, so that the build runs in parallel

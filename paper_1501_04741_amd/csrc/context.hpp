@@ -73,6 +73,15 @@ inline int64_t row_pitch(int32_t nx, int32_t precision) {
   return ((int64_t)nx + per_line - 1) / per_line * per_line;
 }
 
+constexpr int kCus = 256;  // compute units of the GPU
+
+// Launches of several steps: the tile of a block and the steps per launch (1:
+// one-step launches only).
+struct TileChoice {
+  int tx = 0, ty = 0;
+  int ns = 1;
+};
+
 struct Plan {
   int Q = 0, QS = 0, QT = 0;
   int64_t N = 0;             // nodes
@@ -122,6 +131,7 @@ struct lbm_ctx {
   bool os_active = false; // one-shot iteration running (adjoint state in lam[lam_cur])
   bool state_lost = false; // a new design arrived after an adjoint had started: the primal
                            // buffers may hold recomputed states, so c->cur is not h^{t-1}
+  lbmh::TileChoice tile;   // several steps per launch
   int static_dev = -1;     // device whose static workspace this context uses (-1: caller's)
   std::string err;
 };
@@ -576,6 +586,37 @@ inline void* mom_slot(lbm_ctx* c, int64_t k) { return c->mom + (uint64_t)(k % c-
 // Trajectory segment holding the horizon's last step (0 in a store-all plan).
 inline int64_t last_segment(lbm_ctx* c) { return c->cfg.nsteps > 0 ? (c->cfg.nsteps - 1) / c->plan.C : 0; }
 inline void* other_pp(lbm_ctx* c, const void* cur) { return (cur == c->pp[0]) ? c->pp[1] : c->pp[0]; }
+
+// In-place plan with checkpoints (C < N): the working buffer is a slot of its own.
+inline bool checkpointed(const lbm_ctx* c) { return c->plan.inplace && c->plan.C < c->cfg.nsteps; }
+
+// Ping-pong steps cut into launches of at most `most` steps, about equally long,
+// as many of them as keep the number of launches odd or even with the number of
+// steps: a call leaves its result in the buffer that one-step launches would
+// have (a captured call of an even number of steps can be replayed).
+struct Split {
+  int64_t left, launches;
+  int ns = 0;  // steps of the current launch
+  Split(int64_t steps, int most) : left(steps), launches((steps + most - 1) / most) {
+    if ((launches ^ steps) & 1) ++launches;
+  }
+  bool next() {
+    if (left == 0) return false;
+    ns = (int)((left + launches - 1) / launches);
+    left -= ns;
+    --launches;
+    return true;
+  }
+};
+
+// In place, several steps per launch go to another buffer and the next launch
+// brings the state back: e steps there and e back (0: run single steps).  Both
+// buffers hold the layout of an even phase, so `done` (steps so far) and e are even.
+inline int steps_there_and_back(int64_t done, int64_t room, int most) {
+  if (done % 2 != 0) return 0;
+  const int64_t e = std::min<int64_t>(most, room / 2) & ~(int64_t)1;
+  return (int)e;
+}
 
 // Destination of h^k while recording: a checkpoint slot or a ping-pong buffer.
 inline void* rec_dst(lbm_ctx* c, int64_t k) {

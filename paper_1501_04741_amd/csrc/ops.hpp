@@ -5,6 +5,7 @@
 #pragma once
 
 #include "context.hpp"
+#include "tiles.hpp"
 
 namespace lbmh {
 
@@ -60,6 +61,90 @@ struct Ops {
     const dim3 g(blocks), b(kWave * A.kw * A.rpb);
     if (A.nt) adjoint_batch_acc<true>(st, A, g, b, acc);
     else adjoint_batch_acc<false>(st, A, g, b, acc);
+  }
+
+  // ---- several steps per launch (2D tiles, tiles.hpp)
+  static constexpr bool kTiled = Q == 9;
+  // Tile and steps per launch of the 2D lattices `cs` advance together: the least time per
+  // step by what tile launches were measured to take (us).  A launch: 3.75 (its gap, the
+  // first loads, the last stores) and the states read and written once at 5 TB/s; a step:
+  // 0.75 + k W, W the wavefronts of valid region nodes per SIMD, k = 0.37 (FP32 D2Q9), 0.62
+  // (with D2Q5), 1.3 and 2.0 in FP64.  Measured, whole evaluations: 256x128 in FP32, 6 steps
+  // of 16x8 tiles 2.0 us per step (one-step launches 4.2); 1024x512, 5 steps of 24x24
+  // tiles 7.4 (10.0); 512x256 with D2Q5, 4 steps of 16x16 tiles 4.2 (6.0); 64x32 in FP64, 7
+  // steps of 4x4 tiles 2.0 (4.5).
+  static TileChoice choose_tile(lbm_ctx* const* cs, int n) {
+    constexpr int kSizes[] = {4, 8, 12, 16, 20, 24, 28, 32, 48, 56};
+    constexpr int kMostThreads =
+        std::min<int>(tile_threads_max<Real>(), 65536 / (2 * tile_values<Q, QS>() * (int)sizeof(Real)));
+    constexpr double k = sizeof(Real) == 8 ? (QS > 0 ? 2.0 : 1.3) : (QS > 0 ? 0.62 : 0.37);
+    TileChoice best;
+    double least = 0, bytes = 0;
+    for (int q = 0; q < n; ++q) bytes += 2.0 * cs[q]->plan.state_bytes;
+    for (int ns = 2; ns <= 8; ++ns)
+      for (int ty : kSizes)
+        for (int tx : kSizes) {
+          const int threads = (tx + 2 * (ns - 1)) * (ty + 2 * (ns - 1));
+          if (threads > kMostThreads) continue;
+          int64_t blocks = 0, valid = 0;
+          for (int q = 0; q < n; ++q)
+            blocks += (int64_t)((cs[q]->cfg.nx + tx - 1) / tx) * ((cs[q]->cfg.ny + ty - 1) / ty);
+          for (int s = 0; s < ns; ++s) valid += (tx + 2 * s) * (ty + 2 * s);
+          const double per_cu = blocks <= 2 * kCus ? (double)((blocks + kCus - 1) / kCus) : (double)blocks / kCus;
+          const double waves = per_cu * ((threads + 63) / 64) / 4.0 * (double)valid / (ns * threads);
+          const double cost = (3.75 + bytes / 5e6) / ns + 0.75 + k * waves;
+          if (best.ns == 1 || cost < least) {
+            least = cost;
+            best = TileChoice{tx, ty, ns};
+          }
+        }
+    return best;
+  }
+  // called once, when the context is created
+  static void choose(lbm_ctx* c) {
+    if constexpr (kTiled) c->tile = choose_tile(&c, 1);
+  }
+  static dim3 tile_block(const TileChoice& t, int ns) { return dim3(t.tx + 2 * (ns - 1), t.ty + 2 * (ns - 1), 1); }
+  static size_t tile_bytes(const TileChoice& t, int ns) {
+    const dim3 b = tile_block(t, ns);
+    return ns > 1 ? (size_t)2 * tile_values<Q, QS>() * b.x * b.y * sizeof(Real) : 0;
+  }
+  static dim3 tile_grid(lbm_ctx* c, const TileChoice& t) {
+    return dim3((c->cfg.nx + t.tx - 1) / t.tx, (c->cfg.ny + t.ty - 1) / t.ty, 1);
+  }
+  static size_t mom_stride(lbm_ctx* c) { return c->plan.mom_bytes / sizeof(Real); }
+  // ns primal steps from src to dst (different buffers), recording from moment set mom when
+  // it is set.  inplace: both in the in-place layout of an even time, ns even.
+  static void primal_many(lbm_ctx* c, const void* src, void* dst, void* mom, int ns, bool inplace) {
+    if constexpr (kTiled) {
+      const TileChoice& t = c->tile;
+#define LBM_TILE(MOMV, ACCV)                                                                                        \
+  hipLaunchKernelGGL((k_primal_tile<Q, QS, Real, MOMV, V, ACCV>), tile_grid(c, t), tile_block(t, ns),               \
+                     tile_bytes(t, ns), c->stream, P(c), (const Real*)src, (Real*)dst, (const Real*)c->w, (Real*)mom, \
+                     mom_stride(c), ns)
+      if (inplace) {
+        if (mom) LBM_TILE(true, ACC_EVEN);
+        else LBM_TILE(false, ACC_EVEN);
+      } else {
+        if (mom) LBM_TILE(true, ACC_PP);
+        else LBM_TILE(false, ACC_PP);
+      }
+#undef LBM_TILE
+    }
+  }
+  // ns adjoint steps from lin to lout (different buffers), the first of them with moment set
+  // mom.  inplace: both in the layout after an even number of adjoint steps, ns even.
+  static void adjoint_many(lbm_ctx* c, const void* mom, const void* lin, void* lout, int ns, bool inplace) {
+    if constexpr (kTiled) {
+      const TileChoice& t = c->tile;
+#define LBM_TILE(ACCV)                                                                                              \
+  hipLaunchKernelGGL((k_adjoint_tile<Q, QS, Real, V, ACCV>), tile_grid(c, t), tile_block(t, ns),                    \
+                     tile_bytes(t, ns), c->stream, P(c), (const Real*)mom, (const Real*)lin, (Real*)lout,           \
+                     (const Real*)c->w, (Real*)c->grad, mom_stride(c), ns)
+      if (inplace) LBM_TILE(ACC_ODD);
+      else LBM_TILE(ACC_PP);
+#undef LBM_TILE
+    }
   }
 
   // streaming stores (and cotangent loads) when the state buffers a launch touches exceed the
@@ -339,29 +424,56 @@ void capture_window(lbm_ctx* c) {
   }
 }
 
+// Steps from time t that may share launches: up to `left`, within the segment
+// of t when segments matter (recorded: their ends are checkpoints and the moment
+// sets of one are contiguous), and before the window of a time-averaged objective,
+// whose states are captured one by one.
+inline int64_t steps_together(lbm_ctx* c, int64_t t, int64_t left, bool segments) {
+  if (segments) left = std::min<int64_t>(left, c->plan.C - t % c->plan.C);
+  if (c->plan.W > 1) left = std::min<int64_t>(left, c->cfg.nsteps - c->plan.W - t);
+  return std::max<int64_t>(left, 1);
+}
+
 template <class O>
 lbm_status RunPrimal<O>::run(lbm_ctx* c, int64_t nsteps, int record) {
   // A recorded run keeps the moments of the horizon's last segment only (all of
   // them in a store-all plan): the backward recomputes every earlier segment
   // from its checkpoint before it reads that segment's moments.
   const int64_t keep_from = last_segment(c) * c->plan.C;
+  const int most = c->tile.ns;
+  const auto mom = [&](int64_t t) { return record && t >= keep_from ? mom_slot(c, t) : nullptr; };
   if (c->plan.inplace) {
-    const bool ckpts = record && c->work != ckpt_slot(c, 0);  // checkpointed plan (C < N)
-    for (int64_t i = 0; i < nsteps; ++i) {
+    const bool ckpts = record && checkpointed(c);
+    for (int64_t i = 0; i < nsteps;) {
       if (ckpts && c->t % c->plan.C == 0)  // the state at t = sC, in its phase's layout
         O::copy(c, c->work, ckpt_slot(c, c->t / c->plan.C), (size_t)c->plan.QT * c->plan.Np);
-      O::primal_inplace(c, c->work, c->t, record && c->t >= keep_from ? mom_slot(c, c->t) : nullptr);
+      const int64_t room = steps_together(c, c->t, nsteps - i, record != 0);
+      const int e = c->os_active ? 0 : steps_there_and_back(c->t, room, most);
+      if (e) {  // through the adjoint buffer, free until the adjoint starts, and back
+        O::primal_many(c, c->work, c->lam[0], mom(c->t), e, true);
+        O::primal_many(c, c->lam[0], c->work, mom(c->t + e), e, true);
+        c->t += 2 * e;
+        i += 2 * e;
+        continue;
+      }
+      O::primal_inplace(c, c->work, c->t, mom(c->t));
       ++c->t;
+      ++i;
       capture_window<O>(c);
     }
     return launch_check(c, "in-place primal step");
   }
-  for (int64_t i = 0; i < nsteps; ++i) {
-    void* src = c->cur;
-    void* dst = record ? rec_dst(c, c->t) : other_pp(c, c->cur);
-    O::primal(c, src, dst, record && c->t >= keep_from ? mom_slot(c, c->t) : nullptr);
-    c->cur = dst;
-    ++c->t;
+  for (int64_t i = 0; i < nsteps;) {
+    const int64_t room = steps_together(c, c->t, nsteps - i, record != 0);
+    for (Split sp(room, most); sp.next();) {
+      void* src = c->cur;
+      void* dst = record ? rec_dst(c, c->t + sp.ns - 1) : other_pp(c, c->cur);
+      if (sp.ns > 1) O::primal_many(c, src, dst, mom(c->t), sp.ns, false);
+      else O::primal(c, src, dst, mom(c->t));
+      c->cur = dst;
+      c->t += sp.ns;
+      i += sp.ns;
+    }
     capture_window<O>(c);
   }
   return launch_check(c, "primal step");
@@ -388,10 +500,13 @@ void recompute_segment(lbm_ctx* c, int64_t s) {
   const int64_t C = c->plan.C;
   const int64_t end = std::min<int64_t>(s * C + C, c->rec_len);
   const void* src = ckpt_slot(c, s);
-  for (int64_t k = s * C; k < end; ++k) {
+  int64_t k = s * C;
+  for (Split sp(end - k, c->tile.ns); sp.next();) {
     void* dst = other_pp(c, src);
-    O::primal(c, src, dst, mom_slot(c, k));
+    if (sp.ns > 1) O::primal_many(c, src, dst, mom_slot(c, k), sp.ns, false);
+    else O::primal(c, src, dst, mom_slot(c, k));
     src = dst;
+    k += sp.ns;
   }
   c->mom_seg = s;
 }
@@ -399,13 +514,24 @@ void recompute_segment(lbm_ctx* c, int64_t s) {
 // In-place plan: recompute segment s inside its own checkpoint slot (its last
 // use), recording the moments of steps sC .. min(sC + C, N) - 1; step k runs in
 // the access pattern of its phase k mod 2, the layout the slot was saved in.
+// Several steps per launch go through the working buffer, whose state the
+// adjoint has consumed.
 template <class O>
 void recompute_segment_inplace(lbm_ctx* c, int64_t s) {
   Range r("lbm recompute segment (in place)");
   const int64_t C = c->plan.C;
   const int64_t end = std::min<int64_t>(s * C + C, c->rec_len);
   void* buf = ckpt_slot(c, s);
-  for (int64_t k = s * C; k < end; ++k) O::primal_inplace(c, buf, k, mom_slot(c, k));
+  for (int64_t k = s * C; k < end;) {
+    if (const int e = steps_there_and_back(k, end - k, c->tile.ns)) {
+      O::primal_many(c, buf, c->work, mom_slot(c, k), e, true);
+      O::primal_many(c, c->work, buf, mom_slot(c, k + e), e, true);
+      k += 2 * e;
+      continue;
+    }
+    O::primal_inplace(c, buf, k, mom_slot(c, k));
+    ++k;
+  }
   c->mom_seg = s;
 }
 
@@ -429,29 +555,46 @@ void start_adjoint(lbm_ctx* c) {
 template <class O>
 lbm_status RunAdjoint<O>::run(lbm_ctx* c, int64_t nsteps) {
   const int64_t C = c->plan.C;
+  const int most = c->tile.ns;
   // window states n < N whose objective terms enter lambda^n (none unless W > 1)
   const int64_t first = c->plan.W > 1 ? c->cfg.nsteps - c->plan.W + 1 : INT64_MAX;
   if (!c->adj_started) start_adjoint<O>(c);
   if (c->plan.inplace) {  // store-all never recomputes; C < N recomputes each segment in place
-    for (int64_t i = 0; i < nsteps; ++i) {
+    for (int64_t i = 0; i < nsteps;) {
       const int64_t n = c->t_adj - 1;
       const int64_t s = n / C;
       if (s != c->mom_seg) recompute_segment_inplace<O>(c, s);
-      O::adjoint_inplace(c, mom_slot(c, n), c->rec_len - c->t_adj);
+      const int64_t done = c->rec_len - c->t_adj;
+      const int64_t room = n >= first ? 1 : std::min<int64_t>(nsteps - i, n % C + 1);
+      if (const int e = steps_there_and_back(done, room, most)) {
+        // through the working buffer, whose state the adjoint has consumed, and back
+        O::adjoint_many(c, mom_slot(c, n), c->lam[0], c->work, e, true);
+        O::adjoint_many(c, mom_slot(c, n - e), c->work, c->lam[0], e, true);
+        c->t_adj -= 2 * e;
+        i += 2 * e;
+        continue;
+      }
+      O::adjoint_inplace(c, mom_slot(c, n), done);
       --c->t_adj;
+      ++i;
       if (n >= first)  // lambda^n now in the layout of its step count
         O::window_seed(c, n - first, c->lam[0], ((c->rec_len - c->t_adj) % 2 == 0) ? ACC_ODD : ACC_EVEN);
     }
     return launch_check(c, "in-place adjoint step");
   }
-  for (int64_t i = 0; i < nsteps; ++i) {
-    const int64_t n = c->t_adj - 1;
-    const int64_t s = n / C;
+  for (int64_t i = 0; i < nsteps;) {
+    const int64_t n0 = c->t_adj - 1;
+    const int64_t s = n0 / C;
     if (s != c->mom_seg) recompute_segment<O>(c, s);
-    O::adjoint(c, mom_slot(c, n), c->lam[c->lam_cur], c->lam[1 - c->lam_cur]);
-    c->lam_cur ^= 1;
-    --c->t_adj;
-    if (n >= first) O::window_seed(c, n - first, c->lam[c->lam_cur], ACC_PP);
+    for (Split sp(n0 >= first ? 1 : std::min<int64_t>(nsteps - i, n0 % C + 1), most); sp.next();) {
+      const void* mom = mom_slot(c, c->t_adj - 1);
+      if (sp.ns > 1) O::adjoint_many(c, mom, c->lam[c->lam_cur], c->lam[1 - c->lam_cur], sp.ns, false);
+      else O::adjoint(c, mom, c->lam[c->lam_cur], c->lam[1 - c->lam_cur]);
+      c->lam_cur ^= 1;
+      c->t_adj -= sp.ns;
+      i += sp.ns;
+    }
+    if (n0 >= first) O::window_seed(c, n0 - first, c->lam[c->lam_cur], ACC_PP);
   }
   return launch_check(c, "adjoint step");
 }
@@ -550,7 +693,10 @@ lbm_status RunGetDesign<O>::run(lbm_ctx* c, void* out) {
 }
 
 template <class O>
-lbm_status RunWriteStatic<O>::run(lbm_ctx* c) { return O::write_static(c); }
+lbm_status RunWriteStatic<O>::run(lbm_ctx* c) {
+  O::choose(c);
+  return O::write_static(c);
+}
 
 // Batched primal steps: one launch per step covers every context.
 // In place: per step, the checkpoint copies of members at t = sC (checkpointed
@@ -564,7 +710,7 @@ lbm_status primal_batch_inplace(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64_t 
   for (int64_t i = 0; i < nsteps; ++i) {
     for (int k = 0; k < n; ++k) {
       lbm_ctx* c = cs[k];
-      const bool ckpts = record && c->work != ckpt_slot(c, 0);  // checkpointed plan (C < N)
+      const bool ckpts = record && checkpointed(c);
       if (ckpts && c->t % c->plan.C == 0)
         O::copy(c, c->work, ckpt_slot(c, c->t / c->plan.C), (size_t)c->plan.QT * c->plan.Np);
     }
