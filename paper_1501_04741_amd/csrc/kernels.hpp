@@ -503,13 +503,14 @@ __device__ __forceinline__ int lx_span() { return blockDim.x * blockDim.y; }
 // the in-place adjoint takes it (8 x 128x96x96 batched: 0.79 -> 0.81) and the
 // in-place primal does not (FP64 256x128x128: 0.768 -> 0.738 with it).
 template <int Q, int QS, typename Real, int ACC, bool NT, bool NTS>
-__device__ __forceinline__ void load_state_lx(const Real* a, const Nbr& b, Real (&f)[Q], Real (&g)[QS > 0 ? QS : 1],
+__device__ __forceinline__ void load_state_lx(const Real* a, const Nbr& nb, Real (&f)[Q], Real (&g)[QS > 0 ? QS : 1],
                                               Real* lds, int seg, int bt, bool act) {
   static_assert(ACC != ACC_EVEN, "the even phase has no shifted access");
   using L = Lat<Q>;
   using S = SLat<QS>;
   using H = Shifted<Q, QS>;
   constexpr int QT = Q + QS;
+  const Nbr b = here(nb);
   constexpr bool odd = (ACC == ACC_ODD);
 #pragma unroll
   for (int j = 0; j < Q; ++j)
@@ -591,13 +592,14 @@ __device__ __forceinline__ void store_state_lx_end(Real* a, const Nbr& nb, const
 // pattern) with the x-shifted populations staged through LDS; the others as
 // load_cot.  NTS as for load_state_lx.
 template <int Q, int QS, typename Real, int ACC, bool NT, bool NTS>
-__device__ __forceinline__ void load_cot_lx(const Real* a, const Nbr& b, Real (&mu)[Q], Real (&nu)[QS > 0 ? QS : 1],
+__device__ __forceinline__ void load_cot_lx(const Real* a, const Nbr& nb, Real (&mu)[Q], Real (&nu)[QS > 0 ? QS : 1],
                                             Real* lds, int seg, int bt, bool act) {
   static_assert(ACC != ACC_EVEN, "the even pattern has no shifted access");
   using L = Lat<Q>;
   using S = SLat<QS>;
   using H = Shifted<Q, QS>;
   constexpr int QT = Q + QS;
+  const Nbr b = here(nb);
   constexpr bool odd = (ACC == ACC_ODD);
 #pragma unroll
   for (int j = 0; j < Q; ++j)
@@ -743,6 +745,19 @@ __device__ __forceinline__ Real edot(int ex, int ey, int ez, Real vx, Real vy, R
   return s;
 }
 
+// Switching function and derivative at one node: they depend on the design only,
+// so a launch of several steps forms them once.
+template <typename Real>
+struct SwitchValues {
+  Real G, dG;
+};
+template <typename Real>
+__device__ __forceinline__ SwitchValues<Real> switch_values(const Params<Real>& p, Real w) {
+  SwitchValues<Real> s;
+  switch_fn(p, w, s.G, s.dG);
+  return s;
+}
+
 // Density, velocity and switching values of an interior node's pre-collision
 // state: formed once for the recorded moments, the collision and the transposed
 // Jacobian.
@@ -753,7 +768,7 @@ struct Macro {
 };
 
 template <int Q, int QS, typename Real>
-__device__ __forceinline__ Macro<Real> macro_interior(const Params<Real>& p, Real wn, const Real (&f)[Q],
+__device__ __forceinline__ Macro<Real> macro_interior(const SwitchValues<Real>& sw, const Real (&f)[Q],
                                                       const Real (&g)[QS > 0 ? QS : 1]) {
   using L = Lat<Q>;
   Macro<Real> a;
@@ -776,7 +791,8 @@ __device__ __forceinline__ Macro<Real> macro_interior(const Params<Real>& p, Rea
 #pragma unroll
     for (int i = 0; i < QS; ++i) a.T += g[i];
   }
-  switch_fn(p, wn, a.G, a.dG);
+  a.G = sw.G;
+  a.dG = sw.dG;
   return a;
 }
 
@@ -1106,10 +1122,11 @@ __device__ __forceinline__ void boundary_moments(const Params<Real>& p, int cls,
 // lanes still to come stay live beside the finished ones, two sets of registers
 // (D3Q19 FP32 72 VGPRs instead of 52, 102 instead of 86 in FP64).
 template <int Q, int QS, typename Real, bool MOM, int V>
-__device__ __forceinline__ void primal_open(const Params<Real>& p, int cls, Real wn, int y, int z, Real (&f)[Q],
-                                            Real (&g)[QS > 0 ? QS : 1], Real (&m)[Mom<Q, QS, V>::N]) {
+__device__ __forceinline__ void primal_open(const Params<Real>& p, int cls, Real wn, const SwitchValues<Real>& sw,
+                                            int y, int z, Real (&f)[Q], Real (&g)[QS > 0 ? QS : 1],
+                                            Real (&m)[Mom<Q, QS, V>::N]) {
   if (cls == INTERIOR) {
-    const Macro<Real> a = macro_interior<Q, QS, Real>(p, wn, f, g);
+    const Macro<Real> a = macro_interior<Q, QS, Real>(sw, f, g);
     if constexpr (MOM) interior_moments<Q, QS, Real, V>(a, g, m);
     collide_interior<Q, QS, Real, V>(p, wn, a, f, g);
   }
@@ -1135,21 +1152,20 @@ __device__ __forceinline__ void primal_open(const Params<Real>& p, int cls, Real
 // inlet or outlet lane of a wave writes its part of every line by itself (batched
 // 8 x 96x48x48 with streaming stores: 22.1 -> 41.4 ms per pass).
 template <int Q, int QS, typename Real, bool MOM, int V, class Done>
-__device__ __forceinline__ void primal_operator(const Params<Real>& p, int cls, const Nbr& b,
-                                                const Real* __restrict__ w, Real* __restrict__ mom, int x, int y,
-                                                int z, Real (&f)[Q], Real (&g)[QS > 0 ? QS : 1], Done&& done) {
+__device__ __forceinline__ void primal_operator(const Params<Real>& p, int cls, const Nbr& b, Real wn,
+                                                Real* __restrict__ mom, int x, int y, int z, Real (&f)[Q],
+                                                Real (&g)[QS > 0 ? QS : 1], Done&& done) {
   if (cls == WALL) {
     collide_wall<Q, QS, Real>(p, x, y, f, g);
     done(f, g);
     return;
   }
   if (cls == PAD) return;
-  const Nbr bi = here(b);
-  const Real wn = *node_at(w, bi);
   Real m[Mom<Q, QS, V>::N];
-  primal_open<Q, QS, Real, MOM, V>(p, cls, wn, y, z, f, g, m);
+  primal_open<Q, QS, Real, MOM, V>(p, cls, wn, switch_values(p, wn), y, z, f, g, m);
   if constexpr (MOM) {
     if (has_moments(p, cls)) {
+      const Nbr bi = here(b);
 #pragma unroll
       for (int k = 0; k < Mom<Q, QS, V>::N; ++k) put<true>(node_at(mom + (size_t)k * p.Np, bi), m[k]);
     }
@@ -1169,15 +1185,18 @@ __device__ __forceinline__ void primal_node(const Params<Real>& p, const Real* s
                                             int z, Real* lds = nullptr, int seg = 0, int bt = 0, bool act = true) {
   constexpr bool is3d = (Q == 19);
   const Nbr b = make_nbr(p, x, y, z);
-  Real f[Q], g[QS > 0 ? QS : 1];
+  const int cls = act ? node_class(p, x, y, z, is3d) : PAD;
+  Real f[Q], g[QS > 0 ? QS : 1], wn = Real(0);
+  // before the staged loads and their barrier (see adjoint_node)
+  if (LX && cls != WALL && cls != PAD) wn = *node_at(w, here(b));
   if constexpr (LX)
     load_state_lx<Q, QS, Real, ACC, NT, NT && ACC == ACC_PP>(src, b, f, g, lds, seg, bt, act);
   else
     load_state<Q, QS, Real, ACC, NT && (ACC != ACC_EVEN || NTE)>(src, b, f, g);
-  const int cls = act ? node_class(p, x, y, z, is3d) : PAD;
+  if (!LX && cls != WALL && cls != PAD) wn = *node_at(w, here(b));
   constexpr bool kStaged = LX && ACC == ACC_ODD;
   if constexpr (kStaged) __syncthreads();
-  primal_operator<Q, QS, Real, MOM, V>(p, cls, b, w, mom, x, y, z, f, g, [&](const auto& fo, const auto& go) {
+  primal_operator<Q, QS, Real, MOM, V>(p, cls, b, wn, mom, x, y, z, f, g, [&](const auto& fo, const auto& go) {
     if constexpr (kStaged) store_state_lx<Q, QS, Real, NT>(dst, b, fo, go, lds, seg, bt);
     else store_state<Q, QS, Real, NT, ACC>(dst, b, fo, go);
   });
@@ -1625,7 +1644,7 @@ __device__ __forceinline__ void adjoint_interior(const Params<Real>& p, const Ma
 
 // Macroscopic values of an interior node from its recorded moments.
 template <int Q, int QS, typename Real, int V = 0>
-__device__ __forceinline__ Macro<Real> macro_recorded(const Params<Real>& p, Real wn,
+__device__ __forceinline__ Macro<Real> macro_recorded(const SwitchValues<Real>& sw,
                                                       const Real (&m)[Mom<Q, QS, V>::N]) {
   using M = Mom<Q, QS, V>;
   Macro<Real> a;
@@ -1645,7 +1664,8 @@ __device__ __forceinline__ Macro<Real> macro_recorded(const Params<Real>& p, Rea
       a.T = m[M::T];
     }
   }
-  switch_fn(p, wn, a.G, a.dG);
+  a.G = sw.G;
+  a.dG = sw.dG;
   return a;
 }
 
@@ -1797,10 +1817,11 @@ __device__ __forceinline__ void adjoint_outlet(const Params<Real>& p, const Real
 // The transposed operator of an interior, inlet or outlet node from its recorded
 // moments m: the cotangents (mu, nu) of its post-collision populations become
 // those of the pre-collision ones; gw is the gradient term (zero except at
-// interior nodes).  Branches as in primal_open.
+// interior nodes).  Branches as in primal_open (as an if-else chain: 96x48x48
+// evaluation 9.26 -> 9.56 ms, 2D tiles 3% slower).
 template <int Q, int QS, typename Real, int V>
 __device__ __forceinline__ void adjoint_open(const Params<Real>& p, int cls, Real wn,
-                                             const Real (&m)[Mom<Q, QS, V>::N], Real (&mu)[Q],
+                                             const SwitchValues<Real>& sw, const Real (&m)[Mom<Q, QS, V>::N], Real (&mu)[Q],
                                              Real (&nu)[QS > 0 ? QS : 1], Real& gw) {
   using M = Mom<Q, QS, V>;
   const auto keep = [&](const Real(&lf)[Q], const Real(&lg)[QS > 0 ? QS : 1]) {
@@ -1811,7 +1832,7 @@ __device__ __forceinline__ void adjoint_open(const Params<Real>& p, int cls, Rea
   };
   gw = Real(0);
   if (cls == INTERIOR) {
-    const Macro<Real> a = macro_recorded<Q, QS, Real, V>(p, wn, m);
+    const Macro<Real> a = macro_recorded<Q, QS, Real, V>(sw, m);
     Real g[QS > 0 ? QS : 1] = {}, lf[Q], lg[QS > 0 ? QS : 1];
     if constexpr (M::VD) {
 #pragma unroll
@@ -1839,12 +1860,23 @@ __device__ __forceinline__ void adjoint_open(const Params<Real>& p, int cls, Rea
 // primal_operator).  Moments are read once: streaming hint whatever the state
 // size, so that they do not evict a cotangent state the last-level cache could
 // hold between steps.
+template <int Q, int QS, typename Real, int V>
+struct AdjointInputs {
+  Real m[Mom<Q, QS, V>::N], wn, g0;  // a velocity inlet reads no moments (none are recorded)
+  __device__ __forceinline__ void load(const Params<Real>& p, const Nbr& nb, const Real* __restrict__ mom,
+                                       const Real* __restrict__ w, const Real* __restrict__ grad) {
+    const Nbr b = here(nb);
+#pragma unroll
+    for (int k = 0; k < Mom<Q, QS, V>::N; ++k) m[k] = get<true>(node_at(mom + (size_t)k * p.Np, b));
+    wn = *node_at(w, b);
+    g0 = *node_at(grad, b);
+  }
+};
 template <int Q, int QS, typename Real, int V, class Done>
 __device__ __forceinline__ void adjoint_operator(const Params<Real>& p, int cls, const Nbr& nb,
-                                                 const Real* __restrict__ mom, const Real* __restrict__ w,
-                                                 Real* __restrict__ grad, int x, int y, Real (&mu)[Q],
-                                                 Real (&nu)[QS > 0 ? QS : 1], Done&& done) {
-  using M = Mom<Q, QS, V>;
+                                                 const AdjointInputs<Q, QS, Real, V>& in, Real* __restrict__ grad,
+                                                 int x, int y, Real (&mu)[Q], Real (&nu)[QS > 0 ? QS : 1],
+                                                 Done&& done) {
   if (cls == WALL) {
     Real lf[Q], lg[QS > 0 ? QS : 1];
     adjoint_wall<Q, QS, Real>(p, x, y, mu, nu, lf, lg);
@@ -1852,13 +1884,9 @@ __device__ __forceinline__ void adjoint_operator(const Params<Real>& p, int cls,
     return;
   }
   if (cls == PAD) return;
-  const Nbr b = here(nb);
-  Real m[M::N], gw;  // a velocity inlet reads none of its moments (none are recorded)
-#pragma unroll
-  for (int k = 0; k < M::N; ++k) m[k] = get<true>(node_at(mom + (size_t)k * p.Np, b));
-  const Real wn = *node_at(w, b), g0 = *node_at(grad, b);
-  adjoint_open<Q, QS, Real, V>(p, cls, wn, m, mu, nu, gw);
-  if (cls == INTERIOR) *node_at(grad, b) = g0 + gw;
+  Real gw;
+  adjoint_open<Q, QS, Real, V>(p, cls, in.wn, switch_values(p, in.wn), in.m, mu, nu, gw);
+  if (cls == INTERIOR) *node_at(grad, here(nb)) = in.g0 + gw;
   done(mu, nu);
 }
 
@@ -1880,14 +1908,19 @@ __device__ __forceinline__ void adjoint_node(const Params<Real>& p, const Real* 
   constexpr int QSA = QS > 0 ? QS : 1;
   const Nbr b = make_nbr(p, x, y, z);
   Real mu[Q], nu[QSA];
+  const int cls = act ? node_class(p, x, y, z, is3d) : PAD;
+  AdjointInputs<Q, QS, Real, V> in;
+  // the moments come from HBM: asked for before the staged loads, whose barrier
+  // everything after them waits for (256x128x128 odd phase: 111.5 -> 109.5 us)
+  if (LX && cls != WALL && cls != PAD) in.load(p, b, mom, w, grad);
   if constexpr (LX)
     load_cot_lx<Q, QS, Real, ACC, NT, NT && (ACC == ACC_PP || NTE)>(lam_in, b, mu, nu, lds, seg, bt, act);
   else
     load_cot<Q, QS, Real, ACC, NT && (ACC != ACC_EVEN || NTE)>(lam_in, b, mu, nu);
-  const int cls = act ? node_class(p, x, y, z, is3d) : PAD;
+  if (!LX && cls != WALL && cls != PAD) in.load(p, b, mom, w, grad);
   constexpr bool kStaged = LX && ACC == ACC_ODD;
   if constexpr (kStaged) __syncthreads();
-  adjoint_operator<Q, QS, Real, V>(p, cls, b, mom, w, grad, x, y, mu, nu, [&](const auto& lf, const auto& lg) {
+  adjoint_operator<Q, QS, Real, V>(p, cls, b, in, grad, x, y, mu, nu, [&](const auto& lf, const auto& lg) {
     if constexpr (kStaged) store_cot_lx<Q, QS, Real, NT>(lam_out, b, lf, lg, lds, seg, bt);
     else store_cot<Q, QS, Real, NT, ACC>(lam_out, b, lf, lg);
   });
@@ -2149,38 +2182,33 @@ __device__ __forceinline__ void oneshot_node(const Params<Real>& p, const Real* 
   } else if (cls != PAD) {
     const Nbr bi = here(b);
     Real gw = Real(0), wn = *node_at(w, bi);
-    const auto take = [&]() {  // the new cotangent in place of the old one (see primal_open)
+    const auto take = [&]() {  // the new cotangent in place of the old one
 #pragma unroll
       for (int j = 0; j < Q; ++j) mu[j] = lf[j];
 #pragma unroll
       for (int i = 0; i < QS; ++i) nu[i] = lg[i];
     };
-    int c = cls;
-    if (c == INTERIOR) {
-      const Macro<Real> a = macro_interior<Q, QS, Real>(p, wn, f, g);
+    if (cls == INTERIOR) {
+      const Macro<Real> a = macro_interior<Q, QS, Real>(switch_values(p, wn), f, g);
       adjoint_interior<Q, QS, Real, V>(p, a, g, wn, mu, nu, lf, lg, gw);
       take();
       collide_interior<Q, QS, Real, V>(p, wn, a, f, g);
       const Real v = wn + zeta * (gw + c_pen * (Real(1) - Real(2) * wn));
       wn = v < Real(0) ? Real(0) : (v > Real(1) ? Real(1) : v);
-    }
-#pragma unroll
-    for (int side = 0; side < 2; ++side) {
-      asm("" : "+v"(c));
-      if (c != (side ? OUTLET : INLET)) continue;
+    } else {
       Real m[Mom<Q, QS, V>::N];
-      boundary_moments<Q, QS, Real, V>(p, side ? OUTLET : INLET, y, z, f, g, m);
+      boundary_moments<Q, QS, Real, V>(p, cls, y, z, f, g, m);
       double sf[Q], sg[QSA];
-      seed_values<Q, QS, Real>(p, side ? OUTLET : INLET, f, g, glob, sf, sg);
-      if (side) adjoint_outlet<Q, QS, Real, V>(p, m, mu, nu, lf, lg);
-      else adjoint_inlet<Q, QS, Real, V>(p, m, mu, nu, lf, lg);
+      seed_values<Q, QS, Real>(p, cls, f, g, glob, sf, sg);
+      if (cls == INLET) adjoint_inlet<Q, QS, Real, V>(p, m, mu, nu, lf, lg);
+      else adjoint_outlet<Q, QS, Real, V>(p, m, mu, nu, lf, lg);
 #pragma unroll
       for (int j = 0; j < Q; ++j) lf[j] += (Real)sf[j];
 #pragma unroll
       for (int i = 0; i < QS; ++i) lg[i] += (Real)sg[i];
       take();
-      if (side) collide_outlet<Q, QS, Real>(p, f, g);
-      else collide_inlet<Q, QS, Real>(p, y, z, f, g);
+      if (cls == INLET) collide_inlet<Q, QS, Real>(p, y, z, f, g);
+      else collide_outlet<Q, QS, Real>(p, f, g);
     }
     keep_cot(mu, nu);
     keep_state(f, g);

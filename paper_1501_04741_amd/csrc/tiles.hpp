@@ -79,6 +79,7 @@ __device__ __forceinline__ void tile_primal(const Params<Real>& p, const Real* _
   const int n = own_inode(b);
   const int cls = node_class(p, t.x, t.y, 0, false);
   const Real wn = w[n];
+  const SwitchValues<Real> sw = switch_values(p, wn);
   Real f[Q], g[QS > 0 ? QS : 1];
 #pragma unroll
   for (int j = 0; j < Q; ++j)
@@ -92,7 +93,7 @@ __device__ __forceinline__ void tile_primal(const Params<Real>& p, const Real* _
         collide_wall<Q, QS, Real>(p, t.x, t.y, f, g);
       } else {
         Real m[Mom<Q, QS, V>::N];
-        primal_open<Q, QS, Real, MOM, V>(p, cls, wn, t.y, 0, f, g, m);
+        primal_open<Q, QS, Real, MOM, V>(p, cls, wn, sw, t.y, 0, f, g, m);
         if constexpr (MOM) {
           if (t.mine && has_moments(p, cls)) {
 #pragma unroll
@@ -153,6 +154,7 @@ __device__ __forceinline__ void tile_adjoint(const Params<Real>& p, const Real* 
 #pragma unroll
   for (int i = 0; i < QS; ++i)
     nu[i] = lin[push_addr<QT>(b, Q + (ACC == ACC_ODD ? S::opp(i) : i), S::ex(i), S::ey(i), 0)];
+  const SwitchValues<Real> sw = switch_values(p, wn);
   Real gsum = t.mine && cls == INTERIOR ? grad[n] : Real(0);
   for (int s = 0;; ++s) {
     Real next[M::N];
@@ -172,7 +174,7 @@ __device__ __forceinline__ void tile_adjoint(const Params<Real>& p, const Real* 
         for (int i = 0; i < QS; ++i) nu[i] = lg[i];
       } else {
         Real gw;
-        adjoint_open<Q, QS, Real, V>(p, cls, wn, m, mu, nu, gw);
+        adjoint_open<Q, QS, Real, V>(p, cls, wn, sw, m, mu, nu, gw);
         gsum += gw;
       }
     }
