@@ -2278,7 +2278,8 @@ constexpr int kWave = 64;
 template <typename Real>
 struct BatchStatic {
   Params<Real> p;
-  int waves;  // waves per row: ceil(nx / 64)
+  int waves;          // waves per row: ceil(nx / 64)
+  size_t mom_stride;  // values from one moment set to the next
 };
 
 // Per-launch arguments, passed by value (about 1.2 KB for kBatchMax = 32).

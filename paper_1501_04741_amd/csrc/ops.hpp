@@ -77,18 +77,28 @@ struct Ops {
     constexpr int kSizes[] = {4, 8, 12, 16, 20, 24, 28, 32, 48, 56};
     constexpr int kMostThreads =
         std::min<int>(tile_threads_max<Real>(), 65536 / (2 * tile_values<Q, QS>() * (int)sizeof(Real)));
-    constexpr double k = sizeof(Real) == 8 ? (QS > 0 ? 2.0 : 1.3) : (QS > 0 ? 0.62 : 0.37);
+    constexpr double k = sizeof(Real) == 8 ? (QS > 0 ? 1.05 : 0.75) : (QS > 0 ? 0.62 : 0.37);
+    const int by = cs[0]->plan.inplace ? 2 : 1;
     TileChoice best;
     double least = 0, bytes = 0;
-    for (int q = 0; q < n; ++q) bytes += 2.0 * cs[q]->plan.state_bytes;
-    for (int ns = 2; ns <= 8; ++ns)
-      for (int ty : kSizes)
-        for (int tx : kSizes) {
+    int64_t tiles[std::size(kSizes)][std::size(kSizes)] = {};
+    for (int q = 0; q < n; ++q) {
+      bytes += 2.0 * cs[q]->plan.state_bytes;
+      int gx[std::size(kSizes)];
+      for (size_t i = 0; i < std::size(kSizes); ++i) gx[i] = (cs[q]->cfg.nx + kSizes[i] - 1) / kSizes[i];
+      for (size_t j = 0; j < std::size(kSizes); ++j) {
+        const int64_t gy = (cs[q]->cfg.ny + kSizes[j] - 1) / kSizes[j];
+        for (size_t i = 0; i < std::size(kSizes); ++i) tiles[j][i] += gx[i] * gy;
+      }
+    }
+    for (int ns = 2; ns <= 8; ns += by)
+      for (size_t j = 0; j < std::size(kSizes); ++j)
+        for (size_t i = 0; i < std::size(kSizes); ++i) {
+          const int tx = kSizes[i], ty = kSizes[j];
           const int threads = (tx + 2 * (ns - 1)) * (ty + 2 * (ns - 1));
-          if (threads > kMostThreads) continue;
-          int64_t blocks = 0, valid = 0;
-          for (int q = 0; q < n; ++q)
-            blocks += (int64_t)((cs[q]->cfg.nx + tx - 1) / tx) * ((cs[q]->cfg.ny + ty - 1) / ty);
+          if (threads > kMostThreads) break;
+          const int64_t blocks = tiles[j][i];
+          int64_t valid = 0;
           for (int s = 0; s < ns; ++s) valid += (tx + 2 * s) * (ty + 2 * s);
           const double per_cu = blocks <= 2 * kCus ? (double)((blocks + kCus - 1) / kCus) : (double)blocks / kCus;
           const double waves = per_cu * ((threads + 63) / 64) / 4.0 * (double)valid / (ns * threads);
@@ -141,6 +151,39 @@ struct Ops {
   hipLaunchKernelGGL((k_adjoint_tile<Q, QS, Real, V, ACCV>), tile_grid(c, t), tile_block(t, ns),                    \
                      tile_bytes(t, ns), c->stream, P(c), (const Real*)mom, (const Real*)lin, (Real*)lout,           \
                      (const Real*)c->w, (Real*)c->grad, mom_stride(c), ns)
+      if (inplace) LBM_TILE(ACC_ODD);
+      else LBM_TILE(ACC_PP);
+#undef LBM_TILE
+    }
+  }
+
+  // The same over the members of a batch: A's buffers, one tile t for all of them.
+  static int batch_tiles(lbm_ctx* c, const TileChoice& t) {
+    const dim3 g = tile_grid(c, t);
+    return (int)(g.x * g.y);
+  }
+  static void primal_many_batch(hipStream_t st, const BatchArgs<Real>& A, const TileChoice& t, int ns, bool inplace) {
+    if constexpr (kTiled) {
+      const dim3 g(A.start[A.n]);
+#define LBM_TILE(MOMV, ACCV)                                                                               \
+  hipLaunchKernelGGL((k_primal_tile_batch<Q, QS, Real, MOMV, V, ACCV>), g, tile_block(t, ns), tile_bytes(t, ns), st, \
+                     A, ns)
+      const bool mom = A.m[0] != nullptr;  // every member records, or none
+      if (inplace) {
+        if (mom) LBM_TILE(true, ACC_EVEN);
+        else LBM_TILE(false, ACC_EVEN);
+      } else {
+        if (mom) LBM_TILE(true, ACC_PP);
+        else LBM_TILE(false, ACC_PP);
+      }
+#undef LBM_TILE
+    }
+  }
+  static void adjoint_many_batch(hipStream_t st, const BatchArgs<Real>& A, const TileChoice& t, int ns, bool inplace) {
+    if constexpr (kTiled) {
+      const dim3 g(A.start[A.n]);
+#define LBM_TILE(ACCV)                                                                                   \
+  hipLaunchKernelGGL((k_adjoint_tile_batch<Q, QS, Real, V, ACCV>), g, tile_block(t, ns), tile_bytes(t, ns), st, A, ns)
       if (inplace) LBM_TILE(ACC_ODD);
       else LBM_TILE(ACC_PP);
 #undef LBM_TILE
@@ -247,6 +290,7 @@ struct Ops {
     BatchStatic<Real> h;
     h.p = P(c);
     h.waves = batch_waves(c);
+    h.mom_stride = mom_stride(c);
     hipLaunchKernelGGL((k_write_desc<Real>), dim3(1), dim3(64), 0, c->stream, h, (BatchStatic<Real>*)c->desc);
     return launch_check(c, "descriptor upload");
   }
@@ -698,21 +742,82 @@ lbm_status RunWriteStatic<O>::run(lbm_ctx* c) {
   return O::write_static(c);
 }
 
-// Batched primal steps: one launch per step covers every context.
+// Member k of a launch over tiles or row parts.
+template <class O>
+void batch_member(BatchArgs<typename O::RealT>& A, int k, lbm_ctx* c, const void* a, const void* b, void* to, void* m) {
+  using Real = typename O::RealT;
+  A.st[k] = (const BatchStatic<Real>*)c->desc;
+  A.w[k] = (const Real*)c->w;
+  A.g[k] = (Real*)c->grad;
+  A.a[k] = (const Real*)a;
+  A.b[k] = (const Real*)b;
+  A.c[k] = (Real*)to;
+  A.m[k] = (Real*)m;
+}
+
+// Launch geometry of a batch of members `mem`: one-step launches (tile.ns or ns 1) in
+// row parts, several steps in tiles.
+template <class O>
+int batch_geometry(BatchArgs<typename O::RealT>& A, lbm_ctx* const* mem, int nm, const TileChoice& tile, int ns) {
+  A.n = nm;
+  int total = 0;
+  if (ns == 1) {
+    A.kw = batch_block_waves(mem, nm);
+    A.rpb = batch_rows_per_block(mem, nm, A.kw);
+    A.lx = batch_lx(mem, nm, A.kw);
+  }
+  for (int k = 0; k < nm; ++k) {
+    A.start[k] = total;
+    total += ns > 1 ? O::batch_tiles(mem[k], tile) : O::batch_blocks(mem[k], A.kw, A.rpb);
+  }
+  A.start[nm] = total;
+  return total;
+}
+
+// The tile of a batched call: chosen for the members together, whose tiles share the
+// CUs (a batch of 8 fills them with larger tiles and fewer steps than one lattice).
+template <class O>
+TileChoice batch_tile_choice(lbm_ctx* const* cs, int n, int64_t nsteps) {
+  if constexpr (O::kTiled)
+    if (nsteps > 1) return O::choose_tile(cs, n);
+  return TileChoice();
+}
+
+// Batched primal steps: one launch per step, or per several steps of a 2D
+// lattice, covers every context.
 // In place: per step, the checkpoint copies of members at t = sC (checkpointed
 // plans), then one launch per phase among the members (two when their
-// parities differ), each member's buffer read and rewritten in place.
+// parities differ), each member's buffer read and rewritten in place; several
+// steps per launch when every member is at an even time.
 template <class O>
 lbm_status primal_batch_inplace(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64_t nsteps, int record) {
   using Real = typename O::RealT;
   BatchArgs<Real> A;
   std::memset(&A, 0, sizeof A);
-  for (int64_t i = 0; i < nsteps; ++i) {
+  const TileChoice tile = batch_tile_choice<O>(cs, n, nsteps);
+  for (int64_t i = 0; i < nsteps;) {
+    int e = tile.ns;
     for (int k = 0; k < n; ++k) {
       lbm_ctx* c = cs[k];
       const bool ckpts = record && checkpointed(c);
       if (ckpts && c->t % c->plan.C == 0)
         O::copy(c, c->work, ckpt_slot(c, c->t / c->plan.C), (size_t)c->plan.QT * c->plan.Np);
+      const int64_t room = steps_together(c, c->t, nsteps - i, record != 0);
+      e = std::min(e, c->os_active ? 0 : steps_there_and_back(c->t, room, tile.ns));
+    }
+    if (e > 1) {  // through the adjoint buffers and back
+      batch_geometry<O>(A, cs, n, tile, e);
+      for (int back = 0; back < 2; ++back) {
+        for (int k = 0; k < n; ++k) {
+          lbm_ctx* c = cs[k];
+          batch_member<O>(A, k, c, back ? c->lam[0] : c->work, nullptr, back ? c->work : c->lam[0],
+                          record ? mom_slot(c, c->t) : nullptr);
+          c->t += e;
+        }
+        O::primal_many_batch(c0->stream, A, tile, e, true);
+      }
+      i += 2 * e;
+      continue;
     }
     for (int phase = 0; phase < 2; ++phase) {
       lbm_ctx* mem[kBatchMax];
@@ -720,28 +825,14 @@ lbm_status primal_batch_inplace(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64_t 
       for (int k = 0; k < n; ++k)
         if (cs[k]->t % 2 == phase) mem[nm++] = cs[k];
       if (nm == 0) continue;
-      A.n = nm;
-      A.kw = batch_block_waves(mem, nm);
-      A.rpb = batch_rows_per_block(mem, nm, A.kw);
-      A.lx = batch_lx(mem, nm, A.kw);
+      const int total = batch_geometry<O>(A, mem, nm, tile, 1);
       batch_nt_inplace(mem, nm, !record, phase == 1, &A.nt, &A.nte);
-      int total = 0;
-      for (int k = 0; k < nm; ++k) {
-        lbm_ctx* c = mem[k];
-        A.start[k] = total;
-        A.st[k] = (const BatchStatic<Real>*)c->desc;
-        A.w[k] = (const Real*)c->w;
-        A.g[k] = (Real*)c->grad;
-        A.a[k] = (const Real*)c->work;
-        A.b[k] = nullptr;
-        A.c[k] = (Real*)c->work;
-        A.m[k] = record ? (Real*)mom_slot(c, c->t) : nullptr;
-        total += O::batch_blocks(c, A.kw, A.rpb);
-      }
-      A.start[nm] = total;
+      for (int k = 0; k < nm; ++k)
+        batch_member<O>(A, k, mem[k], mem[k]->work, nullptr, mem[k]->work, record ? mom_slot(mem[k], mem[k]->t) : nullptr);
       O::primal_batch(c0->stream, A, total, phase == 0 ? ACC_EVEN : ACC_ODD);
     }
     for (int k = 0; k < n; ++k) ++cs[k]->t;
+    ++i;
   }
   return launch_check(c0, "batched in-place primal step");
 }
@@ -752,30 +843,25 @@ lbm_status RunPrimalBatch<O>::run(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64_
   if (c0->plan.inplace) return primal_batch_inplace<O>(c0, cs, n, nsteps, record);
   BatchArgs<Real> A;
   std::memset(&A, 0, sizeof A);
-  A.n = n;
-  A.kw = batch_block_waves(cs, n);
-  A.rpb = batch_rows_per_block(cs, n, A.kw);
-  A.lx = batch_lx(cs, n, A.kw);
+  const TileChoice tile = batch_tile_choice<O>(cs, n, nsteps);
   A.nt = batch_nt(cs, n);
-  for (int64_t i = 0; i < nsteps; ++i) {
-    int total = 0;
-    for (int k = 0; k < n; ++k) {
-      lbm_ctx* c = cs[k];
-      void* dst = record ? rec_dst(c, c->t) : other_pp(c, c->cur);
-      A.start[k] = total;
-      A.st[k] = (const BatchStatic<Real>*)c->desc;
-      A.w[k] = (const Real*)c->w;
-      A.g[k] = (Real*)c->grad;
-      A.a[k] = (const Real*)c->cur;
-      A.b[k] = nullptr;
-      A.c[k] = (Real*)dst;
-      A.m[k] = record ? (Real*)mom_slot(c, c->t) : nullptr;
-      total += O::batch_blocks(c, A.kw, A.rpb);
-      c->cur = dst;
-      ++c->t;
+  int geometry = 0, total = 0;  // steps per launch that A's geometry is for
+  for (int64_t i = 0; i < nsteps;) {
+    int64_t room = nsteps - i;
+    for (int k = 0; k < n; ++k) room = std::min(room, steps_together(cs[k], cs[k]->t, room, record != 0));
+    for (Split sp(room, tile.ns); sp.next();) {
+      if (sp.ns != geometry) total = batch_geometry<O>(A, cs, n, tile, geometry = sp.ns);
+      for (int k = 0; k < n; ++k) {
+        lbm_ctx* c = cs[k];
+        void* dst = record ? rec_dst(c, c->t + sp.ns - 1) : other_pp(c, c->cur);
+        batch_member<O>(A, k, c, c->cur, nullptr, dst, record ? mom_slot(c, c->t) : nullptr);
+        c->cur = dst;
+        c->t += sp.ns;
+      }
+      if (sp.ns > 1) O::primal_many_batch(c0->stream, A, tile, sp.ns, false);
+      else O::primal_batch(c0->stream, A, total);
+      i += sp.ns;
     }
-    A.start[n] = total;
-    O::primal_batch(c0->stream, A, total);
   }
   return launch_check(c0, "batched primal step");
 }
@@ -785,17 +871,36 @@ lbm_status RunPrimalBatch<O>::run(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64_
 // segment whose moments are not held recompute it, batched together.
 // In place: members whose next step lies in a segment whose moments are not
 // held recompute it inside its checkpoint (single-context launches); then one
-// launch per cotangent pattern among the members.
+// launch per cotangent pattern among the members, or several steps per launch
+// when every member is in the seed's layout.
 template <class O>
 lbm_status adjoint_batch_inplace(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64_t nsteps) {
   using Real = typename O::RealT;
   BatchArgs<Real> A;
   std::memset(&A, 0, sizeof A);
-  for (int64_t i = 0; i < nsteps; ++i) {
+  const TileChoice tile = batch_tile_choice<O>(cs, n, nsteps);
+  for (int64_t i = 0; i < nsteps;) {
+    int e = tile.ns;
     for (int k = 0; k < n; ++k) {
       lbm_ctx* c = cs[k];
-      const int64_t s = (c->t_adj - 1) / c->plan.C;
+      const int64_t last = c->t_adj - 1, s = last / c->plan.C;
       if (s != c->mom_seg) recompute_segment_inplace<O>(c, s);
+      const int64_t room = std::min<int64_t>(nsteps - i, last % c->plan.C + 1);
+      e = std::min(e, steps_there_and_back(c->rec_len - c->t_adj, room, tile.ns));
+    }
+    if (e > 1) {  // through the working buffers and back
+      batch_geometry<O>(A, cs, n, tile, e);
+      for (int back = 0; back < 2; ++back) {
+        for (int k = 0; k < n; ++k) {
+          lbm_ctx* c = cs[k];
+          batch_member<O>(A, k, c, mom_slot(c, c->t_adj - 1), back ? c->work : c->lam[0], back ? c->lam[0] : c->work,
+                          nullptr);
+          c->t_adj -= e;
+        }
+        O::adjoint_many_batch(c0->stream, A, tile, e, true);
+      }
+      i += 2 * e;
+      continue;
     }
     for (int odd = 0; odd < 2; ++odd) {
       lbm_ctx* mem[kBatchMax];
@@ -803,31 +908,64 @@ lbm_status adjoint_batch_inplace(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64_t
       for (int k = 0; k < n; ++k)  // the cotangent is in the odd-pattern layout after an even step count
         if (((cs[k]->rec_len - cs[k]->t_adj) % 2 == 0) == (odd == 1)) mem[nm++] = cs[k];
       if (nm == 0) continue;
-      A.n = nm;
-      A.kw = batch_block_waves(mem, nm);
-      A.rpb = batch_rows_per_block(mem, nm, A.kw);
-      A.lx = batch_lx(mem, nm, A.kw);
+      const int total = batch_geometry<O>(A, mem, nm, tile, 1);
       batch_nt_inplace(mem, nm, false, false, &A.nt, &A.nte);
       A.nt = 1;  // the adjoint streams whatever the state size (see Ops::adjoint_inplace)
-      int total = 0;
-      for (int k = 0; k < nm; ++k) {
-        lbm_ctx* c = mem[k];
-        A.start[k] = total;
-        A.st[k] = (const BatchStatic<Real>*)c->desc;
-        A.w[k] = (const Real*)c->w;
-        A.g[k] = (Real*)c->grad;
-        A.a[k] = (const Real*)mom_slot(c, c->t_adj - 1);
-        A.m[k] = nullptr;
-        A.b[k] = (const Real*)c->lam[0];
-        A.c[k] = (Real*)c->lam[0];
-        total += O::batch_blocks(c, A.kw, A.rpb);
-      }
-      A.start[nm] = total;
+      for (int k = 0; k < nm; ++k)
+        batch_member<O>(A, k, mem[k], mom_slot(mem[k], mem[k]->t_adj - 1), mem[k]->lam[0], mem[k]->lam[0], nullptr);
       O::adjoint_batch(c0->stream, A, total, odd ? ACC_ODD : ACC_EVEN);
     }
     for (int k = 0; k < n; ++k) --cs[k]->t_adj;
+    ++i;
   }
   return launch_check(c0, "batched in-place adjoint step");
+}
+
+// Ping-pong: recomputes the segments of the next reverse steps that are not held.
+template <class O>
+void recompute_batch(lbm_ctx* c0, lbm_ctx* const* cs, int n, const TileChoice& tile) {
+  BatchArgs<typename O::RealT> A;
+  std::memset(&A, 0, sizeof A);
+  lbm_ctx* need[kBatchMax];
+  int64_t next[kBatchMax], end[kBatchMax];
+  const void* src[kBatchMax];
+  int nn = 0;
+  for (int k = 0; k < n; ++k) {
+    lbm_ctx* c = cs[k];
+    const int64_t s = (c->t_adj - 1) / c->plan.C;
+    if (s == c->mom_seg) continue;
+    need[nn] = c;
+    next[nn] = s * c->plan.C;
+    end[nn] = std::min<int64_t>(next[nn] + c->plan.C, c->rec_len);
+    src[nn++] = ckpt_slot(c, s);
+    c->mom_seg = s;
+  }
+  for (;;) {
+    lbm_ctx* mem[kBatchMax];  // the contexts with recompute steps left
+    int at[kBatchMax], nm = 0;
+    int64_t room = INT64_MAX;
+    for (int q = 0; q < nn; ++q)
+      if (next[q] < end[q]) {
+        room = std::min(room, end[q] - next[q]);
+        at[nm] = q;
+        mem[nm++] = need[q];
+      }
+    if (nm == 0) return;
+    A.nt = batch_nt(mem, nm);
+    int geometry = 0, total = 0;
+    for (Split sp(room, tile.ns); sp.next();) {
+      if (sp.ns != geometry) total = batch_geometry<O>(A, mem, nm, tile, geometry = sp.ns);
+      for (int k = 0; k < nm; ++k) {
+        const int q = at[k];
+        void* dst = other_pp(mem[k], src[q]);
+        batch_member<O>(A, k, mem[k], src[q], nullptr, dst, mom_slot(mem[k], next[q]));
+        src[q] = dst;
+        next[q] += sp.ns;
+      }
+      if (sp.ns > 1) O::primal_many_batch(c0->stream, A, tile, sp.ns, false);
+      else O::primal_batch(c0->stream, A, total);
+    }
+  }
 }
 
 template <class O>
@@ -838,82 +976,25 @@ lbm_status RunAdjointBatch<O>::run(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64
   if (c0->plan.inplace) return adjoint_batch_inplace<O>(c0, cs, n, nsteps);
   BatchArgs<Real> A;
   std::memset(&A, 0, sizeof A);
-  for (int64_t i = 0; i < nsteps; ++i) {
-    // segment recomputes
-    lbm_ctx* need[kBatchMax];
-    int64_t first[kBatchMax], last[kBatchMax], seg[kBatchMax];
-    const void* src[kBatchMax];
-    int nn = 0;
-    int64_t longest = 0;
-    for (int k = 0; k < n; ++k) {
-      lbm_ctx* c = cs[k];
-      const int64_t C = c->plan.C;
-      const int64_t s = (c->t_adj - 1) / C;
-      if (s == c->mom_seg) continue;
-      need[nn] = c;
-      seg[nn] = s;
-      first[nn] = s * C;
-      last[nn] = std::min<int64_t>(s * C + C, c->rec_len) - 1;
-      src[nn] = ckpt_slot(c, s);
-      longest = std::max<int64_t>(longest, last[nn] - first[nn] + 1);
-      ++nn;
-    }
-    for (int64_t r = 0; r < longest; ++r) {
-      lbm_ctx* mem[kBatchMax];  // the contexts with a recompute step r left
-      int nm = 0;
-      for (int q = 0; q < nn; ++q)
-        if (first[q] + r <= last[q]) mem[nm++] = need[q];
-      A.kw = batch_block_waves(mem, nm);
-      A.rpb = batch_rows_per_block(mem, nm, A.kw);
-      A.lx = batch_lx(mem, nm, A.kw);
-      A.nt = batch_nt(mem, nm);
-      int m = 0, total = 0;
-      for (int q = 0; q < nn; ++q) {
-        const int64_t kk = first[q] + r;
-        if (kk > last[q]) continue;
-        lbm_ctx* c = need[q];
-        void* dst = other_pp(c, src[q]);
-        A.start[m] = total;
-        A.st[m] = (const BatchStatic<Real>*)c->desc;
-        A.w[m] = (const Real*)c->w;
-        A.g[m] = (Real*)c->grad;
-        A.a[m] = (const Real*)src[q];
-        A.b[m] = nullptr;
-        A.c[m] = (Real*)dst;
-        A.m[m] = (Real*)mom_slot(c, kk);
-        total += O::batch_blocks(c, A.kw, A.rpb);
-        src[q] = dst;
-        ++m;
+  const TileChoice tile = batch_tile_choice<O>(cs, n, nsteps);
+  A.nt = 1;  // the adjoint streams whatever the state size (see Ops::adjoint_inplace)
+  int geometry = 0, total = 0;
+  for (int64_t i = 0; i < nsteps;) {
+    recompute_batch<O>(c0, cs, n, tile);
+    int64_t room = nsteps - i;
+    for (int k = 0; k < n; ++k) room = std::min(room, (cs[k]->t_adj - 1) % cs[k]->plan.C + 1);
+    for (Split sp(room, tile.ns); sp.next();) {
+      if (sp.ns != geometry) total = batch_geometry<O>(A, cs, n, tile, geometry = sp.ns);
+      for (int k = 0; k < n; ++k) {
+        lbm_ctx* c = cs[k];
+        batch_member<O>(A, k, c, mom_slot(c, c->t_adj - 1), c->lam[c->lam_cur], c->lam[1 - c->lam_cur], nullptr);
+        c->lam_cur ^= 1;
+        c->t_adj -= sp.ns;
       }
-      A.n = m;
-      A.start[m] = total;
-      O::primal_batch(c0->stream, A, total);
+      if (sp.ns > 1) O::adjoint_many_batch(c0->stream, A, tile, sp.ns, false);
+      else O::adjoint_batch(c0->stream, A, total);
+      i += sp.ns;
     }
-    for (int q = 0; q < nn; ++q) need[q]->mom_seg = seg[q];
-    // one reverse step for every context
-    int total = 0;
-    A.n = n;
-    A.kw = batch_block_waves(cs, n);
-    A.rpb = batch_rows_per_block(cs, n, A.kw);
-    A.lx = batch_lx(cs, n, A.kw);
-    A.nt = 1;  // the adjoint streams whatever the state size (see Ops::adjoint_inplace)
-    for (int k = 0; k < n; ++k) {
-      lbm_ctx* c = cs[k];
-      const int64_t nstep = c->t_adj - 1;
-      A.start[k] = total;
-      A.st[k] = (const BatchStatic<Real>*)c->desc;
-      A.w[k] = (const Real*)c->w;
-      A.g[k] = (Real*)c->grad;
-      A.a[k] = (const Real*)mom_slot(c, nstep);
-      A.m[k] = nullptr;
-      A.b[k] = (const Real*)c->lam[c->lam_cur];
-      A.c[k] = (Real*)c->lam[1 - c->lam_cur];
-      total += O::batch_blocks(c, A.kw, A.rpb);
-      c->lam_cur ^= 1;
-      --c->t_adj;
-    }
-    A.start[n] = total;
-    O::adjoint_batch(c0->stream, A, total);
   }
   return launch_check(c0, "batched adjoint step");
 }
