@@ -69,15 +69,18 @@ struct Ops {
   // step by what tile launches were measured to take (us).  A launch: 3.75 (its gap, the
   // first loads, the last stores) and the states read and written once at 5 TB/s; a step:
   // 0.75 + k W, W the wavefronts of valid region nodes per SIMD, k = 0.37 (FP32 D2Q9), 0.62
-  // (with D2Q5), 1.3 and 2.0 in FP64.  Measured, whole evaluations: 256x128 in FP32, 6 steps
-  // of 16x8 tiles 2.0 us per step (one-step launches 4.2); 1024x512, 5 steps of 24x24
-  // tiles 7.4 (10.0); 512x256 with D2Q5, 4 steps of 16x16 tiles 4.2 (6.0); 64x32 in FP64, 7
-  // steps of 4x4 tiles 2.0 (4.5).
+  // (with D2Q5), 0.9 and 2.5 in FP64.  In place only an even number of steps (see
+  // steps_there_and_back).  Measured, whole evaluations, per step (one-step launches): 256x128
+  // in FP32, 7 steps of 8x16 tiles 1.7 us (4.2); 1024x512, 5 steps of 16x32 tiles 6.6 (10.0);
+  // 512x256 with D2Q5, 5 steps of 16x16 tiles 3.6 (6.0); 64x32 in FP64, 7 steps of 4x4 tiles
+  // 1.6 (4.5); in place, 1100x560 with D2Q5 in FP64, 2 steps 21.0 (26.5), 4 steps 24.5.  No
+  // size is left to one-step launches: from 48x24 to 4096x2048 they were slower in every
+  // form but D2Q5 in place beyond the caches (2048x2048: 86.6, one-step 85.0).
   static TileChoice choose_tile(lbm_ctx* const* cs, int n) {
     constexpr int kSizes[] = {4, 8, 12, 16, 20, 24, 28, 32, 48, 56};
     constexpr int kMostThreads =
         std::min<int>(tile_threads_max<Real>(), 65536 / (2 * tile_values<Q, QS>() * (int)sizeof(Real)));
-    constexpr double k = sizeof(Real) == 8 ? (QS > 0 ? 1.05 : 0.75) : (QS > 0 ? 0.62 : 0.37);
+    constexpr double k = sizeof(Real) == 8 ? (QS > 0 ? 2.5 : 0.9) : (QS > 0 ? 0.62 : 0.37);
     const int by = cs[0]->plan.inplace ? 2 : 1;
     TileChoice best;
     double least = 0, bytes = 0;
@@ -119,8 +122,9 @@ struct Ops {
     const dim3 b = tile_block(t, ns);
     return ns > 1 ? (size_t)2 * tile_values<Q, QS>() * b.x * b.y * sizeof(Real) : 0;
   }
-  static dim3 tile_grid(lbm_ctx* c, const TileChoice& t) {
-    return dim3((c->cfg.nx + t.tx - 1) / t.tx, (c->cfg.ny + t.ty - 1) / t.ty, 1);
+  static TileRow tile_row(lbm_ctx* c, const TileChoice& t) { return TileRow::of((c->cfg.nx + t.tx - 1) / t.tx); }
+  static int tiles(lbm_ctx* c, const TileChoice& t) {
+    return ((c->cfg.nx + t.tx - 1) / t.tx) * ((c->cfg.ny + t.ty - 1) / t.ty);
   }
   static size_t mom_stride(lbm_ctx* c) { return c->plan.mom_bytes / sizeof(Real); }
   // ns primal steps from src to dst (different buffers), recording from moment set mom when
@@ -129,9 +133,9 @@ struct Ops {
     if constexpr (kTiled) {
       const TileChoice& t = c->tile;
 #define LBM_TILE(MOMV, ACCV)                                                                                        \
-  hipLaunchKernelGGL((k_primal_tile<Q, QS, Real, MOMV, V, ACCV>), tile_grid(c, t), tile_block(t, ns),               \
+  hipLaunchKernelGGL((k_primal_tile<Q, QS, Real, MOMV, V, ACCV>), dim3(tiles(c, t)), tile_block(t, ns),             \
                      tile_bytes(t, ns), c->stream, P(c), (const Real*)src, (Real*)dst, (const Real*)c->w, (Real*)mom, \
-                     mom_stride(c), ns)
+                     mom_stride(c), ns, tile_row(c, t))
       if (inplace) {
         if (mom) LBM_TILE(true, ACC_EVEN);
         else LBM_TILE(false, ACC_EVEN);
@@ -148,9 +152,9 @@ struct Ops {
     if constexpr (kTiled) {
       const TileChoice& t = c->tile;
 #define LBM_TILE(ACCV)                                                                                              \
-  hipLaunchKernelGGL((k_adjoint_tile<Q, QS, Real, V, ACCV>), tile_grid(c, t), tile_block(t, ns),                    \
+  hipLaunchKernelGGL((k_adjoint_tile<Q, QS, Real, V, ACCV>), dim3(tiles(c, t)), tile_block(t, ns),                  \
                      tile_bytes(t, ns), c->stream, P(c), (const Real*)mom, (const Real*)lin, (Real*)lout,           \
-                     (const Real*)c->w, (Real*)c->grad, mom_stride(c), ns)
+                     (const Real*)c->w, (Real*)c->grad, mom_stride(c), ns, tile_row(c, t))
       if (inplace) LBM_TILE(ACC_ODD);
       else LBM_TILE(ACC_PP);
 #undef LBM_TILE
@@ -158,10 +162,6 @@ struct Ops {
   }
 
   // The same over the members of a batch: A's buffers, one tile t for all of them.
-  static int batch_tiles(lbm_ctx* c, const TileChoice& t) {
-    const dim3 g = tile_grid(c, t);
-    return (int)(g.x * g.y);
-  }
   static void primal_many_batch(hipStream_t st, const BatchArgs<Real>& A, const TileChoice& t, int ns, bool inplace) {
     if constexpr (kTiled) {
       const dim3 g(A.start[A.n]);
@@ -768,7 +768,8 @@ int batch_geometry(BatchArgs<typename O::RealT>& A, lbm_ctx* const* mem, int nm,
   }
   for (int k = 0; k < nm; ++k) {
     A.start[k] = total;
-    total += ns > 1 ? O::batch_tiles(mem[k], tile) : O::batch_blocks(mem[k], A.kw, A.rpb);
+    if (ns > 1) A.row[k] = O::tile_row(mem[k], tile);
+    total += ns > 1 ? O::tiles(mem[k], tile) : O::batch_blocks(mem[k], A.kw, A.rpb);
   }
   A.start[nm] = total;
   return total;
