@@ -71,6 +71,7 @@ COUNTER_TRAFFIC = {
 }
 _COUNTER_SOURCES = ("paper_1501_04741_amd/csrc/kernels.hpp", "paper_1501_04741_amd/csrc/lattice.hpp",
                     "paper_1501_04741_amd/csrc/context.hpp", "paper_1501_04741_amd/csrc/ops.hpp",
+                    "paper_1501_04741_amd/csrc/tiles.hpp", "paper_1501_04741_amd/csrc/variants.hip",
                     "paper_1501_04741_amd/csrc/lbm_adj.hip", "paper_1501_04741_amd/build.py")
 
 

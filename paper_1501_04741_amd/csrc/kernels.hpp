@@ -634,31 +634,28 @@ __device__ __forceinline__ void load_cot_lx(const Real* a, const Nbr& nb, Real (
 }
 
 // Cotangent stores of the odd in-place pattern (lambda_j(x) to slot j of
-// x - e_j) with the x-shifted populations staged through LDS.
-template <int Q, int QS, typename Real, bool NT>
-__device__ __forceinline__ void store_cot_lx(Real* a, const Nbr& nb, const Real (&lf)[Q],
-                                             const Real (&lg)[QS > 0 ? QS : 1], Real* lds, int seg, int bt) {
+// x - e_j) with the x-shifted populations staged through LDS.  The others are
+// stored after the barrier too: in the branch of the node's class, before it, their
+// addresses and values cost the branches registers (D3Q7: 75 -> 68; 128x64x64 odd
+// phase 24.1 -> 22.8 us, 256x128x128 113.0 -> 112.4).
+template <int Q, int QS, typename Real>
+__device__ __forceinline__ void stage_cot_lx(const Nbr& b, const Real (&lf)[Q], const Real (&lg)[QS > 0 ? QS : 1],
+                                             Real* lds, int seg, int bt) {
   using L = Lat<Q>;
   using S = SLat<QS>;
   using H = Shifted<Q, QS>;
-  constexpr int QT = Q + QS;
-  const Nbr b = here(nb);
 #pragma unroll
   for (int j = 0; j < Q; ++j)
     if (L::ex(j) != 0) lds[H::flow_slot(j) * bt + seg + b.X[1 - L::ex(j)]] = lf[j];
 #pragma unroll
   for (int i = 0; i < QS; ++i)
     if (S::ex(i) != 0) lds[H::scalar_slot(i) * bt + seg + b.X[1 - S::ex(i)]] = lg[i];
-#pragma unroll
-  for (int j = 0; j < Q; ++j)
-    if (L::ex(j) == 0) put<NT>(pull_at<QT>(a, b, j, L::ex(j), L::ey(j), L::ez(j)), lf[j]);
-#pragma unroll
-  for (int i = 0; i < QS; ++i)
-    if (S::ex(i) == 0) put<NT>(pull_at<QT>(a, b, Q + i, S::ex(i), S::ey(i), S::ez(i)), lg[i]);
 }
 
-template <int Q, int QS, typename Real, bool NTS>
-__device__ __forceinline__ void store_cot_lx_end(Real* a, const Nbr& nb, const Real* lds, int seg, int bt, bool act) {
+template <int Q, int QS, typename Real, bool NT, bool NTS>
+__device__ __forceinline__ void store_cot_lx(Real* a, const Nbr& nb, const Real (&lf)[Q],
+                                             const Real (&lg)[QS > 0 ? QS : 1], const Real* lds, int seg, int bt,
+                                             bool act) {
   using L = Lat<Q>;
   using S = SLat<QS>;
   using H = Shifted<Q, QS>;
@@ -666,6 +663,12 @@ __device__ __forceinline__ void store_cot_lx_end(Real* a, const Nbr& nb, const R
   __syncthreads();
   if (!act) return;
   const Nbr b = here(nb);
+#pragma unroll
+  for (int j = 0; j < Q; ++j)
+    if (L::ex(j) == 0) put<NT>(pull_at<QT>(a, b, j, L::ex(j), L::ey(j), L::ez(j)), lf[j]);
+#pragma unroll
+  for (int i = 0; i < QS; ++i)
+    if (S::ex(i) == 0) put<NT>(pull_at<QT>(a, b, Q + i, S::ex(i), S::ey(i), S::ez(i)), lg[i]);
 #pragma unroll
   for (int j = 0; j < Q; ++j)
     if (L::ex(j) != 0)
@@ -1914,7 +1917,8 @@ __device__ __forceinline__ void adjoint_node(const Params<Real>& p, const Real* 
   const int cls = act ? node_class(p, x, y, z, is3d) : PAD;
   AdjointInputs<Q, QS, Real, V> in;
   // the moments come from HBM: asked for before the staged loads, whose barrier
-  // everything after them waits for (256x128x128 odd phase: 111.5 -> 109.5 us)
+  // everything after them waits for (256x128x128 odd phase 114.0 -> 113.0 us, 192x96x96
+  // 53.6 -> 53.0, 96x48x48 ping-pong 9.85 -> 9.64)
   if (LX && cls != WALL && cls != PAD) in.load(p, b, mom, w, grad);
   if constexpr (LX)
     load_cot_lx<Q, QS, Real, ACC, NT, NT && (ACC == ACC_PP || NTE)>(lam_in, b, mu, nu, lds, seg, bt, act);
@@ -1924,10 +1928,17 @@ __device__ __forceinline__ void adjoint_node(const Params<Real>& p, const Real* 
   constexpr bool kStaged = LX && ACC == ACC_ODD;
   if constexpr (kStaged) __syncthreads();
   adjoint_operator<Q, QS, Real, V>(p, cls, b, in, grad, x, y, mu, nu, [&](const auto& lf, const auto& lg) {
-    if constexpr (kStaged) store_cot_lx<Q, QS, Real, NT>(lam_out, b, lf, lg, lds, seg, bt);
-    else store_cot<Q, QS, Real, NT, ACC>(lam_out, b, lf, lg);
+    if constexpr (kStaged) {
+      stage_cot_lx<Q, QS, Real>(b, lf, lg, lds, seg, bt);
+#pragma unroll
+      for (int j = 0; j < Q; ++j) mu[j] = lf[j];
+#pragma unroll
+      for (int i = 0; i < QS; ++i) nu[i] = lg[i];
+    } else {
+      store_cot<Q, QS, Real, NT, ACC>(lam_out, b, lf, lg);
+    }
   });
-  if constexpr (kStaged) store_cot_lx_end<Q, QS, Real, NT && NTE>(lam_out, b, lds, seg, bt, act);
+  if constexpr (kStaged) store_cot_lx<Q, QS, Real, NT, NT && NTE>(lam_out, b, mu, nu, lds, seg, bt, act);
 }
 
 // LX as for k_primal.
@@ -2174,7 +2185,13 @@ __device__ __forceinline__ void oneshot_node(const Params<Real>& p, const Real* 
   constexpr bool kStaged = LX && ACC == ACC_ODD;
   if constexpr (kStaged) __syncthreads();
   const auto keep_cot = [&](const auto& lf, const auto& lg) {
-    if constexpr (kStaged) store_cot_lx<Q, QS, Real, NT>(lam_out, b, lf, lg, lds + kRuns, seg, bt);
+    if constexpr (kStaged) {
+      stage_cot_lx<Q, QS, Real>(b, lf, lg, lds + kRuns, seg, bt);
+#pragma unroll
+      for (int j = 0; j < Q; ++j) mu[j] = lf[j];
+#pragma unroll
+      for (int i = 0; i < QS; ++i) nu[i] = lg[i];
+    }
     else store_cot<Q, QS, Real, NT, ACC>(lam_out, b, lf, lg);
   };
   const auto keep_state = [&](const auto& fo, const auto& go) {
@@ -2239,7 +2256,7 @@ __device__ __forceinline__ void oneshot_node(const Params<Real>& p, const Real* 
   }
   if constexpr (kStaged) {
     store_state_lx_end<Q, QS, Real, false>(prim_out, b, lds, seg, bt, act);
-    store_cot_lx_end<Q, QS, Real, false>(lam_out, b, lds + kRuns, seg, bt, act);
+    store_cot_lx<Q, QS, Real, NT, false>(lam_out, b, mu, nu, lds + kRuns, seg, bt, act);
   }
 }
 
