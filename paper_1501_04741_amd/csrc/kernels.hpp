@@ -2162,7 +2162,7 @@ __global__ __launch_bounds__(256) void k_get_adjoint(Params<Real> p, const Real*
 // and the classes are one-armed branches.  As one branch per class doing both
 // (280 registers in FP64 with D3Q7, now 251; 128 in FP32, now 104), 100
 // iterations: 96x40x40 with a scalar in FP64 3.00 -> 2.63 ms, 131x67x45 MRT 3.20 ->
-// 2.92, 64x32x32 with a scalar 1.19 -> 1.09, 450x50x50 with a scalar 6.65 -> 6.60.
+// 2.92, 64x32x32 with a scalar 1.19 -> 1.09; 450x50x50 with a scalar stays at 6.6 to 6.7.
 template <int Q, int QS, typename Real, bool NT, int V, int ACC, bool LX = false>
 __device__ __forceinline__ void oneshot_node(const Params<Real>& p, const Real* prim_in, Real* prim_out,
                                              const Real* lam_in, Real* lam_out, Real* __restrict__ w,
