@@ -654,6 +654,25 @@ inline lbm_status check_batch(lbm_ctx* const* cs, int32_t n) {
   return LBM_OK;
 }
 
+// Kernel variant of a context (the V of its Ops).  A launch runs one variant, and the
+// variants record different moments: the members of a batch that differ in it are
+// launched apart.
+inline int kernel_variant(const lbm_ctx* c) {
+  return (c->cfg.collision == LBM_COLL_MRT ? kVarMRT : 0) | (blended_diffusivity(&c->cfg) ? kVarVD : 0);
+}
+
+// The members of a batch whose kernel variant is that of cs[first], from cs[first] on, when
+// no member before it has this variant (else none: they went with that one).
+inline int batch_part(lbm_ctx* const* cs, int n, int first, lbm_ctx** part) {
+  const int v = kernel_variant(cs[first]);
+  for (int k = 0; k < first; ++k)
+    if (kernel_variant(cs[k]) == v) return 0;
+  int m = 0;
+  for (int k = first; k < n; ++k)
+    if (kernel_variant(cs[k]) == v) part[m++] = cs[k];
+  return m;
+}
+
 inline void reset_times(lbm_ctx* c) {
   c->t = 0;
   c->rec_len = 0;

@@ -27,6 +27,22 @@ struct StaticSlot {
 std::mutex g_static_mu;
 StaticSlot g_static[kMaxDevices];
 
+// Runs a checked batch, one kernel variant after the other.
+template <template <class> class F, class... A>
+lbm_status dispatch_batch(lbm_ctx* const* cs, int n, A... a) {
+  for (int k = 0; k < n; ++k) {
+    lbm_ctx* part[kBatchMax];
+    const int m = batch_part(cs, n, k, part);
+    if (m == 0) continue;
+    const lbm_status s = dispatch<F>(part[0], (lbm_ctx* const*)part, m, a...);
+    if (s != LBM_OK) {
+      cs[0]->err = part[0]->err;
+      return s;
+    }
+  }
+  return LBM_OK;
+}
+
 }  // namespace
 
 // ================================================================= C ABI
@@ -357,7 +373,7 @@ lbm_status lbm_primal_steps_batch(lbm_ctx* const* ctxs, int32_t n, int64_t nstep
   }
   if (nsteps == 0) return LBM_OK;
   Range r("lbm_primal_steps_batch");
-  s = dispatch<RunPrimalBatch>(c0, ctxs, (int)n, nsteps, (int)(record != 0));
+  s = dispatch_batch<RunPrimalBatch>(ctxs, (int)n, nsteps, (int)(record != 0));
   for (int k = 0; k < n; ++k) {
     if (record) ctxs[k]->rec_len = ctxs[k]->t;
     else ctxs[k]->rec_open = false;
@@ -384,10 +400,10 @@ lbm_status lbm_adjoint_steps_batch(lbm_ctx* const* ctxs, int32_t n, int64_t nste
   }
   if (nsteps == 0) {
     // still seed, so that a zero-step call behaves like the single-context form
-    return dispatch<RunAdjointBatch>(c0, ctxs, (int)n, (int64_t)0);
+    return dispatch_batch<RunAdjointBatch>(ctxs, (int)n, (int64_t)0);
   }
   Range r("lbm_adjoint_steps_batch");
-  return dispatch<RunAdjointBatch>(c0, ctxs, (int)n, nsteps);
+  return dispatch_batch<RunAdjointBatch>(ctxs, (int)n, nsteps);
 }
 
 const char* lbm_last_error(const lbm_ctx* c) { return c ? c->err.c_str() : "NULL context"; }
