@@ -30,6 +30,15 @@
  *     lbm_create (NULL = the default stream).  Only calls with a "_host"
  *     output synchronise that stream.  Asynchronous HIP faults surface as
  *     LBM_EHIP at a later call.
+ *   - Capture: calls without "_host" outputs may be captured into a HIP graph.
+ *     A replay repeats the device work of the call as captured and moves no
+ *     time on the host, so a captured call that is replayed by itself has to
+ *     advance an even number of steps.  A captured call of an in-place
+ *     context writes no state but the one it streams, so it may be replayed
+ *     while the other is in use (primal steps between one-shot iterations).
+ *     A direct call on a 2D lattice may take its steps through the other
+ *     state's buffer when that is free: the adjoint's before an adjoint or
+ *     one-shot iteration, the primal's once the adjoint has started.
  *   - Layout: node n = x + nx*(y + ny*z), x fastest.  Every state the ABI
  *     exchanges (set/get state, adjoint, fields) is plane-major double:
  *     population j of node n at j*N + n, flow populations first, then scalar

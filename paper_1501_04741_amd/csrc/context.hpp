@@ -618,6 +618,20 @@ inline int steps_there_and_back(int64_t done, int64_t room, int most) {
   return (int)e;
 }
 
+// Most steps per launch of an in-place call.  The buffer that several steps go through
+// is free when the call is made: the adjoint buffer before an adjoint or one-shot
+// iteration, the working buffer once the adjoint has consumed its state.  A captured
+// call runs when its graph is replayed, and the buffer may be in use by then, so such a
+// call streams in its own buffer, one step per launch.
+inline int most_in_place(lbm_ctx* c, int most) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &s) != hipSuccess) {
+    (void)hipGetLastError();
+    return 1;
+  }
+  return s == hipStreamCaptureStatusNone ? most : 1;
+}
+
 // Destination of h^k while recording: a checkpoint slot or a ping-pong buffer.
 inline void* rec_dst(lbm_ctx* c, int64_t k) {
   const int64_t C = c->plan.C;

@@ -484,7 +484,7 @@ lbm_status RunPrimal<O>::run(lbm_ctx* c, int64_t nsteps, int record) {
   // them in a store-all plan): the backward recomputes every earlier segment
   // from its checkpoint before it reads that segment's moments.
   const int64_t keep_from = last_segment(c) * c->plan.C;
-  const int most = c->tile.ns;
+  const int most = c->plan.inplace ? most_in_place(c, c->tile.ns) : c->tile.ns;
   const auto mom = [&](int64_t t) { return record && t >= keep_from ? mom_slot(c, t) : nullptr; };
   if (c->plan.inplace) {
     const bool ckpts = record && checkpointed(c);
@@ -561,13 +561,13 @@ void recompute_segment(lbm_ctx* c, int64_t s) {
 // Several steps per launch go through the working buffer, whose state the
 // adjoint has consumed.
 template <class O>
-void recompute_segment_inplace(lbm_ctx* c, int64_t s) {
+void recompute_segment_inplace(lbm_ctx* c, int64_t s, int most) {
   Range r("lbm recompute segment (in place)");
   const int64_t C = c->plan.C;
   const int64_t end = std::min<int64_t>(s * C + C, c->rec_len);
   void* buf = ckpt_slot(c, s);
   for (int64_t k = s * C; k < end;) {
-    if (const int e = steps_there_and_back(k, end - k, c->tile.ns)) {
+    if (const int e = steps_there_and_back(k, end - k, most)) {
       O::primal_many(c, buf, c->work, mom_slot(c, k), e, true);
       O::primal_many(c, c->work, buf, mom_slot(c, k + e), e, true);
       k += 2 * e;
@@ -599,7 +599,7 @@ void start_adjoint(lbm_ctx* c) {
 template <class O>
 lbm_status RunAdjoint<O>::run(lbm_ctx* c, int64_t nsteps) {
   const int64_t C = c->plan.C;
-  const int most = c->tile.ns;
+  const int most = c->plan.inplace ? most_in_place(c, c->tile.ns) : c->tile.ns;
   // window states n < N whose objective terms enter lambda^n (none unless W > 1)
   const int64_t first = c->plan.W > 1 ? c->cfg.nsteps - c->plan.W + 1 : INT64_MAX;
   if (!c->adj_started) start_adjoint<O>(c);
@@ -607,7 +607,7 @@ lbm_status RunAdjoint<O>::run(lbm_ctx* c, int64_t nsteps) {
     for (int64_t i = 0; i < nsteps;) {
       const int64_t n = c->t_adj - 1;
       const int64_t s = n / C;
-      if (s != c->mom_seg) recompute_segment_inplace<O>(c, s);
+      if (s != c->mom_seg) recompute_segment_inplace<O>(c, s, most);
       const int64_t done = c->rec_len - c->t_adj;
       const int64_t room = n >= first ? 1 : std::min<int64_t>(nsteps - i, n % C + 1);
       if (const int e = steps_there_and_back(done, room, most)) {
@@ -795,7 +795,8 @@ lbm_status primal_batch_inplace(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64_t 
   using Real = typename O::RealT;
   BatchArgs<Real> A;
   std::memset(&A, 0, sizeof A);
-  const TileChoice tile = batch_tile_choice<O>(cs, n, nsteps);
+  TileChoice tile = batch_tile_choice<O>(cs, n, nsteps);
+  tile.ns = most_in_place(c0, tile.ns);
   for (int64_t i = 0; i < nsteps;) {
     int e = tile.ns;
     for (int k = 0; k < n; ++k) {
@@ -879,13 +880,14 @@ lbm_status adjoint_batch_inplace(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64_t
   using Real = typename O::RealT;
   BatchArgs<Real> A;
   std::memset(&A, 0, sizeof A);
-  const TileChoice tile = batch_tile_choice<O>(cs, n, nsteps);
+  TileChoice tile = batch_tile_choice<O>(cs, n, nsteps);
+  tile.ns = most_in_place(c0, tile.ns);
   for (int64_t i = 0; i < nsteps;) {
     int e = tile.ns;
     for (int k = 0; k < n; ++k) {
       lbm_ctx* c = cs[k];
       const int64_t last = c->t_adj - 1, s = last / c->plan.C;
-      if (s != c->mom_seg) recompute_segment_inplace<O>(c, s);
+      if (s != c->mom_seg) recompute_segment_inplace<O>(c, s, most_in_place(c, c->tile.ns));
       const int64_t room = std::min<int64_t>(nsteps - i, last % c->plan.C + 1);
       e = std::min(e, steps_there_and_back(c->rec_len - c->t_adj, room, tile.ns));
     }

@@ -100,3 +100,60 @@ def test_captured_even_call_replays(inplace):
             a.primal_steps(18)
             stream.synchronize()
             _same(_arrays(a.get_state()), _arrays(b.get_state()))
+
+
+def _steps(c, batch, call, *args):
+    if batch:
+        getattr(L, "lbm_%s_steps_batch" % call)([c.ctx], *args)
+    else:
+        getattr(c, call + "_steps")(*args)
+
+
+@pytest.mark.parametrize("batch", [False, True], ids=["alone", "batch"])
+def test_captured_inplace_steps_replayed_between_oneshot_iterations(batch):
+    """The adjoint buffer is free when the primal steps are captured and holds the
+    one-shot iteration's cotangent when the graph is replayed."""
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        w = torch.from_numpy(inputs.porosity(100, 60, 1, 0, 3, np.float32))
+        a, b = [Lbm(dict(HEAT, nx=100, ny=60, nz=1), nsteps=0, precision="fp32", inplace=True, stream=stream)
+                for _ in range(2)]
+        for c in (a, b):
+            c.set_design(w)
+            c.reset()
+            c.primal_steps(4)
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            _steps(b, batch, "primal", 18)
+        for _ in range(3):
+            graph.replay()
+            a.primal_steps(18)
+            for c in (a, b):
+                c.oneshot_steps(6, 1e-3)
+            stream.synchronize()
+            _same(_arrays(a.get_state(), a.get_adjoint(), [a.design(), a.gradient()]),
+                  _arrays(b.get_state(), b.get_adjoint(), [b.design(), b.gradient()]))
+
+
+@pytest.mark.parametrize("batch", [False, True], ids=["alone", "batch"])
+def test_captured_inplace_adjoint_replays_from_the_recorded_state(batch):
+    """Each replay of a captured adjoint seeds from the state that the run ended in."""
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        w = torch.from_numpy(inputs.porosity(100, 60, 1, 0, 3, np.float32))
+        a, b = [Lbm(dict(HEAT, nx=100, ny=60, nz=1), nsteps=400, precision="fp32", inplace=True, stream=stream)
+                for _ in range(2)]
+        for c in (a, b):
+            c.set_design(w)
+            c.reset()
+            c.primal_steps(400, record=True)
+        a.adjoint_steps(400)
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            _steps(b, batch, "adjoint", 400)
+        for _ in range(3):
+            graph.replay()
+            stream.synchronize()
+            _same(_arrays(a.get_adjoint(), [a.gradient()]), _arrays(b.get_adjoint(), [b.gradient()]))
