@@ -73,7 +73,12 @@ inline int64_t row_pitch(int32_t nx, int32_t precision) {
   return ((int64_t)nx + per_line - 1) / per_line * per_line;
 }
 
-constexpr int kCus = 256;  // compute units of the GPU
+constexpr int kCus = 256;                     // compute units of the GPU
+constexpr uint64_t kL2Bytes = 8 * (4ull << 20);  // the L2s of its XCDs together
+
+// What a launch of several steps does: unrecorded primal steps, recorded ones (a
+// forward or a recomputed segment), adjoint steps.
+enum LaunchKind : int { STEPS = 0, RECORDED = 1, ADJOINT = 2, LAUNCH_KINDS = 3 };
 
 // Launches of several steps: the tile of a block and the steps per launch (1:
 // one-step launches only).
@@ -131,7 +136,7 @@ struct lbm_ctx {
   bool os_active = false; // one-shot iteration running (adjoint state in lam[lam_cur])
   bool state_lost = false; // a new design arrived after an adjoint had started: the primal
                            // buffers may hold recomputed states, so c->cur is not h^{t-1}
-  lbmh::TileChoice tile;   // several steps per launch
+  lbmh::TileChoice tile[lbmh::LAUNCH_KINDS];  // several steps per launch
   int static_dev = -1;     // device whose static workspace this context uses (-1: caller's)
   std::string err;
 };
@@ -430,6 +435,36 @@ inline int batch_lx(lbm_ctx* const* cs, int n, int kw) {
   for (int k = 0; k < n; ++k)
     if (batch_waves(cs[k]) != kw) return 0;
   return 1;
+}
+
+// Whether the 2D lattices `cs` advance several steps per launch, in tiles, and whether the
+// tiles' rows are whole 64-byte pieces.  D2Q9 always gains (0.5-0.95 of the time of one-step
+// launches from 512x256 to 4096x2048); with D2Q5 there are three exceptions (times per step,
+// tiles against one-step launches; S: bytes of the states together).
+//  - In place, S between half the cache and about its size: one state stays in the cache,
+//    the two that the tiles go through do not.  Recorded 2400x1200 FP32 59.4 against 49.2 us,
+//    2048x1024 FP64 97.9 / 67.6 (S = 1.2 caches still 1.02); unrecorded FP64 1700x850 46.3 / 43.7.
+//  - Blended diffusivity records and reads 8 moment planes.  The adjoint reads them over the
+//    whole region of a tile: 2048x1024 FP32 59.5 / 53.6, in place 59.4 / 47.8, FP64 117.6 / 103.3;
+//    smaller lattices (700x350 FP32 0.90) and FP64 in place (1024x512 0.83) gain.
+//  - Rows that end inside a 64-byte piece store moments as parts of one: blended recorded
+//    1400x700 FP32 30.8 with 20-wide tiles, 17.4 with 16-wide ones (one-step 20.4); FP64 in
+//    place takes 16x12 for 12x16 (3000x2000 recorded 281 -> 213, adjoint 238 -> 211).
+struct TileRule {
+  bool tiles, whole_rows;
+};
+inline TileRule tile_rule(lbm_ctx* const* cs, int n, LaunchKind kind) {
+  const lbm_config& k = cs[0]->cfg;
+  if (k.scalar == 0) return {true, false};
+  uint64_t s = 0;
+  for (int q = 0; q < n; ++q) s += cs[q]->plan.state_bytes;
+  const bool fp64 = k.precision == LBM_FP64, inplace = cs[0]->plan.inplace, blended = blended_diffusivity(&k);
+  const uint64_t most = kind == RECORDED ? kLastLevelCacheBytes / 4 * 5 : kLastLevelCacheBytes;
+  const bool resident = inplace && 2 * s > kLastLevelCacheBytes && s <= most;  // one state is, two are not
+  const bool rows = (blended && kind == RECORDED) || (fp64 && inplace);
+  if (kind == RECORDED || (kind == STEPS && fp64)) return {!resident, rows};
+  if (kind == ADJOINT && blended) return {fp64 && inplace ? !resident : s <= (fp64 ? 12u : 20u) << 20, rows};
+  return {true, rows};
 }
 
 // Streaming stores and hints in a batched ping-pong launch: decided on the

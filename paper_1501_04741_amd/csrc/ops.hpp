@@ -73,16 +73,18 @@ struct Ops {
   // steps_there_and_back).  Measured, whole evaluations, per step (one-step launches): 256x128
   // in FP32, 7 steps of 8x16 tiles 1.7 us (4.2); 1024x512, 5 steps of 16x32 tiles 6.6 (10.0);
   // 512x256 with D2Q5, 5 steps of 16x16 tiles 3.6 (6.0); 64x32 in FP64, 7 steps of 4x4 tiles
-  // 1.6 (4.5); in place, 1100x560 with D2Q5 in FP64, 2 steps 21.0 (26.5), 4 steps 24.5.  No
-  // size is left to one-step launches: from 48x24 to 4096x2048 they were slower in every
-  // form but D2Q5 in place beyond the caches (2048x2048: 86.6, one-step 85.0).
-  static TileChoice choose_tile(lbm_ctx* const* cs, int n) {
+  // 1.6 (4.5); in place, 1100x560 with D2Q5 in FP64, 2 steps 21.0 (26.5), 4 steps 24.5.  The
+  // model compares tiles with each other only; where one-step launches are the faster
+  // ones is tile_rule's.  Whole rows cost no time where the states fit the L2s.
+  static TileChoice choose_tile(lbm_ctx* const* cs, int n, LaunchKind kind) {
     constexpr int kSizes[] = {4, 8, 12, 16, 20, 24, 28, 32, 48, 56};
     constexpr int kMostThreads =
         std::min<int>(tile_threads_max<Real>(), 65536 / (2 * tile_values<Q, QS>() * (int)sizeof(Real)));
     constexpr double k = sizeof(Real) == 8 ? (QS > 0 ? 2.5 : 0.9) : (QS > 0 ? 0.62 : 0.37);
     const int by = cs[0]->plan.inplace ? 2 : 1;
+    const TileRule rule = tile_rule(cs, n, kind);
     TileChoice best;
+    if (!rule.tiles) return best;
     double least = 0, bytes = 0;
     int64_t tiles[std::size(kSizes)][std::size(kSizes)] = {};
     for (int q = 0; q < n; ++q) {
@@ -98,6 +100,7 @@ struct Ops {
       for (size_t j = 0; j < std::size(kSizes); ++j)
         for (size_t i = 0; i < std::size(kSizes); ++i) {
           const int tx = kSizes[i], ty = kSizes[j];
+          if (rule.whole_rows && bytes > kL2Bytes && tx * sizeof(Real) % 64 != 0) continue;
           const int threads = (tx + 2 * (ns - 1)) * (ty + 2 * (ns - 1));
           if (threads > kMostThreads) break;
           const int64_t blocks = tiles[j][i];
@@ -115,7 +118,8 @@ struct Ops {
   }
   // called once, when the context is created
   static void choose(lbm_ctx* c) {
-    if constexpr (kTiled) c->tile = choose_tile(&c, 1);
+    if constexpr (kTiled)
+      for (const LaunchKind k : {STEPS, RECORDED, ADJOINT}) c->tile[k] = choose_tile(&c, 1, k);
   }
   static dim3 tile_block(const TileChoice& t, int ns) { return dim3(t.tx + 2 * (ns - 1), t.ty + 2 * (ns - 1), 1); }
   static size_t tile_bytes(const TileChoice& t, int ns) {
@@ -131,7 +135,7 @@ struct Ops {
   // it is set.  inplace: both in the in-place layout of an even time, ns even.
   static void primal_many(lbm_ctx* c, const void* src, void* dst, void* mom, int ns, bool inplace) {
     if constexpr (kTiled) {
-      const TileChoice& t = c->tile;
+      const TileChoice& t = c->tile[mom ? RECORDED : STEPS];
 #define LBM_TILE(MOMV, ACCV)                                                                                        \
   hipLaunchKernelGGL((k_primal_tile<Q, QS, Real, MOMV, V, ACCV>), dim3(tiles(c, t)), tile_block(t, ns),             \
                      tile_bytes(t, ns), c->stream, P(c), (const Real*)src, (Real*)dst, (const Real*)c->w, (Real*)mom, \
@@ -150,7 +154,7 @@ struct Ops {
   // mom.  inplace: both in the layout after an even number of adjoint steps, ns even.
   static void adjoint_many(lbm_ctx* c, const void* mom, const void* lin, void* lout, int ns, bool inplace) {
     if constexpr (kTiled) {
-      const TileChoice& t = c->tile;
+      const TileChoice& t = c->tile[ADJOINT];
 #define LBM_TILE(ACCV)                                                                                              \
   hipLaunchKernelGGL((k_adjoint_tile<Q, QS, Real, V, ACCV>), dim3(tiles(c, t)), tile_block(t, ns),                  \
                      tile_bytes(t, ns), c->stream, P(c), (const Real*)mom, (const Real*)lin, (Real*)lout,           \
@@ -484,15 +488,18 @@ lbm_status RunPrimal<O>::run(lbm_ctx* c, int64_t nsteps, int record) {
   // them in a store-all plan): the backward recomputes every earlier segment
   // from its checkpoint before it reads that segment's moments.
   const int64_t keep_from = last_segment(c) * c->plan.C;
-  const int most = c->plan.inplace ? most_in_place(c, c->tile.ns) : c->tile.ns;
   const auto mom = [&](int64_t t) { return record && t >= keep_from ? mom_slot(c, t) : nullptr; };
+  const auto most = [&](int64_t t) {
+    const int ns = c->tile[mom(t) ? RECORDED : STEPS].ns;
+    return c->plan.inplace ? most_in_place(c, ns) : ns;
+  };
   if (c->plan.inplace) {
     const bool ckpts = record && checkpointed(c);
     for (int64_t i = 0; i < nsteps;) {
       if (ckpts && c->t % c->plan.C == 0)  // the state at t = sC, in its phase's layout
         O::copy(c, c->work, ckpt_slot(c, c->t / c->plan.C), (size_t)c->plan.QT * c->plan.Np);
       const int64_t room = steps_together(c, c->t, nsteps - i, record != 0);
-      const int e = c->os_active ? 0 : steps_there_and_back(c->t, room, most);
+      const int e = c->os_active ? 0 : steps_there_and_back(c->t, room, most(c->t));
       if (e) {  // through the adjoint buffer, free until the adjoint starts, and back
         O::primal_many(c, c->work, c->lam[0], mom(c->t), e, true);
         O::primal_many(c, c->lam[0], c->work, mom(c->t + e), e, true);
@@ -509,7 +516,7 @@ lbm_status RunPrimal<O>::run(lbm_ctx* c, int64_t nsteps, int record) {
   }
   for (int64_t i = 0; i < nsteps;) {
     const int64_t room = steps_together(c, c->t, nsteps - i, record != 0);
-    for (Split sp(room, most); sp.next();) {
+    for (Split sp(room, most(c->t)); sp.next();) {
       void* src = c->cur;
       void* dst = record ? rec_dst(c, c->t + sp.ns - 1) : other_pp(c, c->cur);
       if (sp.ns > 1) O::primal_many(c, src, dst, mom(c->t), sp.ns, false);
@@ -545,7 +552,7 @@ void recompute_segment(lbm_ctx* c, int64_t s) {
   const int64_t end = std::min<int64_t>(s * C + C, c->rec_len);
   const void* src = ckpt_slot(c, s);
   int64_t k = s * C;
-  for (Split sp(end - k, c->tile.ns); sp.next();) {
+  for (Split sp(end - k, c->tile[RECORDED].ns); sp.next();) {
     void* dst = other_pp(c, src);
     if (sp.ns > 1) O::primal_many(c, src, dst, mom_slot(c, k), sp.ns, false);
     else O::primal(c, src, dst, mom_slot(c, k));
@@ -561,7 +568,8 @@ void recompute_segment(lbm_ctx* c, int64_t s) {
 // Several steps per launch go through the working buffer, whose state the
 // adjoint has consumed.
 template <class O>
-void recompute_segment_inplace(lbm_ctx* c, int64_t s, int most) {
+void recompute_segment_inplace(lbm_ctx* c, int64_t s) {
+  const int most = most_in_place(c, c->tile[RECORDED].ns);
   Range r("lbm recompute segment (in place)");
   const int64_t C = c->plan.C;
   const int64_t end = std::min<int64_t>(s * C + C, c->rec_len);
@@ -599,7 +607,7 @@ void start_adjoint(lbm_ctx* c) {
 template <class O>
 lbm_status RunAdjoint<O>::run(lbm_ctx* c, int64_t nsteps) {
   const int64_t C = c->plan.C;
-  const int most = c->plan.inplace ? most_in_place(c, c->tile.ns) : c->tile.ns;
+  const int most = c->plan.inplace ? most_in_place(c, c->tile[ADJOINT].ns) : c->tile[ADJOINT].ns;
   // window states n < N whose objective terms enter lambda^n (none unless W > 1)
   const int64_t first = c->plan.W > 1 ? c->cfg.nsteps - c->plan.W + 1 : INT64_MAX;
   if (!c->adj_started) start_adjoint<O>(c);
@@ -607,7 +615,7 @@ lbm_status RunAdjoint<O>::run(lbm_ctx* c, int64_t nsteps) {
     for (int64_t i = 0; i < nsteps;) {
       const int64_t n = c->t_adj - 1;
       const int64_t s = n / C;
-      if (s != c->mom_seg) recompute_segment_inplace<O>(c, s, most);
+      if (s != c->mom_seg) recompute_segment_inplace<O>(c, s);
       const int64_t done = c->rec_len - c->t_adj;
       const int64_t room = n >= first ? 1 : std::min<int64_t>(nsteps - i, n % C + 1);
       if (const int e = steps_there_and_back(done, room, most)) {
@@ -778,9 +786,9 @@ int batch_geometry(BatchArgs<typename O::RealT>& A, lbm_ctx* const* mem, int nm,
 // The tile of a batched call: chosen for the members together, whose tiles share the
 // CUs (a batch of 8 fills them with larger tiles and fewer steps than one lattice).
 template <class O>
-TileChoice batch_tile_choice(lbm_ctx* const* cs, int n, int64_t nsteps) {
+TileChoice batch_tile_choice(lbm_ctx* const* cs, int n, int64_t nsteps, LaunchKind kind) {
   if constexpr (O::kTiled)
-    if (nsteps > 1) return O::choose_tile(cs, n);
+    if (nsteps > 1) return O::choose_tile(cs, n, kind);
   return TileChoice();
 }
 
@@ -795,7 +803,7 @@ lbm_status primal_batch_inplace(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64_t 
   using Real = typename O::RealT;
   BatchArgs<Real> A;
   std::memset(&A, 0, sizeof A);
-  TileChoice tile = batch_tile_choice<O>(cs, n, nsteps);
+  TileChoice tile = batch_tile_choice<O>(cs, n, nsteps, record ? RECORDED : STEPS);
   tile.ns = most_in_place(c0, tile.ns);
   for (int64_t i = 0; i < nsteps;) {
     int e = tile.ns;
@@ -845,7 +853,7 @@ lbm_status RunPrimalBatch<O>::run(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64_
   if (c0->plan.inplace) return primal_batch_inplace<O>(c0, cs, n, nsteps, record);
   BatchArgs<Real> A;
   std::memset(&A, 0, sizeof A);
-  const TileChoice tile = batch_tile_choice<O>(cs, n, nsteps);
+  const TileChoice tile = batch_tile_choice<O>(cs, n, nsteps, record ? RECORDED : STEPS);
   A.nt = batch_nt(cs, n);
   int geometry = 0, total = 0;  // steps per launch that A's geometry is for
   for (int64_t i = 0; i < nsteps;) {
@@ -880,14 +888,14 @@ lbm_status adjoint_batch_inplace(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64_t
   using Real = typename O::RealT;
   BatchArgs<Real> A;
   std::memset(&A, 0, sizeof A);
-  TileChoice tile = batch_tile_choice<O>(cs, n, nsteps);
+  TileChoice tile = batch_tile_choice<O>(cs, n, nsteps, ADJOINT);
   tile.ns = most_in_place(c0, tile.ns);
   for (int64_t i = 0; i < nsteps;) {
     int e = tile.ns;
     for (int k = 0; k < n; ++k) {
       lbm_ctx* c = cs[k];
       const int64_t last = c->t_adj - 1, s = last / c->plan.C;
-      if (s != c->mom_seg) recompute_segment_inplace<O>(c, s, most_in_place(c, c->tile.ns));
+      if (s != c->mom_seg) recompute_segment_inplace<O>(c, s);
       const int64_t room = std::min<int64_t>(nsteps - i, last % c->plan.C + 1);
       e = std::min(e, steps_there_and_back(c->rec_len - c->t_adj, room, tile.ns));
     }
@@ -979,7 +987,7 @@ lbm_status RunAdjointBatch<O>::run(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64
   if (c0->plan.inplace) return adjoint_batch_inplace<O>(c0, cs, n, nsteps);
   BatchArgs<Real> A;
   std::memset(&A, 0, sizeof A);
-  const TileChoice tile = batch_tile_choice<O>(cs, n, nsteps);
+  const TileChoice tile = batch_tile_choice<O>(cs, n, nsteps, ADJOINT);
   A.nt = 1;  // the adjoint streams whatever the state size (see Ops::adjoint_inplace)
   int geometry = 0, total = 0;
   for (int64_t i = 0; i < nsteps;) {

@@ -157,3 +157,20 @@ def test_captured_inplace_adjoint_replays_from_the_recorded_state(batch):
             graph.replay()
             stream.synchronize()
             _same(_arrays(a.get_adjoint(), [a.gradient()]), _arrays(b.get_adjoint(), [b.gradient()]))
+
+
+@pytest.mark.parametrize("size, prec, inplace, solid", [
+    ((1021, 509), "fp32", False, 3.0), ((1024, 512), "fp32", True, 3.0), ((701, 353), "fp64", True, 0.0),
+    ((704, 352), "fp64", True, 3.0)], ids=["vd_pp", "vd_ip", "fp64_ip", "fp64_vd_ip"])
+def test_tiles_of_whole_rows_bitwise_equal_one_step_launches(size, prec, inplace, solid):
+    """States beyond the L2s with D2Q5: recorded runs (and all in place in FP64) take tiles of
+    whole 64-byte rows, the blended adjoint of these sizes one step per launch."""
+    one, many = [_context(dict(HEAT, tau_s_solid=solid), size, prec, inplace, 16, 0, 0) for _ in range(2)]
+    for _ in range(16):
+        one.primal_steps(1, record=True)
+    many.primal_steps(16, record=True)
+    _same(_arrays(one.get_state()), _arrays(many.get_state()))
+    for _ in range(16):
+        one.adjoint_steps(1)
+    many.adjoint_steps(16)
+    _same(_arrays(one.get_adjoint(), [one.gradient()]), _arrays(many.get_adjoint(), [many.gradient()]))
