@@ -783,12 +783,15 @@ int batch_geometry(BatchArgs<typename O::RealT>& A, lbm_ctx* const* mem, int nm,
   return total;
 }
 
-// The tile of a batched call: chosen for the members together, whose tiles share the
-// CUs (a batch of 8 fills them with larger tiles and fewer steps than one lattice).
+// The tile of the batched steps to come: chosen for the members together, whose tiles
+// share the CUs (a batch of 8 fills them with larger tiles and fewer steps than one
+// lattice).  Fewer steps than a launch of several needs (see Split and
+// steps_there_and_back) are not worth the choice: two steps of 32 lattices of 64x32
+// take 13.0 us, 13.6 with it.
 template <class O>
 TileChoice batch_tile_choice(lbm_ctx* const* cs, int n, int64_t nsteps, LaunchKind kind) {
   if constexpr (O::kTiled)
-    if (nsteps > 1) return O::choose_tile(cs, n, kind);
+    if (nsteps >= (cs[0]->plan.inplace ? 4 : 3)) return O::choose_tile(cs, n, kind);
   return TileChoice();
 }
 
@@ -932,9 +935,10 @@ lbm_status adjoint_batch_inplace(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64_t
   return launch_check(c0, "batched in-place adjoint step");
 }
 
-// Ping-pong: recomputes the segments of the next reverse steps that are not held.
+// Ping-pong: recomputes the segments of the next reverse steps that are not held, in
+// launches of its own length, however many reverse steps the call asks for.
 template <class O>
-void recompute_batch(lbm_ctx* c0, lbm_ctx* const* cs, int n, const TileChoice& tile) {
+void recompute_batch(lbm_ctx* c0, lbm_ctx* const* cs, int n) {
   BatchArgs<typename O::RealT> A;
   std::memset(&A, 0, sizeof A);
   lbm_ctx* need[kBatchMax];
@@ -962,6 +966,7 @@ void recompute_batch(lbm_ctx* c0, lbm_ctx* const* cs, int n, const TileChoice& t
         mem[nm++] = need[q];
       }
     if (nm == 0) return;
+    const TileChoice tile = batch_tile_choice<O>(mem, nm, room, RECORDED);
     A.nt = batch_nt(mem, nm);
     int geometry = 0, total = 0;
     for (Split sp(room, tile.ns); sp.next();) {
@@ -991,7 +996,7 @@ lbm_status RunAdjointBatch<O>::run(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64
   A.nt = 1;  // the adjoint streams whatever the state size (see Ops::adjoint_inplace)
   int geometry = 0, total = 0;
   for (int64_t i = 0; i < nsteps;) {
-    recompute_batch<O>(c0, cs, n, tile);
+    recompute_batch<O>(c0, cs, n);
     int64_t room = nsteps - i;
     for (int k = 0; k < n; ++k) room = std::min(room, (cs[k]->t_adj - 1) % cs[k]->plan.C + 1);
     for (Split sp(room, tile.ns); sp.next();) {
