@@ -179,6 +179,18 @@ __device__ __forceinline__ Nbr here(const Nbr& b) {
   for (int k = 0; k < 3; ++k) asm("" : "+v"(c.O[k]));
   return c;
 }
+// The same with the row indices made new values too, so that the stores form their rows'
+// scalar addresses again.  Otherwise an in-place kernel keeps those of its loads: the
+// one-shot's two states hold 80 to 160 of them beyond the scalar registers, moved to vector
+// registers and back (131x67x45 MRT with a scalar in FP32, 100 iterations: 4.04 -> 3.39 ms;
+// 450x50x50 7.54 -> 6.58, BGK 6.39 -> 6.28).  A kernel of one state has registers for them, and forming the
+// addresses twice costs it 1-2% (256x128x128 recorded 96.4 -> 99.0 us).
+__device__ __forceinline__ Nbr here_rows(const Nbr& b) {
+  Nbr c = here(b);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) asm("" : "+s"(c.Yr[k]), "+s"(c.Zr[k]));
+  return c;
+}
 // The node's value in a padded node array (w, grad, one moment plane).
 template <typename R>
 __device__ __forceinline__ Global<R> node_at(R* a, const Nbr& b) {
@@ -350,12 +362,13 @@ __device__ __forceinline__ void load_state(const Real* a, const Nbr& b, Real (&f
   }
 }
 
-template <int Q, int QS, typename Real, bool NT, int ACC>
+// ROWS: see here_rows.
+template <int Q, int QS, typename Real, bool NT, int ACC, bool ROWS = false>
 __device__ __forceinline__ void store_state(Real* a, const Nbr& nb, const Real (&f)[Q], const Real (&g)[QS > 0 ? QS : 1]) {
   using L = Lat<Q>;
   using S = SLat<QS>;
   constexpr int QT = Q + QS;
-  const Nbr b = here(nb);
+  const Nbr b = ROWS ? here_rows(nb) : here(nb);
   if constexpr (ACC == ACC_PP) {
 #pragma unroll
     for (int j = 0; j < Q; ++j) put<NT>(own_at<QT>(a, b, j), f[j]);
@@ -421,12 +434,12 @@ __device__ __forceinline__ void load_cot(const Real* a, const Nbr& b, Real (&mu)
   }
 }
 
-template <int Q, int QS, typename Real, bool NT, int ACC>
+template <int Q, int QS, typename Real, bool NT, int ACC, bool ROWS = false>
 __device__ __forceinline__ void store_cot(Real* a, const Nbr& nb, const Real (&lf)[Q], const Real (&lg)[QS > 0 ? QS : 1]) {
   using L = Lat<Q>;
   using S = SLat<QS>;
   constexpr int QT = Q + QS;
-  const Nbr b = here(nb);
+  const Nbr b = ROWS ? here_rows(nb) : here(nb);
   if constexpr (ACC == ACC_PP) {
 #pragma unroll
     for (int j = 0; j < Q; ++j) put<NT>(own_at<QT>(a, b, j), lf[j]);
@@ -2157,12 +2170,12 @@ __global__ __launch_bounds__(256) void k_get_adjoint(Params<Real> p, const Real*
 // restrict on them here (the ping-pong kernel declares it).
 // LX: x-shifted populations of both states through LDS (lds holds the
 // primal's staging runs, then the cotangent's).
-// Both states of a node are held at once, and the registers decide how many waves
-// can wait for memory: the cotangent is finished and stored before the collision,
-// and the classes are one-armed branches.  As one branch per class doing both
-// (280 registers in FP64 with D3Q7, now 251; 128 in FP32, now 104), 100
-// iterations: 96x40x40 with a scalar in FP64 3.00 -> 2.63 ms, 131x67x45 MRT 3.20 ->
-// 2.92, 64x32x32 with a scalar 1.19 -> 1.09; 450x50x50 with a scalar stays at 6.6 to 6.7.
+// Both states of a node are held at once: the cotangent is finished and stored before
+// the collision, and the classes are one-armed branches.  One branch per class doing both
+// took fewer registers (D3Q7 in place: 105 in FP32 where this takes 127, 168 in FP64 where
+// this takes 250) and more time; 100 iterations in place: 96x48x48 with a scalar 1.95 -> 1.87
+// ms, in FP64 3.35 -> 3.11, 64x32x32 1.11 -> 1.03, 131x67x45 MRT 3.08 -> 2.78, 450x50x50 with
+// a scalar 6.37 -> 6.28; 110x100x33 2.11 -> 2.13.
 template <int Q, int QS, typename Real, bool NT, int V, int ACC, bool LX = false>
 __device__ __forceinline__ void oneshot_node(const Params<Real>& p, const Real* prim_in, Real* prim_out,
                                              const Real* lam_in, Real* lam_out, Real* __restrict__ w,
@@ -2192,11 +2205,11 @@ __device__ __forceinline__ void oneshot_node(const Params<Real>& p, const Real* 
 #pragma unroll
       for (int i = 0; i < QS; ++i) nu[i] = lg[i];
     }
-    else store_cot<Q, QS, Real, NT, ACC>(lam_out, b, lf, lg);
+    else store_cot<Q, QS, Real, NT, ACC, ACC != ACC_PP>(lam_out, b, lf, lg);
   };
   const auto keep_state = [&](const auto& fo, const auto& go) {
     if constexpr (kStaged) store_state_lx<Q, QS, Real, NT>(prim_out, b, fo, go, lds, seg, bt);
-    else store_state<Q, QS, Real, NT, ACC>(prim_out, b, fo, go);
+    else store_state<Q, QS, Real, NT, ACC, ACC != ACC_PP>(prim_out, b, fo, go);
   };
   if (cls == WALL) {
     Real lf[Q], lg[QSA];
@@ -2280,9 +2293,11 @@ __global__ __launch_bounds__(kHotThreads) void k_oneshot(Params<Real> p, const R
 }
 
 // One in-place one-shot iteration (even or odd phase): a is the primal buffer,
-// l the adjoint buffer, each read and rewritten in place.
+// l the adjoint buffer, each read and rewritten in place.  Two waves per SIMD at least:
+// only FP64 with D3Q7 and MRT would need more than the 256 registers that allows, by up to 6;
+// it spills 6 (131x67x45, 100 iterations: 8.9 ms with one wave, 5.5 with two).
 template <int Q, int QS, typename Real, bool NT, int V, int ACC, bool LX = false>
-__global__ __launch_bounds__(kHotThreads) void k_oneshot_inplace(Params<Real> p, Real* a, Real* l, Real* __restrict__ w,
+__global__ __launch_bounds__(kHotThreads, 2) void k_oneshot_inplace(Params<Real> p, Real* a, Real* l, Real* __restrict__ w,
                                                          Real* __restrict__ grad, const double* __restrict__ glob,
                                                          Real zeta, Real c_pen) {
   int x, y, z;
