@@ -528,15 +528,15 @@ __device__ __forceinline__ void load_state_lx(const Real* a, const Nbr& nb, Real
   constexpr int QT = Q + QS;
   const Nbr b = here(nb);
   constexpr bool odd = (ACC == ACC_ODD);
-#pragma unroll
-  for (int j = 0; j < Q; ++j)
-    if (L::ex(j) == 0)
-      f[j] = act ? get<NT>(pull_at<QT>(a, b, odd ? L::opp(j) : j, L::ex(j), L::ey(j), L::ez(j))) : Real(0);
-#pragma unroll
-  for (int i = 0; i < QS; ++i)
-    if (S::ex(i) == 0)
-      g[i] = act ? get<NT>(pull_at<QT>(a, b, Q + (odd ? S::opp(i) : i), S::ex(i), S::ey(i), S::ez(i))) : Real(0);
   if (act) {
+#pragma unroll
+    for (int j = 0; j < Q; ++j)
+      if (L::ex(j) == 0)
+        f[j] = get<NT>(pull_at<QT>(a, b, odd ? L::opp(j) : j, L::ex(j), L::ey(j), L::ez(j)));
+#pragma unroll
+    for (int i = 0; i < QS; ++i)
+      if (S::ex(i) == 0)
+        g[i] = get<NT>(pull_at<QT>(a, b, Q + (odd ? S::opp(i) : i), S::ex(i), S::ey(i), S::ez(i)));
 #pragma unroll
     for (int j = 0; j < Q; ++j)
       if (L::ex(j) != 0)
@@ -549,12 +549,13 @@ __device__ __forceinline__ void load_state_lx(const Real* a, const Nbr& nb, Real
             get<NTS>(lane_at(run_at<QT>(a, b, Q + (odd ? S::opp(i) : i), -S::ey(i), -S::ez(i)), b.O[1]));
   }
   __syncthreads();
+  if (!act) return;
 #pragma unroll
   for (int j = 0; j < Q; ++j)
-    if (L::ex(j) != 0) f[j] = act ? lds[H::flow_slot(j) * bt + seg + b.X[1 - L::ex(j)]] : Real(0);
+    if (L::ex(j) != 0) f[j] = lds[H::flow_slot(j) * bt + seg + b.X[1 - L::ex(j)]];
 #pragma unroll
   for (int i = 0; i < QS; ++i)
-    if (S::ex(i) != 0) g[i] = act ? lds[H::scalar_slot(i) * bt + seg + b.X[1 - S::ex(i)]] : Real(0);
+    if (S::ex(i) != 0) g[i] = lds[H::scalar_slot(i) * bt + seg + b.X[1 - S::ex(i)]];
 }
 
 // Stores of the odd in-place phase (pushed to x + e_j) with the x-shifted
@@ -617,15 +618,15 @@ __device__ __forceinline__ void load_cot_lx(const Real* a, const Nbr& nb, Real (
   constexpr int QT = Q + QS;
   const Nbr b = here(nb);
   constexpr bool odd = (ACC == ACC_ODD);
-#pragma unroll
-  for (int j = 0; j < Q; ++j)
-    if (L::ex(j) == 0)
-      mu[j] = act ? get<NT>(push_at<QT>(a, b, odd ? L::opp(j) : j, L::ex(j), L::ey(j), L::ez(j))) : Real(0);
-#pragma unroll
-  for (int i = 0; i < QS; ++i)
-    if (S::ex(i) == 0)
-      nu[i] = act ? get<NT>(push_at<QT>(a, b, Q + (odd ? S::opp(i) : i), S::ex(i), S::ey(i), S::ez(i))) : Real(0);
   if (act) {
+#pragma unroll
+    for (int j = 0; j < Q; ++j)
+      if (L::ex(j) == 0)
+        mu[j] = get<NT>(push_at<QT>(a, b, odd ? L::opp(j) : j, L::ex(j), L::ey(j), L::ez(j)));
+#pragma unroll
+    for (int i = 0; i < QS; ++i)
+      if (S::ex(i) == 0)
+        nu[i] = get<NT>(push_at<QT>(a, b, Q + (odd ? S::opp(i) : i), S::ex(i), S::ey(i), S::ez(i)));
 #pragma unroll
     for (int j = 0; j < Q; ++j)
       if (L::ex(j) != 0)
@@ -638,12 +639,13 @@ __device__ __forceinline__ void load_cot_lx(const Real* a, const Nbr& nb, Real (
             get<NTS>(lane_at(run_at<QT>(a, b, Q + (odd ? S::opp(i) : i), S::ey(i), S::ez(i)), b.O[1]));
   }
   __syncthreads();
+  if (!act) return;
 #pragma unroll
   for (int j = 0; j < Q; ++j)
-    if (L::ex(j) != 0) mu[j] = act ? lds[H::flow_slot(j) * bt + seg + b.X[1 + L::ex(j)]] : Real(0);
+    if (L::ex(j) != 0) mu[j] = lds[H::flow_slot(j) * bt + seg + b.X[1 + L::ex(j)]];
 #pragma unroll
   for (int i = 0; i < QS; ++i)
-    if (S::ex(i) != 0) nu[i] = act ? lds[H::scalar_slot(i) * bt + seg + b.X[1 + S::ex(i)]] : Real(0);
+    if (S::ex(i) != 0) nu[i] = lds[H::scalar_slot(i) * bt + seg + b.X[1 + S::ex(i)]];
 }
 
 // Cotangent stores of the odd in-place pattern (lambda_j(x) to slot j of
