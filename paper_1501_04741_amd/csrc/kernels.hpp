@@ -518,6 +518,10 @@ __device__ __forceinline__ int lx_span() { return blockDim.x * blockDim.y; }
 // two phases (0.89 plain against 0.78 hinted); for states far beyond the cache
 // the in-place adjoint takes it (8 x 128x96x96 batched: 0.79 -> 0.81) and the
 // in-place primal does not (FP64 256x128x128: 0.768 -> 0.738 with it).
+// All loads of a lane sit in one branch.  As loads under a condition each, they became a
+// branch each, and the D3Q7 cotangent's waited for some before it asked for the others
+// (FP32 ping-pong adjoint, us a step: 96x48x48 14.2 -> 12.8, 128x64x64 25.2 -> 24.0).
+// Padding lanes keep no values: nothing reads them.
 template <int Q, int QS, typename Real, int ACC, bool NT, bool NTS>
 __device__ __forceinline__ void load_state_lx(const Real* a, const Nbr& nb, Real (&f)[Q], Real (&g)[QS > 0 ? QS : 1],
                                               Real* lds, int seg, int bt, bool act) {
@@ -1138,10 +1142,14 @@ __device__ __forceinline__ void boundary_moments(const Params<Real>& p, int cls,
 
 // The node operator of an interior, inlet or outlet node: its pre-collision
 // populations (f, g) become the post-collision ones; with MOM its moments m too.
-// The classes are one-armed branches that the compiler may not join (the empty asm
-// hides that they exclude each other): in an if-else chain the populations of the
-// lanes still to come stay live beside the finished ones, two sets of registers
-// (D3Q19 FP32 72 VGPRs instead of 52, 102 instead of 86 in FP64).
+// The classes are one-armed branches: in an if-else chain the populations of the lanes
+// still to come stay live beside the finished ones, two sets of registers (D3Q19 FP32 72
+// VGPRs instead of 52, 102 instead of 86 in FP64).  The empty asm hides from the compiler
+// that they exclude each other, so that it does not join them.  That is not for registers:
+// without it the kernels that are not staged take fewer (58 -> 50 in FP32, with D3Q7 74 ->
+// 63).  It is for time, which is lost without it where it matters most (recorded, us a step:
+// 96x48x48 with MRT 10.0 -> 10.9, in place with D3Q7 and MRT 11.3 -> 12.4, 110x100x33 with
+// MRT 13.1 -> 13.8; won on lattices of some thousand nodes, 33x17x13 7.1 -> 6.7).
 template <int Q, int QS, typename Real, bool MOM, int V>
 __device__ __forceinline__ void primal_open(const Params<Real>& p, int cls, Real wn, const SwitchValues<Real>& sw,
                                             int y, int z, Real (&f)[Q], Real (&g)[QS > 0 ? QS : 1],
@@ -1839,8 +1847,9 @@ __device__ __forceinline__ void adjoint_outlet(const Params<Real>& p, const Real
 // moments m: the cotangents (mu, nu) of its post-collision populations become
 // those of the pre-collision ones; gw is the gradient term (zero except at
 // interior nodes).  Branches as in primal_open (as an if-else chain: 96x48x48
-// evaluation 9.26 -> 9.56 ms, 2D tiles 3% slower).
-template <int Q, int QS, typename Real, int V>
+// evaluation 9.26 -> 9.56 ms, 2D tiles 3% slower).  APART: the empty asm between them as
+// there; see adjoint_node for who takes it.
+template <int Q, int QS, typename Real, int V, bool APART>
 __device__ __forceinline__ void adjoint_open(const Params<Real>& p, int cls, Real wn,
                                              const SwitchValues<Real>& sw, const Real (&m)[Mom<Q, QS, V>::N], Real (&mu)[Q],
                                              Real (&nu)[QS > 0 ? QS : 1], Real& gw) {
@@ -1862,13 +1871,13 @@ __device__ __forceinline__ void adjoint_open(const Params<Real>& p, int cls, Rea
     adjoint_interior<Q, QS, Real, V>(p, a, g, wn, mu, nu, lf, lg, gw);
     keep(lf, lg);
   }
-  asm("" : "+v"(cls));
+  if constexpr (APART) asm("" : "+v"(cls));
   if (cls == INLET) {
     Real lf[Q], lg[QS > 0 ? QS : 1];
     adjoint_inlet<Q, QS, Real, V>(p, m, mu, nu, lf, lg);
     keep(lf, lg);
   }
-  asm("" : "+v"(cls));
+  if constexpr (APART) asm("" : "+v"(cls));
   if (cls == OUTLET) {
     Real lf[Q], lg[QS > 0 ? QS : 1];
     adjoint_outlet<Q, QS, Real, V>(p, m, mu, nu, lf, lg);
@@ -1893,7 +1902,7 @@ struct AdjointInputs {
     g0 = *node_at(grad, b);
   }
 };
-template <int Q, int QS, typename Real, int V, class Done>
+template <int Q, int QS, typename Real, int V, bool APART, class Done>
 __device__ __forceinline__ void adjoint_operator(const Params<Real>& p, int cls, const Nbr& nb,
                                                  const AdjointInputs<Q, QS, Real, V>& in, Real* __restrict__ grad,
                                                  int x, int y, Real (&mu)[Q], Real (&nu)[QS > 0 ? QS : 1],
@@ -1906,7 +1915,7 @@ __device__ __forceinline__ void adjoint_operator(const Params<Real>& p, int cls,
   }
   if (cls == PAD) return;
   Real gw;
-  adjoint_open<Q, QS, Real, V>(p, cls, in.wn, switch_values(p, in.wn), in.m, mu, nu, gw);
+  adjoint_open<Q, QS, Real, V, APART>(p, cls, in.wn, switch_values(p, in.wn), in.m, mu, nu, gw);
   if (cls == INTERIOR) *node_at(grad, here(nb)) = in.g0 + gw;
   done(mu, nu);
 }
@@ -1942,7 +1951,15 @@ __device__ __forceinline__ void adjoint_node(const Params<Real>& p, const Real* 
   if (!LX && cls != WALL && cls != PAD) in.load(p, b, mom, w, grad);
   constexpr bool kStaged = LX && ACC == ACC_ODD;
   if constexpr (kStaged) __syncthreads();
-  adjoint_operator<Q, QS, Real, V>(p, cls, b, in, grad, x, y, mu, nu, [&](const auto& lf, const auto& lg) {
+  // Branches held apart only where shifted populations are loaded without staging, MRT
+  // excepted: elsewhere the empty asm costs registers and with them waves (in place, even
+  // pattern, VGPRs with it and without: D3Q19 FP32 73 / 63, with D3Q7 90 / 68, in FP64 146 /
+  // 118 and 176 / 142) and time (us a step: 96x48x48 with D3Q7 and MRT in place 15.8 / 14.8,
+  // 128x64x64 with MRT 22.1 / 21.0, FP64 192x96x96 in place with D3Q7 127.6 / 123.5, blended
+  // 139.1 / 134.1).  Rows too wide for staging are faster with it (352x50x50 with D3Q7 in FP64
+  // 72.2 / 75.0, 450x50x50 38.6 / 39.4).
+  constexpr bool kApart = !LX && ACC != ACC_EVEN && !(V & kVarMRT);
+  adjoint_operator<Q, QS, Real, V, kApart>(p, cls, b, in, grad, x, y, mu, nu, [&](const auto& lf, const auto& lg) {
     if constexpr (kStaged) {
       stage_cot_lx<Q, QS, Real>(b, lf, lg, lds, seg, bt);
 #pragma unroll

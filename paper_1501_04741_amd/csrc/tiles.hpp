@@ -177,7 +177,8 @@ __device__ __forceinline__ void tile_adjoint(const Params<Real>& p, const Real* 
         for (int i = 0; i < QS; ++i) nu[i] = lg[i];
       } else {
         Real gw;
-        adjoint_open<Q, QS, Real, V>(p, cls, wn, sw, m, mu, nu, gw);
+        // branches held apart: 87 VGPRs with D2Q5 blended (91 without), in FP64 126 (138)
+        adjoint_open<Q, QS, Real, V, true>(p, cls, wn, sw, m, mu, nu, gw);
         gsum += gw;
       }
     }
