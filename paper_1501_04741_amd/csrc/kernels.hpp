@@ -518,10 +518,14 @@ __device__ __forceinline__ int lx_span() { return blockDim.x * blockDim.y; }
 // two phases (0.89 plain against 0.78 hinted); for states far beyond the cache
 // the in-place adjoint takes it (8 x 128x96x96 batched: 0.79 -> 0.81) and the
 // in-place primal does not (FP64 256x128x128: 0.768 -> 0.738 with it).
-// All loads of a lane sit in one branch.  As loads under a condition each, they became a
+// Ping-pong, all loads of a lane sit in one branch: under a condition each they became a
 // branch each, and the D3Q7 cotangent's waited for some before it asked for the others
-// (FP32 ping-pong adjoint, us a step: 96x48x48 14.2 -> 12.8, 128x64x64 25.2 -> 24.0).
-// Padding lanes keep no values: nothing reads them.
+// (FP32, us a step: adjoint with D3Q7 at 96x48x48 14.0 -> 12.5, at 128x64x64 24.9 -> 23.4;
+// recorded primal with D3Q7 at 96x48x48 11.1 -> 9.5, D3Q19 8.8 -> 8.1).  Padding lanes then
+// keep no values: nothing reads them.  In place a branch each stays: the odd phase gains
+// from one at 96x48x48 (primal with D3Q7 9.9 -> 9.3) and loses at larger sizes (recorded
+// 128x64x64 17.2 -> 18.0 with the registers of one wave more, adjoint at 192x96x96 with D3Q7
+// 63.7 -> 64.6, D3Q19 49.2 -> 49.8).
 template <int Q, int QS, typename Real, int ACC, bool NT, bool NTS>
 __device__ __forceinline__ void load_state_lx(const Real* a, const Nbr& nb, Real (&f)[Q], Real (&g)[QS > 0 ? QS : 1],
                                               Real* lds, int seg, int bt, bool act) {
@@ -532,15 +536,19 @@ __device__ __forceinline__ void load_state_lx(const Real* a, const Nbr& nb, Real
   constexpr int QT = Q + QS;
   const Nbr b = here(nb);
   constexpr bool odd = (ACC == ACC_ODD);
-  if (act) {
+  constexpr bool kOneBranch = ACC == ACC_PP;
+  if (!kOneBranch || act) {
 #pragma unroll
     for (int j = 0; j < Q; ++j)
       if (L::ex(j) == 0)
-        f[j] = get<NT>(pull_at<QT>(a, b, odd ? L::opp(j) : j, L::ex(j), L::ey(j), L::ez(j)));
+        f[j] = kOneBranch || act ? get<NT>(pull_at<QT>(a, b, odd ? L::opp(j) : j, L::ex(j), L::ey(j), L::ez(j))) : Real(0);
 #pragma unroll
     for (int i = 0; i < QS; ++i)
       if (S::ex(i) == 0)
-        g[i] = get<NT>(pull_at<QT>(a, b, Q + (odd ? S::opp(i) : i), S::ex(i), S::ey(i), S::ez(i)));
+        g[i] = kOneBranch || act ? get<NT>(pull_at<QT>(a, b, Q + (odd ? S::opp(i) : i), S::ex(i), S::ey(i), S::ez(i)))
+                                   : Real(0);
+  }
+  if (act) {
 #pragma unroll
     for (int j = 0; j < Q; ++j)
       if (L::ex(j) != 0)
@@ -553,13 +561,13 @@ __device__ __forceinline__ void load_state_lx(const Real* a, const Nbr& nb, Real
             get<NTS>(lane_at(run_at<QT>(a, b, Q + (odd ? S::opp(i) : i), -S::ey(i), -S::ez(i)), b.O[1]));
   }
   __syncthreads();
-  if (!act) return;
+  if (kOneBranch && !act) return;
 #pragma unroll
   for (int j = 0; j < Q; ++j)
-    if (L::ex(j) != 0) f[j] = lds[H::flow_slot(j) * bt + seg + b.X[1 - L::ex(j)]];
+    if (L::ex(j) != 0) f[j] = kOneBranch || act ? lds[H::flow_slot(j) * bt + seg + b.X[1 - L::ex(j)]] : Real(0);
 #pragma unroll
   for (int i = 0; i < QS; ++i)
-    if (S::ex(i) != 0) g[i] = lds[H::scalar_slot(i) * bt + seg + b.X[1 - S::ex(i)]];
+    if (S::ex(i) != 0) g[i] = kOneBranch || act ? lds[H::scalar_slot(i) * bt + seg + b.X[1 - S::ex(i)]] : Real(0);
 }
 
 // Stores of the odd in-place phase (pushed to x + e_j) with the x-shifted
@@ -622,15 +630,19 @@ __device__ __forceinline__ void load_cot_lx(const Real* a, const Nbr& nb, Real (
   constexpr int QT = Q + QS;
   const Nbr b = here(nb);
   constexpr bool odd = (ACC == ACC_ODD);
-  if (act) {
+  constexpr bool kOneBranch = ACC == ACC_PP;
+  if (!kOneBranch || act) {
 #pragma unroll
     for (int j = 0; j < Q; ++j)
       if (L::ex(j) == 0)
-        mu[j] = get<NT>(push_at<QT>(a, b, odd ? L::opp(j) : j, L::ex(j), L::ey(j), L::ez(j)));
+        mu[j] = kOneBranch || act ? get<NT>(push_at<QT>(a, b, odd ? L::opp(j) : j, L::ex(j), L::ey(j), L::ez(j))) : Real(0);
 #pragma unroll
     for (int i = 0; i < QS; ++i)
       if (S::ex(i) == 0)
-        nu[i] = get<NT>(push_at<QT>(a, b, Q + (odd ? S::opp(i) : i), S::ex(i), S::ey(i), S::ez(i)));
+        nu[i] = kOneBranch || act ? get<NT>(push_at<QT>(a, b, Q + (odd ? S::opp(i) : i), S::ex(i), S::ey(i), S::ez(i)))
+                                   : Real(0);
+  }
+  if (act) {
 #pragma unroll
     for (int j = 0; j < Q; ++j)
       if (L::ex(j) != 0)
@@ -643,13 +655,13 @@ __device__ __forceinline__ void load_cot_lx(const Real* a, const Nbr& nb, Real (
             get<NTS>(lane_at(run_at<QT>(a, b, Q + (odd ? S::opp(i) : i), S::ey(i), S::ez(i)), b.O[1]));
   }
   __syncthreads();
-  if (!act) return;
+  if (kOneBranch && !act) return;
 #pragma unroll
   for (int j = 0; j < Q; ++j)
-    if (L::ex(j) != 0) mu[j] = lds[H::flow_slot(j) * bt + seg + b.X[1 + L::ex(j)]];
+    if (L::ex(j) != 0) mu[j] = kOneBranch || act ? lds[H::flow_slot(j) * bt + seg + b.X[1 + L::ex(j)]] : Real(0);
 #pragma unroll
   for (int i = 0; i < QS; ++i)
-    if (S::ex(i) != 0) nu[i] = lds[H::scalar_slot(i) * bt + seg + b.X[1 + S::ex(i)]];
+    if (S::ex(i) != 0) nu[i] = kOneBranch || act ? lds[H::scalar_slot(i) * bt + seg + b.X[1 + S::ex(i)]] : Real(0);
 }
 
 // Cotangent stores of the odd in-place pattern (lambda_j(x) to slot j of
@@ -1951,14 +1963,15 @@ __device__ __forceinline__ void adjoint_node(const Params<Real>& p, const Real* 
   if (!LX && cls != WALL && cls != PAD) in.load(p, b, mom, w, grad);
   constexpr bool kStaged = LX && ACC == ACC_ODD;
   if constexpr (kStaged) __syncthreads();
-  // Branches held apart only where shifted populations are loaded without staging, MRT
-  // excepted: elsewhere the empty asm costs registers and with them waves (in place, even
-  // pattern, VGPRs with it and without: D3Q19 FP32 73 / 63, with D3Q7 90 / 68, in FP64 146 /
-  // 118 and 176 / 142) and time (us a step: 96x48x48 with D3Q7 and MRT in place 15.8 / 14.8,
-  // 128x64x64 with MRT 22.1 / 21.0, FP64 192x96x96 in place with D3Q7 127.6 / 123.5, blended
-  // 139.1 / 134.1).  Rows too wide for staging are faster with it (352x50x50 with D3Q7 in FP64
-  // 72.2 / 75.0, 450x50x50 38.6 / 39.4).
-  constexpr bool kApart = !LX && ACC != ACC_EVEN && !(V & kVarMRT);
+  // Where the branches are held apart.  The empty asm costs registers and with them waves (in
+  // place, even pattern, VGPRs with it and without: with D3Q7 90 / 68, in FP64 176 / 142) and
+  // time (us a step: 96x48x48 with D3Q7 and MRT in place 15.8 / 14.8, 128x64x64 with MRT 22.1 /
+  // 21.0, FP64 192x96x96 in place with D3Q7 127.6 / 123.5, blended 139.1 / 134.1), but for two
+  // kinds: shifted populations loaded without staging (352x50x50 with D3Q7 in FP64 72.2 /
+  // 75.0, 450x50x50 38.6 / 39.4), and D3Q19 alone in FP32 in place, which has waves enough (73
+  // / 63 VGPRs; 256x64x64 29.8 / 30.2; ping-pong 96x48x48 10.5 / 10.0).
+  constexpr bool kPlain = !LX && ACC != ACC_EVEN;
+  constexpr bool kApart = !(V & kVarMRT) && (kPlain || (QS == 0 && sizeof(Real) == 4 && ACC != ACC_PP));
   adjoint_operator<Q, QS, Real, V, kApart>(p, cls, b, in, grad, x, y, mu, nu, [&](const auto& lf, const auto& lg) {
     if constexpr (kStaged) {
       stage_cot_lx<Q, QS, Real>(b, lf, lg, lds, seg, bt);
