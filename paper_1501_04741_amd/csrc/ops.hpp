@@ -14,6 +14,7 @@ template <int Q, int QS, typename Real, int V>
 struct Ops {
   using RealT = Real;
   static constexpr int kQ = Q, kQS = QS;
+  static constexpr bool kLx = !(V & kVarMRT);  // staged kernels; MRT keeps the plain access (see lx_rows)
   static Params<Real> P(lbm_ctx* c) { return make_params<Real>(c->cfg, c->plan.N); }
   static int batch_blocks(lbm_ctx* c, int kw, int rpb) {
     const int rows = c->cfg.ny * c->cfg.nz;
@@ -22,7 +23,6 @@ struct Ops {
   // batched steps in access pattern acc (ping-pong, or one in-place phase)
   template <bool NTV, bool MOMV>
   static void primal_batch_acc(hipStream_t st, const BatchArgs<Real>& A, dim3 g, dim3 b, int acc) {
-    constexpr bool kLx = !(V & kVarMRT);  // the MRT kernels keep the plain access (see lx_rows)
     if (acc == ACC_EVEN && NTV && A.nte)
       hipLaunchKernelGGL((k_primal_batch<Q, QS, Real, V, NTV, MOMV, ACC_EVEN, true>), g, b, 0, st, A);
     else if (acc == ACC_EVEN) hipLaunchKernelGGL((k_primal_batch<Q, QS, Real, V, NTV, MOMV, ACC_EVEN>), g, b, 0, st, A);
@@ -43,24 +43,19 @@ struct Ops {
       else primal_batch_acc<false, false>(st, A, g, b, acc);
     }
   }
-  template <bool NTV>
-  static void adjoint_batch_acc(hipStream_t st, const BatchArgs<Real>& A, dim3 g, dim3 b, int acc) {
-    constexpr bool kLx = !(V & kVarMRT);  // the MRT kernels keep the plain access (see lx_rows)
-    if (acc == ACC_EVEN && NTV && A.nte)
-      hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, NTV, ACC_EVEN, true>), g, b, 0, st, A);
-    else if (acc == ACC_EVEN) hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, NTV, ACC_EVEN>), g, b, 0, st, A);
-    else if (acc == ACC_ODD && A.lx && A.nte)
-      hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, NTV, ACC_ODD, true, kLx>), g, b, 0, st, A);
-    else if (acc == ACC_ODD && A.lx)
-      hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, NTV, ACC_ODD, false, kLx>), g, b, 0, st, A);
-    else if (acc == ACC_ODD) hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, NTV, ACC_ODD>), g, b, 0, st, A);
-    else if (A.lx) hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, NTV, ACC_PP, false, kLx>), g, b, 0, st, A);
-    else hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, NTV, ACC_PP>), g, b, 0, st, A);
-  }
+  // streaming stores and hints whatever the state size (see adjoint_inplace)
   static void adjoint_batch(hipStream_t st, const BatchArgs<Real>& A, int blocks, int acc = ACC_PP) {
     const dim3 g(blocks), b(kWave * A.kw * A.rpb);
-    if (A.nt) adjoint_batch_acc<true>(st, A, g, b, acc);
-    else adjoint_batch_acc<false>(st, A, g, b, acc);
+    if (acc == ACC_EVEN && A.nte)
+      hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, true, ACC_EVEN, true>), g, b, 0, st, A);
+    else if (acc == ACC_EVEN) hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, true, ACC_EVEN>), g, b, 0, st, A);
+    else if (acc == ACC_ODD && A.lx && A.nte)
+      hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, true, ACC_ODD, true, kLx>), g, b, 0, st, A);
+    else if (acc == ACC_ODD && A.lx)
+      hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, true, ACC_ODD, false, kLx>), g, b, 0, st, A);
+    else if (acc == ACC_ODD) hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, true, ACC_ODD>), g, b, 0, st, A);
+    else if (A.lx) hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, true, ACC_PP, false, kLx>), g, b, 0, st, A);
+    else hipLaunchKernelGGL((k_adjoint_batch<Q, QS, Real, V, true, ACC_PP>), g, b, 0, st, A);
   }
 
   // ---- several steps per launch (2D tiles, tiles.hpp)
@@ -230,7 +225,7 @@ struct Ops {
 #define LBM_PI(NTV, MOMV, ACCV)                                                                                    \
   do {                                                                                                             \
     if (ACCV == ACC_ODD && lx)                                                                                     \
-      hipLaunchKernelGGL((k_primal_inplace<Q, QS, Real, NTV, MOMV, V, ACC_ODD, false, true>), g.grid, g.block,     \
+      hipLaunchKernelGGL((k_primal_inplace<Q, QS, Real, NTV, MOMV, V, ACC_ODD, false, kLx>), g.grid, g.block,     \
                          lx_bytes(g, 1), c->stream, P(c), a, w, m);                                                \
     else                                                                                                           \
       hipLaunchKernelGGL((k_primal_inplace<Q, QS, Real, NTV, MOMV, V, ACCV>), g.grid, g.block, 0, c->stream, P(c), \
@@ -274,7 +269,7 @@ struct Ops {
 #define LBM_OS_INPLACE(NTV, ACCV)                                                                                 \
   do {                                                                                                            \
     if (ACCV == ACC_ODD && lx)                                                                                    \
-      hipLaunchKernelGGL((k_oneshot_inplace<Q, QS, Real, NTV, V, ACC_ODD, true>), g.grid, g.block, lx_bytes(g, 2),  \
+      hipLaunchKernelGGL((k_oneshot_inplace<Q, QS, Real, NTV, V, ACC_ODD, kLx>), g.grid, g.block, lx_bytes(g, 2),  \
                          c->stream, P(c), a, l, w, gr, gl, (Real)zeta, (Real)pen);                                \
     else                                                                                                          \
       hipLaunchKernelGGL((k_oneshot_inplace<Q, QS, Real, NTV, V, ACCV>), g.grid, g.block, 0, c->stream, P(c), a, l, \
@@ -310,7 +305,7 @@ struct Ops {
 #define LBM_PP(NTV, MOMV)                                                                                     \
   do {                                                                                                        \
     if (Ops::lx(c, g, 1))                                                                                     \
-      hipLaunchKernelGGL((k_primal<Q, QS, Real, NTV, MOMV, V, true>), g.grid, g.block, lx_bytes(g, 1), c->stream,  \
+      hipLaunchKernelGGL((k_primal<Q, QS, Real, NTV, MOMV, V, kLx>), g.grid, g.block, lx_bytes(g, 1), c->stream,  \
                          P(c), s, d, w, m);                                                                   \
     else                                                                                                      \
       hipLaunchKernelGGL((k_primal<Q, QS, Real, NTV, MOMV, V>), g.grid, g.block, 0, c->stream, P(c), s, d, w, m); \
@@ -365,10 +360,10 @@ struct Ops {
 #define LBM_AI(NTV, ACCV)                                                                                         \
   do {                                                                                                            \
     if (ACCV == ACC_ODD && lx && far)                                                                             \
-      hipLaunchKernelGGL((k_adjoint_inplace<Q, QS, Real, NTV, V, ACC_ODD, true, true>), g.grid, g.block,          \
+      hipLaunchKernelGGL((k_adjoint_inplace<Q, QS, Real, NTV, V, ACC_ODD, true, kLx>), g.grid, g.block,          \
                          lx_bytes(g, 1), c->stream, P(c), m, l, w, gr);                                           \
     else if (ACCV == ACC_ODD && lx)                                                                               \
-      hipLaunchKernelGGL((k_adjoint_inplace<Q, QS, Real, NTV, V, ACC_ODD, false, true>), g.grid, g.block,         \
+      hipLaunchKernelGGL((k_adjoint_inplace<Q, QS, Real, NTV, V, ACC_ODD, false, kLx>), g.grid, g.block,         \
                          lx_bytes(g, 1), c->stream, P(c), m, l, w, gr);                                           \
     else                                                                                                          \
       hipLaunchKernelGGL((k_adjoint_inplace<Q, QS, Real, NTV, V, ACCV>), g.grid, g.block, 0, c->stream, P(c), m, l, \
@@ -391,7 +386,7 @@ struct Ops {
     const bool lx = Ops::lx(c, g, 1);
     // streaming whatever the state size, as the in-place adjoint
     if (lx)
-      hipLaunchKernelGGL((k_adjoint<Q, QS, Real, true, V, true>), g.grid, g.block, lx_bytes(g, 1), c->stream, P(c), m,
+      hipLaunchKernelGGL((k_adjoint<Q, QS, Real, true, V, kLx>), g.grid, g.block, lx_bytes(g, 1), c->stream, P(c), m,
                          li, lo, w, gr);
     else
       hipLaunchKernelGGL((k_adjoint<Q, QS, Real, true, V>), g.grid, g.block, 0, c->stream, P(c), m, li, lo, w, gr);
@@ -404,7 +399,7 @@ struct Ops {
     const double* gl = (const double*)c->glob;
     const bool lx = Ops::lx(c, g, 2);
 #define LBM_OS(NTV, LXV)                                                                                   \
-  hipLaunchKernelGGL((k_oneshot<Q, QS, Real, NTV, V, LXV>), g.grid, g.block, LXV ? lx_bytes(g, 2) : 0, c->stream, \
+  hipLaunchKernelGGL((k_oneshot<Q, QS, Real, NTV, V, LXV && kLx>), g.grid, g.block, LXV ? lx_bytes(g, 2) : 0, c->stream, \
                      P(c), s, d, li, lo, w, gr, gl, (Real)zeta, (Real)pen)
     if (nt(c, 4)) {
       if (lx) LBM_OS(true, true);
@@ -924,7 +919,6 @@ lbm_status adjoint_batch_inplace(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64_t
       if (nm == 0) continue;
       const int total = batch_geometry<O>(A, mem, nm, tile, 1);
       batch_nt_inplace(mem, nm, false, false, &A.nt, &A.nte);
-      A.nt = 1;  // the adjoint streams whatever the state size (see Ops::adjoint_inplace)
       for (int k = 0; k < nm; ++k)
         batch_member<O>(A, k, mem[k], mom_slot(mem[k], mem[k]->t_adj - 1), mem[k]->lam[0], mem[k]->lam[0], nullptr);
       O::adjoint_batch(c0->stream, A, total, odd ? ACC_ODD : ACC_EVEN);
@@ -993,7 +987,6 @@ lbm_status RunAdjointBatch<O>::run(lbm_ctx* c0, lbm_ctx* const* cs, int n, int64
   BatchArgs<Real> A;
   std::memset(&A, 0, sizeof A);
   const TileChoice tile = batch_tile_choice<O>(cs, n, nsteps, ADJOINT);
-  A.nt = 1;  // the adjoint streams whatever the state size (see Ops::adjoint_inplace)
   int geometry = 0, total = 0;
   for (int64_t i = 0; i < nsteps;) {
     recompute_batch<O>(c0, cs, n);
