@@ -174,3 +174,35 @@ def test_tiles_of_whole_rows_bitwise_equal_one_step_launches(size, prec, inplace
         one.adjoint_steps(1)
     many.adjoint_steps(16)
     _same(_arrays(one.get_adjoint(), [one.gradient()]), _arrays(many.get_adjoint(), [many.gradient()]))
+
+
+@pytest.mark.parametrize("batch", [False, True], ids=["alone", "batch"])
+@pytest.mark.parametrize("case", [c for c in CASES if c[5]], ids=lambda c: "%dx%d_%s" % (c[1] + c[2:3]))
+def test_recomputed_segments_bitwise_equal_a_run_that_recomputes_nothing(case, batch):
+    """The reference holds every step's moments and takes one step per call; the segments of
+    the others, recomputed in launches of several steps, start at odd and at even times."""
+    p, (nx, ny), prec, inplace, steps, interval = case
+    sizes = [(nx, ny), (nx + 1, ny), (2 * nx, ny + 3)] if batch else [(nx, ny)]
+    whole = [_context(p, s, prec, inplace, steps, steps, k) for k, s in enumerate(sizes)]
+    parts = [_context(p, s, prec, inplace, steps, interval, k) for k, s in enumerate(sizes)]
+    assert whole[0].plan()["interval"] == steps and parts[0].plan()["interval"] == interval
+    handles = [c.ctx for c in parts]
+    for c in whole:
+        for _ in range(steps):
+            c.primal_steps(1, record=True)
+    if batch:
+        L.lbm_primal_steps_batch(handles, steps, record=True)
+    else:
+        parts[0].primal_steps(steps, record=True)
+    for k in (interval + 3, 1, steps - interval - 4):
+        for c in whole:
+            for _ in range(k):
+                c.adjoint_steps(1)
+        if batch:
+            L.lbm_adjoint_steps_batch(handles, k)
+        else:
+            parts[0].adjoint_steps(k)
+        for a, b in zip(whole, parts):
+            _same(_arrays(a.get_adjoint()), _arrays(b.get_adjoint()))
+    for a, b in zip(whole, parts):
+        _same(_arrays([a.gradient()]), _arrays([b.gradient()]))
