@@ -171,6 +171,15 @@ def oneshot_bytes(p, precision):
     return ni * (4 * qt * s + 3 * s) + (nw + nin + nout) * (4 * qt * s + s)
 
 
+def per_step_2d(family, p, precision, us, mode=""):
+    """What the line reports for a 2D lattice in a roofline's place: the time of one step.  Its
+    launches take several steps each, in tiles (where the library's rule says so), and read and
+    write the state once for all of them, so bytes per step over time would be no kernel's
+    bandwidth."""
+    return {"bound": "latency, vector units and caches", "kernel": klabel(family, p, precision, mode),
+            "achieved": None, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": None, "avg_step_us": us}
+
+
 def mixer_leg(dev, steps=4000, os_iters=400):
     """Forward steps and one-shot iterations on the paper's mixing duct (450x50x50
     D3Q19 + D3Q7, pressure inlet with velocity limit, mixing objective), FP32:
@@ -856,6 +865,9 @@ def main(argv=None):
                                  "bytes_per_launch": ob,
                                  "avg_launch_us": os_launch_ms * 1e3}},
     }
+    if p["flow"] == 9:
+        rec["roofline_primal"] = per_step_2d("k_primal_tile", p, prec, primal_launch_ms * 1e3, "recorded")
+        rec["roofline_adjoint"] = per_step_2d("k_adjoint_tile", p, prec, adjoint_launch_ms * 1e3 if k_last > 1 else None)
     # the dominant kernel is the one with more time in an evaluation: N primal launches against
     # N adjoint launches
     adj_dominant = k_last > 1 and adjoint_launch_ms > primal_launch_ms
