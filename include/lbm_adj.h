@@ -310,13 +310,13 @@ lbm_status lbm_plan(const lbm_ctx* ctx, int64_t* interval, int64_t* n_checkpoint
                     int64_t* n_ring, uint64_t* state_bytes);
 
 /* Batched forms for many contexts with the same (flow, scalar, precision):
- * one kernel launch per step covers every context in ctxs (a descriptor
- * table in each context's workspace maps blocks to contexts).  A batch is
- * all ping-pong or all in place (inplace = 1).  Members that differ in
- * collision or in blended diffusivity (tau_s_solid) use different kernels
- * and go in launches of their own; in place, members whose
- * phase differs go in a second launch of the same step, checkpoint copies
- * and recomputed segments run per member.  Every context must be in a state
+ * a kernel launch covers every context in ctxs (a descriptor table in each
+ * context's workspace maps blocks to contexts) and takes one step, or several
+ * of a 2D lattice.  A batch is all ping-pong or all in place (inplace = 1).
+ * Members that differ in collision or in blended diffusivity (tau_s_solid)
+ * use different kernels and go in launches of their own; in place, members
+ * whose phase differs go in a second launch of the same step, checkpoint
+ * copies and recomputed segments run per member.  Every context must be in a state
  * where the single-context call would be valid; the call validates all
  * first and runs none on error.  All contexts must share one stream (that
  * of ctxs[0]).  Results are bitwise identical to the single-context calls.

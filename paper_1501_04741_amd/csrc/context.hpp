@@ -32,7 +32,12 @@
 // it is copied to ckpt[k / C] (in the buffer layout of phase k), and segment s
 // is recomputed in place inside ckpt[s] itself, which the backward sweep needs
 // no more once the segment's moments are rebuilt (segments are reversed in
-// decreasing order, each once).
+// decreasing order, each once).  Launches of several steps (2D lattices) cannot
+// read and rewrite one buffer: they go through another and back, the primal's
+// through the adjoint buffer, free until an adjoint or one-shot iteration starts,
+// the adjoint's and a recomputed segment's through the working buffer, whose state
+// the started adjoint has consumed (calls that read it are refused from then on).
+// Captured calls take one step per launch (see most_in_place).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -374,9 +379,11 @@ constexpr int kHotWaves = 4;
 // part spans a whole row, i.e. nx <= 256.  Measured on the 256x128x128 D3Q19
 // FP32 channel (fraction of HBM peak): recorded in-place primal 0.839 -> 0.892,
 // in-place adjoint 0.846 -> 0.903, ping-pong primal 0.732 -> 0.752, ping-pong
-// adjoint 0.798 -> 0.807; FP64 and the one-shot unchanged.  The MRT kernels
-// (87-90 registers, five waves per SIMD) lose at the barriers (adjoint 0.80 ->
-// 0.75, primal 0.79 -> 0.77) and keep the plain access.
+// adjoint 0.798 -> 0.807; FP64 and the one-shot unchanged.  MRT lengthens the chain that
+// a block's barriers hold together, and loses with staging although its primal would have
+// more waves (FP32 57 VGPRs against 74; us a recorded step, plain / staged: 96x48x48 10.1 /
+// 11.0, 131x67x45 15.2 / 16.1, with D3Q7 18.4 / 24.6, 256x128x128 116.5 / 119.2; the adjoint,
+// 89 VGPRs either way, 0.80 -> 0.75 of peak at 256x128x128): it keeps the plain access.
 inline bool lx_rows(const lbm_config& c) { return c.nx <= kHotThreads && c.collision != LBM_COLL_MRT; }
 
 // Launch geometry of the hot kernels: a row of up to kHotThreads / 64 waves

@@ -13,7 +13,9 @@ Requests of different lattice sizes arrive over time.  The scheduler:
   gradient is ready;
 * on each tick advances, per lattice kind (flow, scalar, precision) and
   per-step cost class (power-of-two state size), all requests in their
-  primal phase by one quantum with ONE batched launch per step, then all
+  primal phase by one quantum with batched launches that cover them all (one per
+  step, or per several steps of a 2D lattice; requests of another collision or
+  blended diffusivity have launches of their own), then all
   requests in their adjoint phase likewise (the adjoint call seeds newcomers
   and recomputes trajectory segments as needed).  With a time quantum, each
   class advances by the number of steps that takes about that much device
