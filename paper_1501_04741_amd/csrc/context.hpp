@@ -452,8 +452,11 @@ inline int batch_lx(lbm_ctx* const* cs, int n, int kw) {
 //    the two that the tiles go through do not.  Recorded 2400x1200 FP32 59.4 against 49.2 us,
 //    2048x1024 FP64 97.9 / 67.6 (S = 1.2 caches still 1.02); unrecorded FP64 1700x850 46.3 / 43.7.
 //  - Blended diffusivity records and reads 8 moment planes.  The adjoint reads them over the
-//    whole region of a tile: 2048x1024 FP32 59.5 / 53.6, in place 59.4 / 47.8, FP64 117.6 / 103.3;
-//    smaller lattices (700x350 FP32 0.90) and FP64 in place (1024x512 0.83) gain.
+//    whole region of a tile.  Ping-pong, FP32 1100x560 16.8 / 19.1, 1400x700 26.0 / 27.0,
+//    1536x768 33.1 / 32.2, 2048x1024 59.5 / 53.6; FP64 600x300 11.9 / 12.9, 760x380 18.0 / 18.6,
+//    900x450 24.3 / 23.6, 2048x1024 117.6 / 103.3.  In place, FP32 800x400 10.6 / 11.8,
+//    1000x500 13.8 / 14.4, 1024x512 16.2 / 14.5, 1152x576 19.1 / 18.1, 2048x1024 59.4 / 47.8;
+//    FP64 gains (1024x512 0.83).
 //  - Rows that end inside a 64-byte piece store moments as parts of one: blended recorded
 //    1400x700 FP32 30.8 with 20-wide tiles, 17.4 with 16-wide ones (one-step 20.4); FP64 in
 //    place takes 16x12 for 12x16 (3000x2000 recorded 281 -> 213, adjoint 238 -> 211).
@@ -470,7 +473,8 @@ inline TileRule tile_rule(lbm_ctx* const* cs, int n, LaunchKind kind) {
   const bool resident = inplace && 2 * s > kLastLevelCacheBytes && s <= most;  // one state is, two are not
   const bool rows = (blended && kind == RECORDED) || (fp64 && inplace);
   if (kind == RECORDED || (kind == STEPS && fp64)) return {!resident, rows};
-  if (kind == ADJOINT && blended) return {fp64 && inplace ? !resident : s <= (fp64 ? 12u : 20u) << 20, rows};
+  if (kind == ADJOINT && blended)
+    return {inplace && fp64 ? !resident : s <= uint64_t(inplace ? 20 : fp64 ? 36 : 56) << 20, rows};
   return {true, rows};
 }
 

@@ -82,7 +82,7 @@ int main() {
   for (int members : {1, 8})
     for (int kind : {STEPS, RECORDED, ADJOINT})
       for (bool fp64 : {false, true})
-        for (uint64_t state : {1 * MB, 24 * MB, 100 * MB, 160 * MB, 256 * MB, 300 * MB, 400 * MB, 2000 * MB}) {
+        for (uint64_t state : {1 * MB, 24 * MB, 48 * MB, 100 * MB, 160 * MB, 256 * MB, 300 * MB, 400 * MB, 2000 * MB}) {
           for (bool inplace : {false, true})  // D2Q9 alone: always, any rows
             CHECK(rule(kind, 0, fp64, inplace, false, state, members).tiles &&
                   !rule(kind, 0, fp64, inplace, false, state, members).whole_rows);
@@ -91,7 +91,7 @@ int main() {
           const TileRule r = rule(kind, 5, fp64, true, false, state, members);
           CHECK(r.tiles == !(most && (kind == RECORDED || (kind == STEPS && fp64))) && r.whole_rows == fp64);
           const TileRule pp = rule(kind, 5, fp64, false, true, state, members);
-          CHECK(pp.tiles == (kind != ADJOINT || state <= (fp64 ? 12 : 20) * MB) && pp.whole_rows == (kind == RECORDED));
+          CHECK(pp.tiles == (kind != ADJOINT || state <= (fp64 ? 36 : 56) * MB) && pp.whole_rows == (kind == RECORDED));
           const TileRule ip = rule(kind, 5, fp64, true, true, state, members);
           if (kind == ADJOINT) CHECK(ip.tiles == (fp64 ? !most : state <= 20 * MB));
           else CHECK(ip.tiles == r.tiles);
