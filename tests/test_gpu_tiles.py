@@ -164,7 +164,7 @@ def test_captured_inplace_adjoint_replays_from_the_recorded_state(batch):
     ((704, 352), "fp64", True, 3.0)], ids=["vd_pp", "vd_ip", "fp64_ip", "fp64_vd_ip"])
 def test_tiles_of_whole_rows_bitwise_equal_one_step_launches(size, prec, inplace, solid):
     """States beyond the L2s with D2Q5: recorded runs (and all in place in FP64) take tiles of
-    whole 64-byte rows, the blended adjoint of these sizes one step per launch."""
+    whole 64-byte rows, the blended FP32 adjoint in place one step per launch."""
     one, many = [_context(dict(HEAT, tau_s_solid=solid), size, prec, inplace, 16, 0, 0) for _ in range(2)]
     for _ in range(16):
         one.primal_steps(1, record=True)
